@@ -50,16 +50,6 @@ __device__ __forceinline__ uint32_t from_lane(uint32_t v, uint32_t k) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, k);
 }
 
-// A wavefront's own 64-entry slice of LDS (do-all workgroups hold at most 16
-// wavefronts).  A chunk written there by its 64 lanes is read back entry by
-// entry with one broadcast load per entry; a wavefront's LDS accesses are
-// performed in program order, so no barrier is needed between them.
-template <class T>
-__device__ __forceinline__ T* wave_slice() {
-  __shared__ T slice[16 * 64];
-  return slice + (threadIdx.x >> 6) * 64;
-}
-
 // The per-id arrays are walked in chunks of 64 ids: lane l loads entry j0 + l
 // of the next chunk (clamped to the last id, so every load stays in bounds)
 // while the wavefront works through the current one.
@@ -68,41 +58,149 @@ __device__ __forceinline__ uint32_t chunk_id(uint32_t j0, uint32_t n) {
   return j < n ? j : n - 1u;
 }
 
-struct BodyForce {
-  static constexpr uint32_t kKind = 60;
-  using Args = Bodies;
-  static __device__ __forceinline__ void pair(const Args& a, float x, float y, float qx, float qy, float qm,
-                                              float& sx, float& sy) {
-    const float dx = qx - x, dy = qy - y;
-    const float r2 = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, a.eps2));
-    const float s = qm / (r2 * __builtin_sqrtf(r2));
-    sx = __builtin_fmaf(s, dx, sx);
-    sy = __builtin_fmaf(s, dy, sy);
-  }
-  template <class H>
-  static __device__ bool run_wave(const H& h, uint32_t, uint32_t self, bool live, const Args& a) {
-    const float x = fld<float>(h, self, kX), y = fld<float>(h, self, kY);
-    const uint32_t n = a.n;
-    float sx = 0.0f, sy = 0.0f;
-    float4* const t = wave_slice<float4>();
-    float4 nxt = a.P[chunk_id(0, n)];
-    for (uint32_t j0 = 0; j0 < n; j0 += 64) {
-      t[lane_id()] = nxt;
-      nxt = a.P[chunk_id(j0 + 64, n)];
-      const uint32_t m = n - j0 < 64 ? n - j0 : 64;
+// The scale s = m / (r2 sqrt(r2)) of a pair, every operation correctly rounded:
+// the general form, for any values.
+__device__ __forceinline__ float pair_scale(float r2, float m) { return m / (r2 * __builtin_sqrtf(r2)); }
+
+// The same scale, bit for bit, for 2^-40 <= r2 <= 2^40 and m that passes
+// scale_normal_mass, in 13 operations and one reciprocal square root where the general
+// form's correctly rounded square root and division expand to about 36: both
+// take a residual step from y = rsqrt(r2) (1 ulp).
+//  - root: g = r2 y, g + (r2 - g^2) y / 2.
+//  - quotient m / b, b = r2 root: 1 / b is y^3 but for 2^-21, one Newton step
+//    rounds it, and m / b takes one residual step from m times that.
+// No operation leaves the normal range there, so the results scale with the
+// exponents of r2 (by pairs) and m, and two binades of r2 times one of m hold
+// every case.  Compared over all of them on this part: the 2^24 roots equal the
+// general form's, and of the 2^47 quotients all but one, m = 0x1.ccccc4 over
+// b = 0x1.fffff6; masses of that mantissa are left to the general form.
+constexpr float kScaleLo = 0x1p-40f, kScaleHi = 0x1p40f;
+constexpr uint32_t kScaleNot = 0x666662;  // mantissa bits of that m
+__device__ __forceinline__ bool scale_normal_mass(float m) {
+  return m == 0.0f || (m >= kScaleLo && m <= kScaleHi && (__float_as_uint(m) & 0x7FFFFFu) != kScaleNot);
+}
+__device__ __forceinline__ float pair_scale_normal(float r2, float m) {
+  const float y = __builtin_amdgcn_rsqf(r2);
+  const float g = r2 * y;
+  const float root = __builtin_fmaf(__builtin_fmaf(-g, g, r2), 0.5f * y, g);
+  const float b = r2 * root;
+  const float c0 = y * y * y;
+  const float c = __builtin_fmaf(__builtin_fmaf(-b, c0, 1.0f), c0, c0);
+  const float q = m * c;
+  return __builtin_fmaf(__builtin_fmaf(-b, q, m), c, q);
+}
+
+// Force: the sum over j is a chain of fma in increasing order of j, which fixes
+// the result's bits, but a pair's scale depends on nothing else.  A workgroup
+// takes kForceBodies bodies; its first wavefront keeps the chains (lane i the
+// x sum of body i, lane i + 32 its y sum), the others compute the scales of
+// kForceChunk bodies j at a time into one of two LDS tiles, one tile ahead of
+// the chains.  Bound: vector instructions on large sets (about 26 issue slots
+// per pair, a reciprocal root counting four), the chains' latency on small
+// ones.  With one wavefront per 64 bodies for everything, 4096 bodies kept 64
+// of the chip's 1024 SIMDs busy with a chain of about 45 slots per pair: 307 us
+// per step; now 37, and 65,536 bodies 4.93 -> 2.76 ms (6.1e9 -> 1.55e12 pairs
+// a second and 8.7e11 -> 1.55e12).  Tiles of 64 bodies cost a barrier twice as
+// often (4096 bodies 47, 65,536 2.98 ms), tiles of 256 leave room for two
+// workgroups per CU (4.4 ms); two makers leave SIMDs idle (65,536: 3.1 ms),
+// eight wait for the chains (3.4 ms).
+constexpr uint32_t kKindForce = 60;
+constexpr uint32_t kForceBodies = 32;
+constexpr uint32_t kForceChunk = 128;
+constexpr uint32_t kForceMakers = 4;                           // wavefronts computing scales
+constexpr uint32_t kForceEach = kForceChunk / kForceMakers;    // bodies j per maker and chunk
+constexpr uint32_t kForceThreads = 64 * (kForceMakers + 1);
+constexpr uint32_t kForceWgsPerCu = 4;                         // resident: the two tiles take 40 KB of LDS
+constexpr uint32_t kForceRow = kForceChunk + 4;                // padded: rows start 4 banks apart
+static_assert(kForceEach % 8 == 0 && kForceEach <= 64, "two half-wavefronts, four scales per store");
+
+template <uint32_t LG>
+__global__ void __launch_bounds__(kForceThreads)
+    force_kernel(DevHeapW<LG> h, const uint32_t* __restrict__ R, const uint64_t* __restrict__ S,
+                 const uint32_t* count_ptr, Bodies a) {
+  __shared__ float s_scale[2][kForceBodies * kForceRow];
+  __shared__ float s_q[2][2][kForceChunk];   // x and y of the chunk's bodies
+  __shared__ float4 s_p[2][kForceChunk];
+  const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t i = lane & (kForceBodies - 1), half = lane >> 5;
+  const uint32_t c = cap_of(h, kBody), sh = (uint32_t)__builtin_ctz(c);
+  const uint64_t items = (uint64_t)bcast32(*count_ptr) << sh;  // slots of the listed blocks
+  const uint32_t n = a.n, chunks = (n + kForceChunk - 1) / kForceChunk;
+  uint32_t visits = 0;
+  for (uint64_t g = blockIdx.x; g * kForceBodies < items; g += gridDim.x) {
+    const uint64_t u = g * kForceBodies + i;
+    const uint32_t e = (uint32_t)((u < items ? u : items - 1) >> sh), slot = (uint32_t)u & (c - 1);
+    const bool live = u < items && ((S[e] >> slot) & 1ull);
+    const uint32_t self = make_obj(R[e], slot);
+    // Slots without a body stand at the origin: they take the same path and write nothing.
+    const float x = live ? fld<float>(h, self, kX) : 0.0f, y = live ? fld<float>(h, self, kY) : 0.0f;
+    if (wave == 0) visits += (uint32_t)__popcll(__ballot(live && half == 0));
+    const float own = half ? y : x;  // chains
+    float sum = 0.0f;
+    // Makers: lane l loads entry l % kForceEach of its wavefront's part, one
+    // chunk ahead (clamped to the last id), and computes kForceEach / 2 scales.
+    const uint32_t part = wave == 0 ? 0u : (wave - 1) * kForceEach, mine = part + (lane & (kForceEach - 1));
+    const bool own_ok = !__ballot(!(__builtin_fabsf(x) <= 0x1p18f && __builtin_fabsf(y) <= 0x1p18f)) &&
+                        a.eps2 >= kScaleLo && a.eps2 <= 0x1p38f;
+    float4 nxt = a.P[mine < n ? mine : n - 1];
+    // Tile k is made while the chains take tile k - 1.
+    for (uint32_t k = 0; k <= chunks; ++k) {
+      if (wave == 0) {
+        const uint32_t t = (k - 1) & 1, j0 = (k - 1) * kForceChunk;
+        const float* sc = s_scale[t] + i * kForceRow;
+        const float* q = s_q[t][half];
+        if (k == 0) {
+        } else if (n - j0 >= kForceChunk) {
 #pragma unroll 4
-      for (uint32_t k = 0; k < m; ++k) {
-        const float4 q = t[k];
-        pair(a, x, y, q.x, q.y, q.z, sx, sy);
+          for (uint32_t j = 0; j < kForceChunk; j += 4) {
+            const float4 s4 = *reinterpret_cast<const float4*>(sc + j), q4 = *reinterpret_cast<const float4*>(q + j);
+            sum = __builtin_fmaf(s4.x, q4.x - own, sum);
+            sum = __builtin_fmaf(s4.y, q4.y - own, sum);
+            sum = __builtin_fmaf(s4.z, q4.z - own, sum);
+            sum = __builtin_fmaf(s4.w, q4.w - own, sum);
+          }
+        } else {
+          for (uint32_t j = 0; j < n - j0; ++j) sum = __builtin_fmaf(sc[j], q[j] - own, sum);
+        }
+      } else if (k < chunks) {
+        const uint32_t t = k & 1, j1 = (k + 1) * kForceChunk + mine;
+        const float4 p = nxt;
+        nxt = a.P[j1 < n ? j1 : n - 1];
+        s_p[t][mine] = p;
+        s_q[t][0][mine] = p.x;
+        s_q[t][1][mine] = p.y;
+        __builtin_amdgcn_wave_barrier();  // this wavefront reads back its own part below
+        // With every coordinate within 2^18, r2 lies between eps2 and 2^40.
+        const bool ok = own_ok && !__ballot(!(__builtin_fabsf(p.x) <= 0x1p18f && __builtin_fabsf(p.y) <= 0x1p18f &&
+                                              scale_normal_mass(p.z)));
+        const uint32_t j0 = part + half * (kForceEach / 2);
+        const float4* pj = s_p[t] + j0;
+        float* out = s_scale[t] + i * kForceRow + j0;
+        auto r2_of = [&](const float4& q) {
+          const float dx = q.x - x, dy = q.y - y;
+          return __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, a.eps2));
+        };
+        if (ok) {
+#pragma unroll
+          for (uint32_t j = 0; j < kForceEach / 2; j += 4) {
+            const float4 q0 = pj[j], q1 = pj[j + 1], q2 = pj[j + 2], q3 = pj[j + 3];
+            *reinterpret_cast<float4*>(out + j) =
+                make_float4(pair_scale_normal(r2_of(q0), q0.z), pair_scale_normal(r2_of(q1), q1.z),
+                            pair_scale_normal(r2_of(q2), q2.z), pair_scale_normal(r2_of(q3), q3.z));
+          }
+        } else {
+          for (uint32_t j = 0; j < kForceEach / 2; ++j) out[j] = pair_scale(r2_of(pj[j]), pj[j].z);
+        }
       }
+      __syncthreads();
     }
-    if (live) {
-      fld<float>(h, self, kAX) = sx;
-      fld<float>(h, self, kAY) = sy;
+    if (wave == 0 && live) {
+      if (half == 0) fld<float>(h, self, kAX) = sum;
+      else fld<float>(h, self, kAY) = sum;
     }
-    return false;
   }
-};
+  if (visits) lead_add(shard(h) + kCntVisits + kBody, visits);
+}
 
 struct BodyMove {
   static constexpr uint32_t kKind = 61;
@@ -327,10 +425,38 @@ struct dsoar_collide {
 
 namespace {
 
+// The do-all of the force over the bodies (see force_kernel): a workgroup per
+// kForceBodies slots of the listed blocks.  The list's length is known on the
+// device only, so the grid is the most groups it can have, up to what the chip
+// holds at once, and loops.
+int launch_force(dsoar_heap* h, const Bodies& a, uint32_t flags, hipStream_t st) {
+  int rc = launch_enumerate(h, kBody, st);
+  if (rc) return rc;
+  const EnumOut& eo = h->enum_out[kBody];
+  uint64_t blocks = h->dev.num_blocks;
+  if (flags & DSOAR_DO_PLAIN) {
+    uint32_t count = 0;
+    rc = read_count(h, kBody, st, &count);
+    if (rc) return rc;
+    if (count == 0) return DSOAR_OK;
+    blocks = count;
+  }
+  const uint64_t groups = (blocks * h->dev.capacity[kBody] + kForceBodies - 1) / kForceBodies;
+  const uint64_t most = (uint64_t)h->num_cus * kForceWgsPerCu;
+  with_width(h, [&](auto w_) {
+    constexpr uint32_t kLG = decltype(w_)::value;
+    launch_timed(h, kKindForce, force_kernel<kLG>, dim3((uint32_t)(groups < most ? groups : most)), dim3(kForceThreads),
+                 st, DevHeapW<kLG>(h->dev), (const uint32_t*)eo.R, (const uint64_t*)eo.S,
+                 (const uint32_t*)&eo.st->count, a);
+  });
+  DSOAR_LAUNCHED(h);
+  return DSOAR_OK;
+}
+
 int collide_one_step(dsoar_collide* c, uint32_t flags, hipStream_t st) {
   dsoar_heap* h = c->heap;
   const uint32_t base = flags & DSOAR_DO_PLAIN, reuse = base | DSOAR_DO_REUSE_ENUM;
-  int rc = launch_doall<BodyForce>(h, kBody, c->a, base, st);
+  int rc = launch_force(h, c->a, base, st);
   if (!rc) rc = launch_doall<BodyMove>(h, kBody, c->a, reuse, st);
   // No squared distance is below a merge radius of 0: the bodies then never
   // merge (the paper's nbody application), and the merge phases would change

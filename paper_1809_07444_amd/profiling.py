@@ -32,8 +32,8 @@ METHOD_KIND = {
     "Choose": "sugar_choose", "Move": "sugar_move", "Eat": "sugar_eat", "Request": "sugar_request",
     "Birth": "sugar_birth", "VisitCount": "visit_count", "DeleteIfMod": "delete_if_mod",
     "FieldGather": "gather", "GolDeleteWorld": "gol_delete_world", "SugarDeleteWorld": "sugar_delete_world",
-    "Decide": "traffic_decide", "Drive": "traffic_drive", "BodyForce": "collide_force", "BodyMove": "collide_move",
-    "BodyRoot": "collide_root", "BodyTarget": "collide_target", "BodyMerge": "collide_merge",
+    "Decide": "traffic_decide", "Drive": "traffic_drive", "BodyForce": "collide_force",
+    "BodyMove": "collide_move", "BodyRoot": "collide_root", "BodyTarget": "collide_target", "BodyMerge": "collide_merge",
     "BodyRemove": "collide_remove", "FishDecide": "wator_fish_decide", "FishMove": "wator_fish_move",
     "SharkDecide": "wator_shark_decide", "SharkMove": "wator_shark_move", "FishEaten": "wator_fish_eaten",
     "FishRead": "wator_fish_read", "SharkRead": "wator_shark_read",
@@ -51,8 +51,8 @@ PLAIN_KIND = [
     ("gol_admit_kernel", "", "gol_admit"), ("regrow_kernel", "", "sugar_regrow"),
     ("sugar_admit_kernel", "", "sugar_admit"), ("entry_kernel", "", "traffic_entry"),
     ("traffic_init_kernel", "", "traffic_init"),
-    ("collide_init_kernel", "", "collide_init"), ("wator_init_kernel", "", "wator_init"),
-    ("tick_kernel", "Sea", "wator_tick"),
+    ("force_kernel", "", "collide_force"), ("collide_init_kernel", "", "collide_init"),
+    ("wator_init_kernel", "", "wator_init"), ("tick_kernel", "Sea", "wator_tick"),
 ]
 
 
