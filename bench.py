@@ -547,7 +547,7 @@ class CollideWorkload(GolWorkload):
         self.box = float(16.0 * math.sqrt(self.n / 16384))
         self.inp = W.collide_inputs(self.n, seed=args.seed, box=self.box)
         self.params = dict(W.COLLIDE_PARAMS, r2_merge=0.0) if args.workload == "nbody" else W.COLLIDE_PARAMS
-        self.doalls = 6  # do-alls per step, each visiting every live body
+        self.doalls = 6  # phases per step, each visiting every live body (merge and removal in one do-all)
         if args.workload == "nbody":
             self.name = "nbody"  # merge radius 0: force and move only
             self.doalls = 2
@@ -581,7 +581,7 @@ class CollideWorkload(GolWorkload):
     def kernel_bytes(self, kind, launches, st):
         v = st["visits"][0] / self.doalls
         per = {"collide_force": 12 + 8 + 16 * 0, "collide_move": 32 + 24, "collide_root": 12 + 4,
-               "collide_target": 16 + 4, "collide_merge": 24 + 4, "collide_remove": 8}
+               "collide_target": 16 + 4, "collide_merge": 24 + 4}
         if kind in per:
             return v * per[kind] + v / 64 * 12
         if kind == "collide_init":

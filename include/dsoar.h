@@ -117,7 +117,7 @@ typedef struct {
   uint64_t allocs[DSOAR_MAX_TYPES];       /* successful device news */
   uint64_t frees[DSOAR_MAX_TYPES];        /* successful device deletes */
   uint64_t live_objects[DSOAR_MAX_TYPES]; /* popcount of the object bitmaps */
-  uint64_t visits[DSOAR_MAX_TYPES];       /* objects visited by do-all methods */
+  uint64_t visits[DSOAR_MAX_TYPES];       /* objects visited by do-all methods (once per phase) */
   uint32_t allocated_blocks[DSOAR_MAX_TYPES];
   uint32_t active_blocks[DSOAR_MAX_TYPES];
   uint32_t typed_blocks[DSOAR_MAX_TYPES]; /* blocks whose type word is t */
@@ -567,14 +567,15 @@ int dsoar_traffic_read(dsoar_traffic* traffic, int32_t* vel_dev, void* stream);
 /* --------------------------------------------------------------- collisions
  * Merging bodies in the plane (the paper's "collisions" application, Fig.
  * 6b): Body objects {x, y, vx, vy, ax, ay, m, id} (type 0 of the heap: at
- * least eight 4-byte fields).  Per step six do-alls: accelerations summed
+ * least eight 4-byte fields).  Per step six phases: accelerations summed
  * over all ids in increasing order (m_j (p_j - p) / (r2 sqrt(r2)), r2 = |p_j -
  * p|^2 + eps2), Euler move (v += dt a, p += dt v), roots (no live body of
  * lower id within the merge radius), targets (a non-root merges into the
  * lowest-id root within the radius), merges (mass, momentum and mass-weighted
  * position added in increasing id order), removal of the merged bodies
- * (delete).  Single-precision operations, one rounding each, in that order.
- * With r2_merge = 0 no body ever merges and a step is the first two do-alls
+ * (delete).  Single-precision operations, one rounding each, in that order;
+ * the last two phases share a do-all (visits count each phase).
+ * With r2_merge = 0 no body ever merges and a step is the first two phases
  * only: the paper's "nbody" application (Fig. 6d). */
 typedef struct dsoar_collide dsoar_collide;
 typedef struct {

@@ -220,6 +220,15 @@ struct MinWaves : std::integral_constant<uint32_t, 1> {};
 template <class M>
 struct MinWaves<M, std::void_t<decltype(M::kMinWaves)>> : std::integral_constant<uint32_t, M::kMinWaves> {};
 
+// A method that does the work of several phases that would otherwise each be a
+// do-all of their own declares
+//   static constexpr uint32_t kPhases = 2;
+// its visits are counted once per phase.
+template <class M, class = void>
+struct Phases : std::integral_constant<uint32_t, 1> {};
+template <class M>
+struct Phases<M, std::void_t<decltype(M::kPhases)>> : std::integral_constant<uint32_t, M::kPhases> {};
+
 template <class Method, class H>
 __device__ __forceinline__ bool run_method(const H& h, uint32_t type, uint32_t self,
                                            const typename Method::Args& a) {
@@ -559,7 +568,7 @@ doall_kernel(DevHeapW<LG> h, uint32_t type, const uint32_t* __restrict__ R,
   uint32_t visits = 0, freed = 0;
   doall_list<Method, DeletesOnlyThis<Method>::value>(h, type, R, S, bcast32(*count_ptr), grid_wave(), nw, args,
                                                       visits, freed);
-  if (visits) lead_add(shard(h) + kCntVisits + type, visits);
+  if (visits) lead_add(shard(h) + kCntVisits + type, visits * Phases<Method>::value);
   if (freed) lead_add(shard(h) + kCntFrees + type, freed);
 }
 
@@ -582,11 +591,11 @@ doall2_kernel(DevHeapW<LG> h, uint32_t t1, const uint32_t* __restrict__ R1,
   uint32_t visits = 0, freed = 0;
   constexpr bool kOnlyThis = DeletesOnlyThis<M1>::value && DeletesOnlyThis<M2>::value;
   doall_list<M1, kOnlyThis>(h, t1, R1, S1, bcast32(*c1), gw, nw, a1, visits, freed);
-  if (visits) lead_add(shard(h) + kCntVisits + t1, visits);
+  if (visits) lead_add(shard(h) + kCntVisits + t1, visits * Phases<M1>::value);
   if (freed) lead_add(shard(h) + kCntFrees + t1, freed);
   visits = freed = 0;
   doall_list<M2, kOnlyThis>(h, t2, R2, S2, bcast32(*c2), gw, nw, a2, visits, freed);
-  if (visits) lead_add(shard(h) + kCntVisits + t2, visits);
+  if (visits) lead_add(shard(h) + kCntVisits + t2, visits * Phases<M2>::value);
   if (freed) lead_add(shard(h) + kCntFrees + t2, freed);
 }
 

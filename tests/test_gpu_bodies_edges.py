@@ -63,3 +63,39 @@ def test_the_quotient_left_to_the_general_form():
     inp.x[7] = np.nextafter(np.float32(0.5), np.float32(1))
     inp.m[:] = m
     same(inp, dict(dt=1.0, eps2=eps2, r2_merge=0.0), 1)
+
+
+# Merge phases.  Cells: a few bodies near each other, crowds longer than a
+# walk (one point, or everything in one cell), bodies outside the cells' range,
+# radii that the cells do not serve.
+@pytest.mark.parametrize("n,box,r2,capacity", [
+    (1, 1.0, 1e-4, 64), (2, 0.001, 1e-4, 64), (500, 0.4, 1e-4, 64), (500, 0.4, 1e-4, 32), (3000, 0.4, 1e-4, 64),
+    (200, 0.0, 1e-4, 64), (300, 0.5, 0.25, 64), (200, 1.0, 2.0 ** -61, 64), (200, 0.0, 2.0 ** -61, 64),
+    (150, 1.0, 2.0 ** 61, 64), (2000, 8.0, 2.0 ** -10, 64)])
+def test_merges(n, box, r2, capacity):
+    ref = same(W.collide_inputs(n, seed=n + 5, box=box), dict(dt=0.01, eps2=0.01, r2_merge=r2), 4, capacity)
+    if n >= 200 and r2 > 2.0 ** -60:
+        assert ref.merges > 0
+
+
+@pytest.mark.parametrize("flags", [C.DO_PERSISTENT, C.DO_PLAIN, C.DO_PERSISTENT | C.GRAPH])
+def test_merges_with_a_crowd(flags):
+    # 40 bodies at one point among spread ones: some wavefronts' lanes walk, some scan.
+    inp = W.collide_inputs(700, seed=8, box=2.0)
+    inp.x[100:700:15], inp.y[100:700:15] = 0.5, 0.75
+    ref = same(inp, W.COLLIDE_PARAMS, 12, flags=flags)
+    assert ref.merges >= 39
+
+
+@pytest.mark.parametrize("x,y", [(1.0e9, 0.0), (0.0, -3.0e38), (np.inf, 1.0), (0.5, np.nan), (2.0 ** 20 / 75, 0.0)])
+def test_merges_with_a_far_body(x, y):
+    inp = W.collide_inputs(400, seed=4, box=0.5)
+    inp.x[77], inp.y[77] = x, y
+    assert same(inp, W.COLLIDE_PARAMS, 3).merges > 0 or not np.isfinite(x + y)
+
+
+def test_merges_across_negative_cells():
+    inp = W.collide_inputs(600, seed=6, box=0.4)
+    inp.x -= np.float32(0.2)
+    inp.y -= np.float32(0.2)
+    assert same(inp, W.COLLIDE_PARAMS, 5).merges > 0
