@@ -585,7 +585,11 @@ typedef struct {
   uint32_t reserved;
 } dsoar_collide_params;
 /* Device bytes for n body ids (0 if n is 0 or above 2^24). */
+/* Device bytes for n bodies: the least dsoar_collide_create takes, and the same
+ * with a table of cells (16 to 32 bytes more per body) through which the merge
+ * phases find near bodies; with less they compare every pair. */
 size_t dsoar_collide_bytes(uint32_t n);
+size_t dsoar_collide_bytes_cells(uint32_t n);
 int dsoar_collide_create(dsoar_heap* heap, uint32_t n, const dsoar_collide_params* params, void* dev_mem,
                          size_t dev_bytes, dsoar_collide** out);
 int dsoar_collide_destroy(dsoar_collide* collide);

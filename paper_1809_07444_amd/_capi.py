@@ -168,6 +168,7 @@ SIGNATURES = {
     "dsoar_sugar_step": (ctypes.c_int, [vp, u32, u32, vp]),
     "dsoar_sugar_read": (ctypes.c_int, [vp, vp, vp, vp, vp, vp, vp, ctypes.POINTER(u32), vp]),
     "dsoar_collide_bytes": (sz, [u32]),
+    "dsoar_collide_bytes_cells": (sz, [u32]),
     "dsoar_collide_create": (ctypes.c_int, [H, u32, vp, vp, sz, ctypes.POINTER(vp)]),
     "dsoar_collide_destroy": (ctypes.c_int, [vp]),
     "dsoar_collide_init": (ctypes.c_int, [vp, vp, vp, vp, vp, vp, vp]),

@@ -331,7 +331,7 @@ class Collisions:
         blocks = num_blocks or max(64, 1 << (2 * -(-self.n // (capacity or 64)) - 1).bit_length())
         self.heap = Heap(blocks, capacity, BODY_TYPE, device=device, stream=self.stream)
         self.lib = self.heap.lib
-        nbytes = int(self.lib.dsoar_collide_bytes(self.n))
+        nbytes = int(self.lib.dsoar_collide_bytes_cells(self.n))
         if nbytes == 0:
             raise ValueError("bad body count")
         self.buf = torch.empty(nbytes, dtype=torch.uint8, device=device)

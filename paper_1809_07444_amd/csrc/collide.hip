@@ -598,7 +598,12 @@ extern "C" {
 
 size_t dsoar_collide_bytes(uint32_t n) {
   if (n == 0 || n > (1u << 24)) return 0;
-  return align256((size_t)n * 16) + align256((size_t)n * 8) + align256((size_t)n * 4) + 256 + cell_buckets(n) * 4;
+  return align256((size_t)n * 16) + align256((size_t)n * 8) + align256((size_t)n * 4);
+}
+
+size_t dsoar_collide_bytes_cells(uint32_t n) {
+  const size_t b = dsoar_collide_bytes(n);
+  return b ? b + 256 + cell_buckets(n) * 4 : 0;
 }
 
 int dsoar_collide_create(dsoar_heap* heap, uint32_t n, const dsoar_collide_params* params, void* dev_mem,
@@ -623,9 +628,11 @@ int dsoar_collide_create(dsoar_heap* heap, uint32_t n, const dsoar_collide_param
   c->a.dt = params->dt;
   c->a.eps2 = params->eps2;
   c->a.r2_merge = params->r2_merge;
-  // The cells serve radii whose squares do not run into the ends of the range.
-  if (params->r2_merge >= 0x1p-60f && params->r2_merge <= 0x1p60f) {
-    c->a.far_out = (uint32_t*)((uint8_t*)c->a.T + align256((size_t)n * 4));
+  // The cells serve radii whose squares do not run into the ends of the range;
+  // a buffer without room for their table keeps the scans.
+  if (dev_bytes >= dsoar_collide_bytes_cells(n) && params->r2_merge >= 0x1p-60f &&
+      params->r2_merge <= 0x1p60f) {
+    c->a.far_out = (uint32_t*)(b + need);
     c->a.head = c->a.far_out + 64;
     c->a.mask = (uint32_t)(cell_buckets(n) - 1);
     c->a.inv_cell = 0.75f / sqrtf(params->r2_merge);

@@ -1,6 +1,8 @@
 """Force do-all at the edges of its tiles and of its arithmetic's two forms,
 against the oracle: every operation is rounded once in the oracle's order, so
 the results are equal bit for bit (NaN wherever the oracle has NaN)."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -14,8 +16,14 @@ from synth import workloads as W  # noqa: E402
 FIELDS = ("x", "y", "vx", "vy", "m")
 
 
-def same(inp, params, steps, capacity=64, flags=C.DO_PERSISTENT):
+def same(inp, params, steps, capacity=64, flags=C.DO_PERSISTENT, least=False):
     sim = apps.Collisions(inp, params, capacity=capacity)
+    if least:  # the smallest buffer: no table of cells
+        sim.close()
+        c = ctypes.c_void_p()
+        C.check(sim.lib.dsoar_collide_create(sim.heap.h, inp.n, ctypes.byref(sim.params), sim.buf.data_ptr(),
+                                             sim.lib.dsoar_collide_bytes(inp.n), ctypes.byref(c)), "create")
+        sim.c = c
     sim.init()
     sim.step(steps, flags)
     ref = oracle.collide_run(oracle.CollideState(inp.x, inp.y, inp.vx, inp.vy, inp.m), steps, params)
@@ -85,6 +93,10 @@ def test_merges_with_a_crowd(flags):
     inp.x[100:700:15], inp.y[100:700:15] = 0.5, 0.75
     ref = same(inp, W.COLLIDE_PARAMS, 12, flags=flags)
     assert ref.merges >= 39
+
+
+def test_merges_in_the_least_buffer():
+    assert same(W.collide_inputs(500, seed=3, box=0.4), W.COLLIDE_PARAMS, 4, least=True).merges > 0
 
 
 @pytest.mark.parametrize("x,y", [(1.0e9, 0.0), (0.0, -3.0e38), (np.inf, 1.0), (0.5, np.nan), (2.0 ** 20 / 75, 0.0)])
