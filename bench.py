@@ -423,21 +423,18 @@ class TrafficWorkload(GolWorkload):
         return self.sim.heap
 
     def kernel_bytes(self, kind, launches, st):
-        v = st["visits"][0] / 2  # two do-alls per step visit every car
-        # (this + new objects, other).  Decide: cell and speed read, next
-        # speed written; other: up to vmax road cells ahead.  Drive: next
-        # speed and cell read, speed and cell written; other: two road cells.
-        per = {"traffic_decide": (12, 4 * self.rules["vmax"]), "traffic_drive": (16, 8)}
-        if kind in per:
-            return v * per[kind][0] + v / 64 * 12, v * per[kind][1]
+        v = st["visits"][0] / 2  # two phases per step visit every car
         cars0 = int((self.inp.vel >= 0).sum())
-        if kind == "traffic_entry":
-            # new cars: three fields each; other: every road's first cell read
-            # and an entering car's first cell written
+        if kind == "traffic_step":
+            # (this + new objects, other).  Cell and speed read, cell, speed
+            # and next speed written; new cars: three fields each; other (two
+            # bytes per road cell): up to vmax cells ahead read and one
+            # written per car, every road's first cell read.
             entered = st["allocs"][0] - cars0
-            return entered * 12, launches * self.roads * 4 + entered * 4
+            return (v * 20 + v / 64 * 12 + entered * 12,
+                    v * 2 * (self.rules["vmax"] + 1) + launches * self.roads * 2 + entered * 2)
         if kind == "traffic_init":  # new cars' fields; other: input speed read and cell written per cell
-            return cars0 * 12 + cars0 / 64 * 12, self.roads * self.length * 8
+            return cars0 * 12 + cars0 / 64 * 12, self.roads * self.length * 8  # two 16-bit planes
         if kind == "enumerate":
             return launches * (self.M / 8) + v / 64 * 20
         return None

@@ -241,10 +241,9 @@ int dsoar_heap_set_unroll(dsoar_heap* heap, uint32_t blocks_per_pass);
  * Kinds: 1 enumeration; do-alls 10 visit count, 11 delete-if-mod, 12 gather,
  * 20/21 micro update/cull, 30..33 Game of Life phases 1..4 (35: phases 3 and
  * 4 in one launch, 34 world deletion), 40..45 Sugarscape phases and world
- * deletion, 50/51 traffic decide/drive, 60..65 collisions, 70..76 wa-tor;
+ * deletion, 51 traffic step, 60..64 collisions, 70..76 wa-tor;
  * other kernels 22 micro creation, 36/37 Game of Life initial cells and
- * admission, 46/47 Sugarscape regrow and admission, 52/53 traffic entry and
- * initial cars, 66 collisions initial bodies, 77/78 wa-tor initial sea and
+ * admission, 46/47 Sugarscape regrow and admission, 53 traffic initial cars, 66 collisions initial bodies, 77/78 wa-tor initial sea and
  * step tick. */
 int dsoar_heap_set_timing(dsoar_heap* heap, int enable);
 int dsoar_heap_timing(dsoar_heap* heap, uint32_t* kinds, uint32_t* counts, double* total_ms,
@@ -535,10 +534,10 @@ int dsoar_sugar_read(dsoar_sugar* sugar, int32_t* sugar_dev, uint8_t* occ_dev, i
  * `roads` open single-lane roads of `length` cells: Car objects {cell, speed,
  * next speed} (type 0 of the heap: at least three 4-byte fields) advance by
  * the model's rules; cars enter at a road's first cell and are deleted when
- * they pass its last cell.  Per step: a do-all decides every car's speed
+ * they pass its last cell.  Per step, in one kernel: every car's speed is decided
  * (accelerate, brake to the empty cells ahead, dawdle with probability
- * p_slow24 / 2^24 from hash(seed, 32, cell, t)), a second do-all moves the
- * cars, then a car enters each empty first cell with probability p_in24 /
+ * p_slow24 / 2^24 from hash(seed, 32, cell, t)), the cars move (visits count
+ * both phases), and a car enters each empty first cell with probability p_in24 /
  * 2^24 from hash(seed, 33, road, t) (the hash of the workload generator). */
 typedef struct dsoar_traffic dsoar_traffic;
 typedef struct {

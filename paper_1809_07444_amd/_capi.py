@@ -35,12 +35,12 @@ KIND_NAMES = {1: "enumerate", 10: "visit_count", 11: "delete_if_mod", 12: "gathe
               21: "micro_cull", 30: "gol_alive_prep", 31: "gol_cand_prep", 32: "gol_alive_update",
               33: "gol_cand_update", 35: "gol_update", 40: "sugar_choose", 41: "sugar_move", 42: "sugar_eat",
               43: "sugar_request", 44: "sugar_birth", 34: "gol_delete_world", 45: "sugar_delete_world",
-              50: "traffic_decide", 51: "traffic_drive", 60: "collide_force", 61: "collide_move",
+              51: "traffic_step", 60: "collide_force", 61: "collide_move",
               62: "collide_root", 63: "collide_target", 64: "collide_merge",
               70: "wator_fish_decide", 71: "wator_fish_move", 72: "wator_shark_decide",
               73: "wator_shark_move", 74: "wator_fish_eaten", 75: "wator_fish_read", 76: "wator_shark_read",
               22: "micro_create", 36: "gol_init", 37: "gol_admit", 46: "sugar_regrow", 47: "sugar_admit",
-              52: "traffic_entry", 53: "traffic_init", 66: "collide_init",
+              53: "traffic_init", 66: "collide_init",
               77: "wator_init", 78: "wator_tick"}
 INV_NAMES = ["bitmap_range", "allocated", "active", "active_implies_allocated", "free",
              "container", "live_count", "free_count"]

@@ -413,6 +413,10 @@ __global__ void __launch_bounds__(enum_waves(WPW) * 64) enumerate_kernel(DevHeap
   if (tile == out.num_tiles - 1 && threadIdx.x == 0) {
     __hip_atomic_store(&out.st->count, s_prefix + tile_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (out.count_out) *out.count_out = s_prefix + tile_total;
+    if (out.clock) {
+      out.clock->t += 1;
+      out.clock->epoch = next_epoch(out.clock->epoch);
+    }
     __hip_atomic_store(&out.st->tile_counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&out.st->epoch, epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
@@ -682,8 +686,10 @@ int launch_enumerate_into(dsoar_heap* h, uint32_t type, const EnumOut& eo, hipSt
   return DSOAR_OK;
 }
 
-int launch_enumerate(dsoar_heap* h, uint32_t type, hipStream_t s) {
-  return launch_enumerate_into(h, type, h->enum_out[type], s);
+int launch_enumerate(dsoar_heap* h, uint32_t type, hipStream_t s, StepClock* clock) {
+  EnumOut eo = h->enum_out[type];
+  eo.clock = clock;
+  return launch_enumerate_into(h, type, eo, s);
 }
 
 // Scratch of the allocation-free enumeration (dsoar_enumerate_noalloc): the
@@ -879,6 +885,7 @@ int dsoar_heap_create(const dsoar_heap_desc* desc, void* dev_mem, size_t dev_byt
     e.flags = (uint64_t*)(h->base + p.scan_off[t] + sizeof(ScanState));
     e.num_tiles = p.num_tiles;
     e.count_out = nullptr;
+    e.clock = nullptr;
   }
   int dev = 0;
   hipDeviceProp_t prop;

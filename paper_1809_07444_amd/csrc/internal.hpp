@@ -34,6 +34,18 @@ struct ScanState {
   uint32_t pad;
 };
 
+// An application's step clock in device memory: the step index and an epoch
+// that goes round from 2 to kEpochs - 1 (an even number of values).  The
+// enumeration that starts a step advances it when it is handed one, so that a
+// captured step replays correctly and no kernel of the step both reads and
+// writes it.
+constexpr uint32_t kEpochs = 1u << 12;
+struct StepClock {
+  uint32_t t;
+  uint32_t epoch;
+};
+__host__ __device__ __forceinline__ uint32_t next_epoch(uint32_t e) { return e + 1 == kEpochs ? 2u : e + 1; }
+
 struct EnumOut {
   uint32_t* R;          // compacted block ids
   uint64_t* S;          // snapshot of each listed block's object bitmap
@@ -41,6 +53,7 @@ struct EnumOut {
   uint64_t* flags;      // num_tiles look-back words
   uint32_t num_tiles;
   uint32_t* count_out;  // where the count also goes (nullptr: only st->count)
+  StepClock* clock;     // advanced by one step (nullptr: none)
 };
 
 struct StatsOut {
@@ -102,7 +115,6 @@ constexpr uint32_t kKindGolInit = 36;
 constexpr uint32_t kKindGolAdmit = 37;
 constexpr uint32_t kKindSugarRegrow = 46;
 constexpr uint32_t kKindSugarAdmit = 47;
-constexpr uint32_t kKindTrafficEntry = 52;
 constexpr uint32_t kKindTrafficInit = 53;
 constexpr uint32_t kKindCollideInit = 66;
 constexpr uint32_t kKindWatorInit = 77;
@@ -136,7 +148,7 @@ inline void with_width(const dsoar_heap* h, F&& f) {
     f(std::integral_constant<uint32_t, 5>{});
 }
 
-int launch_enumerate(dsoar_heap* h, uint32_t type, hipStream_t s);
+int launch_enumerate(dsoar_heap* h, uint32_t type, hipStream_t s, StepClock* clock = nullptr);
 int read_count(dsoar_heap* h, uint32_t type, hipStream_t s, uint32_t* count);
 
 // A method may split into a load phase and an apply phase:

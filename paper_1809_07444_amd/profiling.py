@@ -50,6 +50,7 @@ PLAIN_KIND = [
     ("micro_create_kernel", "", "micro_create"), ("gol_init_kernel", "", "gol_init"),
     ("gol_admit_kernel", "", "gol_admit"), ("regrow_kernel", "", "sugar_regrow"),
     ("sugar_admit_kernel", "", "sugar_admit"), ("entry_kernel", "", "traffic_entry"),
+    ("traffic_step_kernel", "", "traffic_step"),
     ("traffic_init_kernel", "", "traffic_init"),
     ("force_kernel", "", "collide_force"), ("collide_init_kernel", "", "collide_init"),
     ("wator_init_kernel", "", "wator_init"), ("tick_kernel", "Sea", "wator_tick"),
