@@ -116,23 +116,23 @@ def gol_init_bytes(cells, alive):
 def sugar_kernel_bytes(kind, launches, st, M, init_agents, cells):
     """(this + new-object bytes, other bytes) of the Sugarscape kernels.  Per
     agent visit, this: choose reads pos, vision and world and writes target;
-    move reads pos, target and world and writes pos; eat reads pos, sugar,
-    metabolism and age and writes sugar and age; request reads sugar and age
+    move and eat read pos, target, world, sugar, metabolism and age and write
+    pos, sugar and age; request reads sugar and age
     and writes target; birth reads target, pos and world.  New objects: a
     child's seven fields.  Other: the grid cells in sight (one byte each, 25
     loaded), the world table, request words and the cells a move, meal,
     request or birth touches."""
-    v = st["visits"][0] / 5  # five do-alls per step
+    v = st["visits"][0] / 5  # five phases per step
     births = st["allocs"][0] - init_agents
-    per = {"sugar_choose": (16, 25 + 8 + 4), "sugar_move": (16, 4 + 16), "sugar_eat": (24, 2 + 4),
+    per = {"sugar_choose": (16, 25 + 8 + 4), "sugar_move_eat": (36, 8 + 4),
            "sugar_request": (12, 8 + 16 + 4), "sugar_birth": (12, 4)}
     if kind in per:
         this, other = per[kind]
         if kind == "sugar_birth":  # a child's seven fields; its cell's occupant word and byte
-            return v * this + v / 64 * 12 + births * 28, v * other + births * 5
+            return v * this + v / 64 * 12 + births * 28, v * other + births
         return v * this + v / 64 * 12, v * other
-    if kind == "sugar_regrow":  # other state only: sugar byte and capacity read, sugar byte written, per cell
-        return 0.0, launches * cells * 6
+    if kind == "sugar_regrow":  # other state only: sugar and capacity bytes read, sugar byte written, per cell
+        return 0.0, launches * cells * 3
     if kind == "enumerate":
         return launches * (M / 8) + (2 * v / 64) * 20
     return None

@@ -235,7 +235,7 @@ struct MinWaves<M, std::void_t<decltype(M::kMinWaves)>> : std::integral_constant
 // A method that does the work of several phases that would otherwise each be a
 // do-all of their own declares
 //   static constexpr uint32_t kPhases = 2;
-// its visits are counted once per phase.
+// its visits are counted once per phase (0: not at all, for a readout).
 template <class M, class = void>
 struct Phases : std::integral_constant<uint32_t, 1> {};
 template <class M>

@@ -1,16 +1,19 @@
 // Sugarscape-style agents as objects on a square torus (the paper's
 // sugarscape application, Sec. 4; its rules are not in the paper, so this is
 // a synchronous, deterministic variant).  Agent {sugar, metabolism, vision,
-// age, pos, target}; the sugar, capacity, occupancy and request grids are
-// plain device arrays.  One step t:
+// age, pos, target, world}; the sugar (with occupancy), capacity and request
+// grids are plain device arrays.  One step t:
 //   regrow (grid kernel): sugar = min(sugar + 1, cap)
 //   1 choose  (do-all): best of the own cell and the unoccupied cells up to
 //             `vision` away along the four axes: most sugar, then nearest,
-//             then lowest index; a move request is an atomicMin of the own
-//             cell index into req[target]
-//   2 move    (do-all): the lowest requesting cell index wins the target
-//   3 eat     (do-all): sugar += cell; cell = 0; sugar -= metabolism; age++;
-//             die (delete) if sugar <= 0 or age >= max_age
+//             then lowest index; a move request is the direction and distance
+//             of the target, written to the own cell of the request grid
+//   2 move    (do-all): the lowest requesting cell index wins the target; a
+//             mover looks for lower ones in the cells that can see its target
+//   3 eat     (same do-all: an agent touches only the cell it leaves and the
+//             one it ends on, which no other agent does): sugar += cell; cell
+//             = 0; sugar -= metabolism; age++; die (delete) if sugar <= 0 or
+//             age >= max_age
 //   4 request (do-all): fertile agents with enough sugar request their
 //             lowest-index empty von Neumann neighbour (atomicMin)
 //   5 birth   (do-all): the winner creates a child there with half its sugar
@@ -56,19 +59,20 @@ __device__ __forceinline__ int32_t uniform_int(uint64_t h, int32_t lo, int32_t h
 // its own seed, step index and move count, so a world evolves exactly as it
 // would alone.
 // A cell's sugar is one byte, its low seven bits the amount and the top bit
-// the occupancy (kOccupied), so that the cells an agent looks at take one
-// load each and the grid of a 2048^2 world (4 MB) stays in an XCD's L2; occ
-// keeps the agent handle.  Amounts and capacities are 0..kMaxSugar.
+// the occupancy (kOccupied), so that a row of the cells an agent looks at is
+// one load and the grid of a 2048^2 world (4 MB) stays in an XCD's L2.  Which
+// agent stands in a cell is in the agents alone (a grid of handles beside the
+// bits cost every move two scattered stores, and only the readout used it).
+// Amounts and capacities are 0..kMaxSugar.
 constexpr int32_t kOccupied = 0x80;
 constexpr int32_t kMaxSugar = 0x7F;
 __device__ __forceinline__ int32_t sugar_of(int32_t w) { return w & kMaxSugar; }
 
 struct Grid {
   uint8_t* sugar;     // sugar | kOccupied when an agent stands there
-  const int32_t* cap;
-  uint32_t* occ;      // agent handle or kNull
-  uint32_t* req;      // lowest requesting cell index or kInf
-  uint32_t* breq;
+  uint8_t* cap;
+  uint8_t* req;       // request of the agent standing there in this step (request_code), 0: none
+  uint32_t* breq;     // lowest cell index requesting a birth there or kInf
   uint32_t* w_off;    // per slot
   uint32_t* w_side;
   uint64_t* w_seed;
@@ -114,73 +118,153 @@ __device__ __forceinline__ uint32_t step_cell(const Where& c, int32_t dx, int32_
 
 constexpr int32_t kMaxVision = 6;
 
+// Move request k cells along direction d (0 .. 3: x up, x down, y up, y down).
+constexpr uint32_t request_code(uint32_t d, uint32_t k) { return 1u + d * kMaxVision + (k - 1u); }
+
+// Byte planes (sugar, capacity, requests) keep a world's rows in groups of
+// four, each group column by column (the last group of a side that is not a
+// multiple of four has the rows that are left), so a world takes the same
+// side^2 bytes as its cells and byte [off, off + side^2) of each plane.  Four
+// cells of a column are then a dword and a 128-byte line holds 32 x 4 cells:
+// the row and the column that an agent sees are 8 loads from about 5 lines
+// (row by row: 13 loads from as many lines, and once the agents of a wavefront
+// are scattered over the torus, lines are what the L2s deliver a limited
+// number of).
+__device__ __forceinline__ uint32_t byte_at(const Where& c, int32_t x, int32_t y) {
+  const uint32_t side = (uint32_t)c.side, r = (uint32_t)y & 3u, g = (uint32_t)y - r;
+  return c.off + g * side + (uint32_t)x * (g + 4u <= side ? 4u : side & 3u) + r;
+}
+__device__ __forceinline__ uint32_t byte_here(const Where& c) { return byte_at(c, c.x, c.y); }
+__device__ __forceinline__ int32_t wrapped(int32_t v, int32_t side) {
+  if (v < 0 || v >= side) {
+    v %= side;
+    if (v < 0) v += side;
+  }
+  return v;
+}
+
+// The cells that an agent at c sees (of a byte plane): col[i] at (x, y + i -
+// kMaxVision), row[i] at (x + i - kMaxVision, y), around the torus.
+constexpr int32_t kSeen = 2 * kMaxVision + 1;
+__device__ __forceinline__ void cross(const uint8_t* plane, const Where& c, uint32_t (&col)[kSeen],
+                                      uint32_t (&row)[kSeen]) {
+  const int32_t full = c.side & ~3;  // rows in whole groups
+  if (c.y >= kMaxVision && c.y + kMaxVision < full) {
+    // 13 rows from row y - 6 on lie in the four groups from that row's on.
+    const uint32_t y0 = (uint32_t)(c.y - kMaxVision), sh = y0 & 3u;
+    const uint8_t* b = plane + c.off + (y0 - sh) * (uint32_t)c.side + 4u * (uint32_t)c.x;
+    uint32_t d[4];
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) __builtin_memcpy(&d[i], b + i * 4u * (uint32_t)c.side, 4);
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) {
+      const uint32_t w = __builtin_amdgcn_alignbyte(i < 3 ? d[i + 1] : 0u, d[i], sh);
+#pragma unroll
+      for (uint32_t e = 0; e < 4; ++e)
+        if (4 * i + e < (uint32_t)kSeen) col[4 * i + e] = (w >> (8 * e)) & 0xFFu;
+    }
+  } else {
+#pragma unroll
+    for (int32_t i = 0; i < kSeen; ++i) col[i] = plane[byte_at(c, c.x, wrapped(c.y + i - kMaxVision, c.side))];
+  }
+  if (c.x >= kMaxVision && c.x + kMaxVision < c.side && c.y < full) {
+    const uint32_t r = (uint32_t)c.y & 3u;
+    const uint8_t* b = plane + c.off + ((uint32_t)c.y - r) * (uint32_t)c.side + 4u * (uint32_t)(c.x - kMaxVision);
+    uint32_t d[kSeen];
+    __builtin_memcpy(d, b, sizeof(d));
+#pragma unroll
+    for (int32_t i = 0; i < kSeen; ++i) row[i] = (d[i] >> (8 * r)) & 0xFFu;
+  } else {
+#pragma unroll
+    for (int32_t i = 0; i < kSeen; ++i) row[i] = plane[byte_at(c, wrapped(c.x + i - kMaxVision, c.side), c.y)];
+  }
+}
+
+// Index of the cell k steps along direction d (0 .. 3) from c.
+__device__ __forceinline__ uint32_t seen_cell(const Where& c, uint32_t p, uint32_t d, int32_t k) {
+  const int32_t n = d & 1u ? -k : k;
+  if (d < 2) {
+    const int32_t x = c.x + n;
+    return (uint32_t)x < (uint32_t)c.side ? p + (uint32_t)n : step_cell(c, 1, 0, n);
+  }
+  const int32_t y = c.y + n;
+  return (uint32_t)y < (uint32_t)c.side ? p + (uint32_t)(n * c.side) : step_cell(c, 0, 1, n);
+}
+
 struct Choose {
   static constexpr uint32_t kKind = 40;
   using Args = Grid;
+  // The best of the cells in sight: most sugar, then nearest, then lowest
+  // index.  The order in which the candidates are compared does not matter
+  // for that total order.  Bound: scattered lines and addresses; with a load
+  // per cell from rows and an atomic minimum per request 82 us for 1.05 M
+  // agents, now 50.
   template <class H>
   static __device__ bool run(const H& h, uint32_t, uint32_t self, const Args& g) {
     const uint32_t p = af<uint32_t>(h, self, kPos);
     const int32_t vision = af<int32_t>(h, self, kVision);
     const Where c = where(g, af<uint32_t>(h, self, kWorld), p);
-    // The cells in sight along two axis directions at a time (beyond
-    // `vision` the own cell stands in, so that the loads of a half are all
-    // issued together, unconditionally), then the choice: most sugar, then
-    // nearest, then lowest index.  The order in which the candidates are
-    // compared does not matter for that total order.
-    uint32_t best = p;
-    int32_t best_sugar = sugar_of(g.sugar[p]), best_dist = 0;
+    uint32_t col[kSeen], row[kSeen];
+    cross(g.sugar, c, col, row);
+    uint32_t best = p, best_key = ((uint32_t)sugar_of((int32_t)row[kMaxVision]) << 3) | 7u, code = 0;
 #pragma unroll
-    for (int32_t half = 0; half < 2; ++half) {
-      uint32_t q[2 * kMaxVision];
-      int32_t sg[2 * kMaxVision];
+    for (int32_t k = 1; k <= kMaxVision; ++k)
 #pragma unroll
-      for (int32_t j = 0; j < 2; ++j)
-#pragma unroll
-        for (int32_t k = 1; k <= kMaxVision; ++k) {
-          const int32_t d = 2 * half + j;
-          const int32_t dx = d == 0 ? 1 : (d == 1 ? -1 : 0);
-          const int32_t dy = d == 2 ? 1 : (d == 3 ? -1 : 0);
-          q[j * kMaxVision + k - 1] = k <= vision ? step_cell(c, dx, dy, k) : p;
-        }
-#pragma unroll
-      for (int32_t i = 0; i < 2 * kMaxVision; ++i) sg[i] = g.sugar[q[i]];
-#pragma unroll
-      for (int32_t i = 0; i < 2 * kMaxVision; ++i) {
-        const int32_t k = i % kMaxVision + 1;
-        if (k > vision || (sg[i] & kOccupied)) continue;
-        const int32_t s = sg[i];
-        if (s > best_sugar || (s == best_sugar && (k < best_dist || (k == best_dist && q[i] < best)))) {
-          best = q[i];
-          best_sugar = s;
-          best_dist = k;
+      for (uint32_t d = 0; d < 4; ++d) {
+        const uint32_t v = (d < 2 ? row : col)[kMaxVision + (d & 1u ? -k : k)];
+        const uint32_t key = (v << 3) | (uint32_t)(7 - k);
+        if (k > vision || (v & kOccupied) || key < best_key) continue;
+        const uint32_t q = seen_cell(c, p, d, k);
+        if (key > best_key || q < best) {
+          best = q;
+          best_key = key;
+          code = request_code(d, (uint32_t)k);
         }
       }
-    }
     af<uint32_t>(h, self, kTarget) = best;
-    if (best != p) atomicMin(g.req + best, p);
-    wave_count(h, kCntMethodAtomics, best != p ? 1u : 0u);
+    if (best != p) g.req[byte_here(c)] = (uint8_t)code;
     return false;
   }
 };
 
-struct Move {
+// Move and eat.  The agents that may want cell q stand within kMaxVision of it
+// along the axes, and each one's request in its own cell says which cell it
+// wants, so a mover reads those 24 cells (8 loads) instead of all requesters
+// meeting in an atomic minimum per target, whose 4-byte words cost every mover
+// an atomic, a load and a reset beyond the L2.  119 us as two do-alls (Choose
+// 82), 84 fused (Choose 68), 90 with the requests (Choose 50).
+struct MoveEat {
   static constexpr uint32_t kKind = 41;
+  static constexpr uint32_t kPhases = 2;
+  static constexpr uint32_t kMinWaves = 8;
+  static constexpr bool kDeletesOnlyThis = true;
   using Args = Grid;
   template <class H>
   static __device__ bool run(const H& h, uint32_t, uint32_t self, const Args& g) {
     const uint32_t p = af<uint32_t>(h, self, kPos);
     const uint32_t q = af<uint32_t>(h, self, kTarget);
     const uint32_t wid = af<uint32_t>(h, self, kWorld);
-    const bool moves = q != p && __hip_atomic_load(g.req + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == p;
+    const Where from = where(g, wid, p), to = where(g, wid, q);
+    const uint32_t bp = byte_here(from), bq = byte_here(to);
+    const int32_t here = g.sugar[bp], there = g.sugar[bq];
+    const int32_t had = af<int32_t>(h, self, kSugar), metab = af<int32_t>(h, self, kMetab);
+    const int32_t age = af<int32_t>(h, self, kAge) + 1;
+    bool moves = q != p;
     if (moves) {
-      // Distinct cells per mover: q was empty and p occupied when chosen.
-      g.occ[q] = self;
-      g.occ[p] = kNull;
-      g.sugar[q] = (uint8_t)(g.sugar[q] | kOccupied);
-      g.sugar[p] = (uint8_t)sugar_of(g.sugar[p]);
-      af<uint32_t>(h, self, kPos) = q;
-      __hip_atomic_store(g.req + q, kInf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      uint32_t col[kSeen], row[kSeen];
+      cross(g.req, to, col, row);
+      // A requester k cells from q, whose direction leads to q, wins over this
+      // agent from a cell r < p.
+#pragma unroll
+      for (int32_t k = 1; k <= kMaxVision; ++k)
+#pragma unroll
+        for (uint32_t d = 0; d < 4; ++d)
+          if ((d < 2 ? row : col)[kMaxVision + (d & 1u ? -k : k)] == request_code(d ^ 1u, (uint32_t)k) &&
+              seen_cell(to, q, d, k) < p)
+            moves = false;
     }
+    const uint32_t at_cell = moves ? bq : bp;
+    if (moves) g.sugar[bp] = (uint8_t)sugar_of(here);  // distinct cells per mover: q was empty and p occupied
     // Count moves per world: one sharded atomic per world present in the wavefront.
     uint64_t pending = __ballot(moves);
     const uint32_t sh = (blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) & (kMoveShards - 1);
@@ -190,26 +274,13 @@ struct Move {
       lead_add(g.w_moves + (uint64_t)w0 * kMoveShards + sh, (uint64_t)__popcll(mine));
       pending &= ~mine;
     }
-    return false;
-  }
-};
-
-struct Eat {
-  static constexpr uint32_t kKind = 42;
-  static constexpr uint32_t kMinWaves = 8;
-  static constexpr bool kDeletesOnlyThis = true;
-  using Args = Grid;
-  template <class H>
-  static __device__ bool run(const H& h, uint32_t, uint32_t self, const Args& g) {
-    const uint32_t p = af<uint32_t>(h, self, kPos);
-    const int32_t sugar = af<int32_t>(h, self, kSugar) + sugar_of(g.sugar[p]) - af<int32_t>(h, self, kMetab);
-    const int32_t age = af<int32_t>(h, self, kAge) + 1;
+    const int32_t sugar = had + sugar_of(moves ? there : here) - metab;
     if (sugar <= 0 || age >= g.max_age) {
-      g.sugar[p] = 0;
-      g.occ[p] = kNull;
+      g.sugar[at_cell] = 0;
       return true;  // delete this; its fields are not written
     }
-    g.sugar[p] = kOccupied;  // eaten, still here
+    g.sugar[at_cell] = kOccupied;  // eaten, still here
+    if (moves) af<uint32_t>(h, self, kPos) = q;
     af<int32_t>(h, self, kSugar) = sugar;
     af<int32_t>(h, self, kAge) = age;
     return false;
@@ -226,11 +297,18 @@ struct Request {
     if (sugar >= g.repro_min && age >= g.fertile_min && age <= g.fertile_max) {
       const uint32_t p = af<uint32_t>(h, self, kPos);
       const Where c = where(g, af<uint32_t>(h, self, kWorld), p);
-      const uint32_t nb[4] = {wrap_cell(c.off, c.side, c.x + 1, c.y), wrap_cell(c.off, c.side, c.x - 1, c.y),
-                              wrap_cell(c.off, c.side, c.x, c.y + 1), wrap_cell(c.off, c.side, c.x, c.y - 1)};
+      uint32_t occ[4];
 #pragma unroll
-      for (int d = 0; d < 4; ++d)
-        if (g.occ[nb[d]] == kNull && nb[d] < best) best = nb[d];
+      for (uint32_t d = 0; d < 4; ++d) {
+        const int32_t n = d & 1u ? -1 : 1;
+        const int32_t x = d < 2 ? wrapped(c.x + n, c.side) : c.x, y = d < 2 ? c.y : wrapped(c.y + n, c.side);
+        occ[d] = g.sugar[byte_at(c, x, y)];
+      }
+#pragma unroll
+      for (uint32_t d = 0; d < 4; ++d) {
+        const uint32_t q = seen_cell(c, p, d, 1);
+        if (!(occ[d] & kOccupied) && q < best) best = q;
+      }
       if (best != kNull) atomicMin(g.breq + best, p);
     }
     af<uint32_t>(h, self, kTarget) = best;
@@ -267,8 +345,8 @@ struct Birth {
       af<uint32_t>(h, o, kPos) = n;
       af<uint32_t>(h, o, kTarget) = kNull;
       af<uint32_t>(h, o, kWorld) = wid;
-      g.occ[n] = o;
-      g.sugar[n] = (uint8_t)(g.sugar[n] | kOccupied);
+      const uint32_t b = byte_here(where(g, wid, n));
+      g.sugar[b] = (uint8_t)(g.sugar[b] | kOccupied);
     });
     return false;
   }
@@ -283,15 +361,33 @@ struct SugarDeleteWorld {
   }
 };
 
-// Regrow every arena cell, and advance every slot's step index (read by the
-// births of this step).  Cells outside resident worlds are rewritten at
-// admission, so regrowing them is harmless.
+// Regrow every arena cell, 16 per lane, clear its move request, and advance
+// every slot's step index (read by the births of this step).  Cells outside resident worlds (and the
+// bytes up to the next multiple of 16) are rewritten at admission, so
+// regrowing them is harmless.  Bound: the three byte planes' bandwidth (capacities
+// of four bytes and one cell per lane took 6.1 us for 2048^2 cells).
 __global__ void regrow_kernel(Grid g) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < g.max_worlds) g.w_step[i] += 1;
-  for (uint32_t c = i; c < g.arena; c += gridDim.x * blockDim.x) {
-    const int32_t w = g.sugar[c], s = sugar_of(w) + 1, k = g.cap[c];
-    g.sugar[c] = (uint8_t)((s < k ? s : k) | (w & kOccupied));
+  uint4* const sv = reinterpret_cast<uint4*>(g.sugar);
+  uint4* const rv = reinterpret_cast<uint4*>(g.req);
+  const uint4* const cv = reinterpret_cast<const uint4*>(g.cap);
+  for (uint32_t c = i; c < (g.arena + 15) / 16; c += gridDim.x * blockDim.x) {
+    const uint4 w = sv[c], k = cv[c];
+    const uint32_t win[4] = {w.x, w.y, w.z, w.w}, kin[4] = {k.x, k.y, k.z, k.w};
+    uint32_t out[4];
+#pragma unroll
+    for (uint32_t d = 0; d < 4; ++d) {
+      const uint32_t grown = (win[d] & 0x7F7F7F7Fu) + 0x01010101u;  // at most 0x80 per byte
+      out[d] = win[d] & 0x80808080u;
+#pragma unroll
+      for (uint32_t e = 0; e < 32; e += 8) {
+        const uint32_t a = (grown >> e) & 0xFFu, b = (kin[d] >> e) & 0xFFu;
+        out[d] |= (a < b ? a : b) << e;
+      }
+    }
+    sv[c] = make_uint4(out[0], out[1], out[2], out[3]);
+    rv[c] = make_uint4(0, 0, 0, 0);
   }
 }
 
@@ -323,11 +419,11 @@ __global__ void sugar_admit_kernel(DevHeapW<LG> h, Grid g, uint32_t slot, uint32
   const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= n) return;
   const uint32_t q = off + c;
-  g.sugar[q] = (uint8_t)sugar[c];  // checked to be 0..kMaxSugar before the launch
-  const_cast<int32_t*>(g.cap)[q] = cap[c];
-  g.req[q] = kInf;
+  const uint32_t b = byte_here(where(g, slot, q));
+  const uint8_t amount = (uint8_t)sugar[c];  // checked to be 0..kMaxSugar before the launch
+  g.sugar[b] = amount;
+  g.cap[b] = (uint8_t)cap[c];
   g.breq[q] = kInf;
-  g.occ[q] = kNull;
   new_many(h, kAgent, occ[c] ? 1u : 0u, [&](uint32_t, uint32_t o) {
     if (o == kNull) return;
     af<int32_t>(h, o, kSugar) = as[c];
@@ -337,23 +433,41 @@ __global__ void sugar_admit_kernel(DevHeapW<LG> h, Grid g, uint32_t slot, uint32
     af<uint32_t>(h, o, kPos) = q;
     af<uint32_t>(h, o, kTarget) = kNull;
     af<uint32_t>(h, o, kWorld) = slot;
-    g.occ[q] = o;
-    g.sugar[q] = (uint8_t)(g.sugar[q] | kOccupied);
+    g.sugar[b] = (uint8_t)(amount | kOccupied);
   });
 }
 
-__global__ void sugar_read_kernel(DevHeap h, Grid g, uint32_t off, uint32_t n, int32_t* sugar, uint8_t* occ,
-                                  int32_t* as, int32_t* am, int32_t* av, int32_t* aa) {
+// Readout of one world: its cells' sugar, and its agents' fields by cell (a
+// do-all over all agents fills the occupied cells that the kernel zeroed).
+struct ReadArgs {
+  uint32_t slot, off;
+  uint8_t* occ;
+  int32_t *sugar, *metab, *vision, *age;
+};
+
+struct AgentRead {
+  static constexpr uint32_t kKind = 48;
+  static constexpr uint32_t kPhases = 0;  // no phase of a step: its visits are not counted
+  using Args = ReadArgs;
+  template <class H>
+  static __device__ bool run(const H& h, uint32_t, uint32_t self, const Args& a) {
+    if (af<uint32_t>(h, self, kWorld) != a.slot) return false;
+    const uint32_t c = af<uint32_t>(h, self, kPos) - a.off;
+    a.occ[c] = 1;
+    a.sugar[c] = af<int32_t>(h, self, kSugar);
+    a.metab[c] = af<int32_t>(h, self, kMetab);
+    a.vision[c] = af<int32_t>(h, self, kVision);
+    a.age[c] = af<int32_t>(h, self, kAge);
+    return false;
+  }
+};
+
+__global__ void sugar_read_kernel(Grid g, ReadArgs a, uint32_t n, int32_t* sugar) {
   const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= n) return;
-  const uint32_t q = off + c;
-  sugar[c] = sugar_of(g.sugar[q]);
-  const uint32_t o = g.occ[q];
-  occ[c] = o != kNull;
-  as[c] = o != kNull ? af<int32_t>(h, o, kSugar) : 0;
-  am[c] = o != kNull ? af<int32_t>(h, o, kMetab) : 0;
-  av[c] = o != kNull ? af<int32_t>(h, o, kVision) : 0;
-  aa[c] = o != kNull ? af<int32_t>(h, o, kAge) : 0;
+  sugar[c] = sugar_of(g.sugar[byte_here(where(g, a.slot, a.off + c))]);
+  a.occ[c] = 0;
+  a.sugar[c] = a.metab[c] = a.vision[c] = a.age[c] = 0;
 }
 
 bool sugar_heap_ok(const dsoar_heap* h) {
@@ -385,14 +499,13 @@ namespace {
 int sugar_one_step(dsoar_sugar* s, uint32_t flags, hipStream_t st) {
   dsoar_heap* h = s->heap;
   const uint32_t base = flags & DSOAR_DO_PLAIN;
-  const uint32_t grid = std::min<uint32_t>(std::max<uint32_t>((s->g.arena + 255) / 256, (s->g.max_worlds + 255) / 256),
-                                           std::max<uint32_t>(h->num_cus * 16, (s->g.max_worlds + 255) / 256));
+  const uint32_t slots = (s->g.max_worlds + 255) / 256, cells = (s->g.arena + 4095) / 4096;  // workgroups
+  const uint32_t grid = std::max(slots, std::min(cells, h->num_cus * 16));
   launch_timed(s->heap, kKindSugarRegrow, regrow_kernel, dim3(grid), dim3(256), st, s->g);
   DSOAR_LAUNCHED(h);
   int rc = launch_doall<Choose>(h, kAgent, s->g, base, st);
-  // choose and move create and delete nothing: move and eat reuse the list.
-  if (!rc) rc = launch_doall<Move>(h, kAgent, s->g, base | DSOAR_DO_REUSE_ENUM, st);
-  if (!rc) rc = launch_doall<Eat>(h, kAgent, s->g, base | DSOAR_DO_REUSE_ENUM, st);
+  // choose creates and deletes nothing: move and eat reuse the list.
+  if (!rc) rc = launch_doall<MoveEat>(h, kAgent, s->g, base | DSOAR_DO_REUSE_ENUM, st);
   // eat deletes: the request phase enumerates again; birth reuses that list.
   if (!rc) rc = launch_doall<Request>(h, kAgent, s->g, base, st);
   if (!rc) rc = launch_doall<Birth>(h, kAgent, s->g, base | DSOAR_DO_REUSE_ENUM, st);
@@ -400,6 +513,9 @@ int sugar_one_step(dsoar_sugar* s, uint32_t flags, hipStream_t st) {
 }
 
 size_t plane_bytes(uint64_t cells) { return (size_t)((cells * 4 + 255) / 256 * 256); }
+// A plane of one byte per cell, with 16 bytes past the last that a row window
+// or a regrowing lane may touch.
+size_t byte_plane_bytes(uint64_t cells) { return (size_t)((cells + 16 + 255) / 256 * 256); }
 
 // World table: seeds, offsets, sides, steps; the move counters; one 256-byte
 // line for the admission input check.
@@ -414,7 +530,7 @@ extern "C" {
 
 size_t dsoar_sugarpool_bytes(uint32_t max_worlds, uint32_t arena_cells) {
   if (max_worlds == 0 || max_worlds > (1u << 16) || arena_cells == 0 || arena_cells > (1u << 30)) return 0;
-  return table_bytes(max_worlds) + 5 * plane_bytes(arena_cells);
+  return table_bytes(max_worlds) + 3 * byte_plane_bytes(arena_cells) + plane_bytes(arena_cells);
 }
 
 int dsoar_sugarpool_create(dsoar_heap* heap, uint32_t max_worlds, uint32_t arena_cells,
@@ -450,12 +566,11 @@ int dsoar_sugarpool_create(dsoar_heap* heap, uint32_t max_worlds, uint32_t arena
   g.w_moves = (uint64_t*)(b + ((uint64_t)max_worlds * 20 + 255) / 256 * 256);
   s->bad_input = (uint32_t*)(b + table_bytes(max_worlds) - 256);
   uint8_t* planes = b + table_bytes(max_worlds);
-  const uint64_t plane = plane_bytes(arena_cells);
-  g.sugar = planes;  // one byte per cell in a plane sized like the others
-  g.cap = (const int32_t*)(planes + plane);
-  g.occ = (uint32_t*)(planes + 2 * plane);
-  g.req = (uint32_t*)(planes + 3 * plane);
-  g.breq = (uint32_t*)(planes + 4 * plane);
+  const uint64_t bytes = byte_plane_bytes(arena_cells);
+  g.sugar = planes;
+  g.cap = planes + bytes;
+  g.req = planes + 2 * bytes;
+  g.breq = (uint32_t*)(planes + 3 * bytes);
   g.arena = arena_cells;
   g.max_worlds = max_worlds;
   g.max_age = rules->max_age;
@@ -521,9 +636,11 @@ int dsoar_sugar_read_world(dsoar_sugar* s, uint32_t slot, int32_t* sugar_dev, ui
     return DSOAR_ERR_INVALID_ARG;
   hipStream_t st = (hipStream_t)stream;
   const uint32_t n = s->h_side[slot] * s->h_side[slot];
-  hipLaunchKernelGGL(sugar_read_kernel, dim3((n + 255) / 256), dim3(256), 0, st, s->heap->dev, s->g, s->h_off[slot], n,
-                     sugar_dev, occ_dev, a_sugar_dev, a_metab_dev, a_vision_dev, a_age_dev);
+  const ReadArgs r{slot, s->h_off[slot], occ_dev, a_sugar_dev, a_metab_dev, a_vision_dev, a_age_dev};
+  hipLaunchKernelGGL(sugar_read_kernel, dim3((n + 255) / 256), dim3(256), 0, st, s->g, r, n, sugar_dev);
   DSOAR_LAUNCHED(s->heap);
+  const int rc = launch_doall<AgentRead>(s->heap, kAgent, r, DSOAR_DO_PERSISTENT, st);
+  if (rc) return rc;
   if (moves) {
     uint64_t m[kMoveShards];
     DSOAR_HIP(s->heap, hipMemcpyAsync(m, s->g.w_moves + (uint64_t)slot * kMoveShards, sizeof(m), hipMemcpyDeviceToHost, st));

@@ -29,8 +29,8 @@ CAL_BYTES_KIB = 256 * 1024  # the calibration add reads and writes 256 MiB
 METHOD_KIND = {
     "AlivePrep": "gol_alive_prep", "CandPrep": "gol_cand_prep", "AliveUpdate": "gol_alive_update",
     "CandUpdate": "gol_cand_update", "MicroUpdate": "micro_update", "MicroCull": "micro_cull",
-    "Choose": "sugar_choose", "Move": "sugar_move", "Eat": "sugar_eat", "Request": "sugar_request",
-    "Birth": "sugar_birth", "VisitCount": "visit_count", "DeleteIfMod": "delete_if_mod",
+    "Choose": "sugar_choose", "Move": "sugar_move", "Eat": "sugar_eat", "MoveEat": "sugar_move_eat", "Request": "sugar_request",
+    "Birth": "sugar_birth", "AgentRead": "sugar_read", "VisitCount": "visit_count", "DeleteIfMod": "delete_if_mod",
     "FieldGather": "gather", "GolDeleteWorld": "gol_delete_world", "SugarDeleteWorld": "sugar_delete_world",
     "Decide": "traffic_decide", "Drive": "traffic_drive", "BodyForce": "collide_force",
     "BodyMove": "collide_move", "BodyRoot": "collide_root", "BodyTarget": "collide_target", "BodyMerge": "collide_merge",
