@@ -211,7 +211,9 @@ int dsoar_heap_set_type_policy(dsoar_heap* heap, uint32_t type, uint32_t policy)
  * level (and the lowest free slots of a block), the sequential choice.
  * DSOAR_SEARCH_XCD: the hash, with the top level's choice narrowed to the
  * eighth of the top container that the wavefront's XCD owns, so that the
- * eight XCDs mostly work in disjoint parts of the heap.  Other values:
+ * eight XCDs mostly work in disjoint parts of the heap; Sugarscape then also
+ * cuts its do-alls' lists and its initial cells into eight runs, one per XCD,
+ * so that an XCD's agents stay in one part of the grid.  Other values:
  * DSOAR_ERR_INVALID_ARG. */
 enum { DSOAR_SEARCH_HASHED = 0, DSOAR_SEARCH_LOWEST = 1, DSOAR_SEARCH_XCD = 2 };
 int dsoar_heap_set_search(dsoar_heap* heap, uint32_t policy);

@@ -183,6 +183,8 @@ SUGAR_MAX = 127  # a cell keeps its sugar and capacity in seven bits
 class Sugarscape:
     """The Sugarscape-style agent model of one world as objects in a device heap."""
 
+    XCD_MIN_CELLS = 1 << 21
+
     def __init__(self, inp, rules: dict, capacity: int = 64, num_blocks: int | None = None, stream=None,
                  device="cuda"):
         self.side = inp.side
@@ -194,6 +196,12 @@ class Sugarscape:
         self.stream = stream if stream is not None else torch.cuda.Stream(device=device)
         blocks = num_blocks or max(64, 1 << (max(1, -(-n // (capacity or 64))) - 1).bit_length())
         self.heap = Heap(blocks, capacity, SUGAR_TYPE, device=device, stream=self.stream)
+        # Worlds whose two byte planes outgrow an XCD's 4 MB L2: each XCD keeps
+        # one run of the agents and, as children go to its part of the heap,
+        # one strip of the torus (2048^2: 22.9 -> 21.3 ms per 100 steps; 1024^2,
+        # which fits, 9.7 -> 10.4).
+        if n >= self.XCD_MIN_CELLS:
+            self.heap.set_search(C.SEARCH_XCD)
         self.lib = self.heap.lib
         nbytes = int(self.lib.dsoar_sugar_bytes(self.side))
         if nbytes == 0:

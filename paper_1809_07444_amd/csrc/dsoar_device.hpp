@@ -100,6 +100,8 @@ struct DevHeap {
   uint32_t bm_units;        // 32-bit units per bitmap (all levels, padded)
   uint32_t bm_off[kMaxLevels];  // unit offset of each level in a bitmap
   uint32_t search_start;    // kStartHashed, kStartLowest or kStartXcd
+  uint32_t search_keep;     // start bits that name a search's part of the bitmap (kStartXcd: the
+                            // top three of the top level's digit, one value per XCD)
   uint32_t bulk_min;        // requests of at least this many take whole free blocks
   uint32_t fresh_types;     // bit t: requests of type t skip the active lookup
   uint32_t bounded_types;   // bit t: at most kBoundedPasses active lookups per request of type t
@@ -216,6 +218,12 @@ __device__ __forceinline__ uint32_t hash32(uint32_t x) {
   x *= 0x846ca68bu;
   x ^= x >> 16;
   return x;
+}
+
+// Start of a search repeated after a failure: another hash in the same part of
+// the bitmap.
+__device__ __forceinline__ uint32_t restart(uint32_t start, uint32_t salt, uint32_t keep) {
+  return (start & keep) | (hash32(start + salt) & ~keep);
 }
 
 // Stress builds (compiled with DSOAR_CHAOS): at each named race window a
@@ -385,6 +393,7 @@ struct Bitmap {
   uint32_t lg;  // log2 of the container width: 6 or 5
   uint64_t* retry_flag;
   const uint32_t* off;  // unit offset of each level (in the kernel's arguments)
+  uint32_t keep;        // start bits that a repeated search keeps (DevHeap::search_keep)
 
   // 64-bit group g of level 0.
   __device__ __forceinline__ uint64_t* group(uint32_t g) const { return reinterpret_cast<uint64_t*>(units) + g; }
@@ -395,7 +404,7 @@ struct Bitmap {
 template <class H>
 __device__ __forceinline__ Bitmap heap_bitmap(const H& h, uint32_t k) {
   return Bitmap{h.bitmaps + (uint64_t)k * h.bm_units, h.num_blocks, h.nlevels, heap_lg(h), h.ctrl + kCtlRetryLimit,
-                h.bm_off};
+                h.bm_off, h.search_keep};
 }
 template <class H>
 __device__ __forceinline__ Bitmap free_bm(const H& h) { return heap_bitmap(h, 0); }
@@ -743,7 +752,7 @@ __device__ inline int32_t bm_find_clear(const Bitmap& b, uint32_t start, uint32_
     const int32_t i = bm_try_find_set(b, start);
     if (i != kFail && bm_try_clear(b, (uint32_t)i)) return i;
     if (i == kFail && load_top(b) == 0) return kFail;
-    start = hash32(start + 0x9e3779b9u + spins);
+    start = restart(start, 0x9e3779b9u + spins, b.keep);
   }
   lead_flag(b.retry_flag);
   return kFail;
@@ -779,7 +788,7 @@ __device__ inline uint64_t bm_take_word(const Bitmap& b, uint32_t start, uint32_
     } else if (load_top(b) == 0) {
       return 0;
     }
-    start = hash32(start + 0x9e3779b9u + spins);
+    start = restart(start, 0x9e3779b9u + spins, b.keep);
   }
   lead_flag(b.retry_flag);
   return 0;
@@ -874,6 +883,15 @@ __device__ __forceinline__ uint32_t* wave_hints() {
   return s_hints + ((threadIdx.x >> 6) & 15u) * (kMaxTypes + 1);
 }
 
+// Workgroup index for creations that take their items in order: under the
+// per-XCD search policy each XCD takes one run of the items, as it does of a
+// do-all's list.
+template <class H>
+__device__ __forceinline__ uint32_t creation_wg(const H& h) {
+  const uint32_t b = blockIdx.x, n = gridDim.x >> 3;
+  return h.search_start == kStartXcd && b < 8u * n ? (b & 7u) * n + (b >> 3) : b;
+}
+
 // Start value of this wavefront's bitmap searches (and slot rotation) under
 // the heap's search-start policy.  Workgroups are dispatched to the eight
 // XCDs round-robin, so blockIdx.x mod 8 is the XCD.
@@ -881,13 +899,9 @@ template <class H>
 __device__ __forceinline__ uint32_t search_start(const H& h) {
   if (h.search_start == kStartLowest) return 0u;
   const uint32_t r = bcast32(hash32((blockIdx.x << 5) ^ (threadIdx.x >> 6) ^ 0x5bd1e995u));
-  if (h.search_start != kStartXcd) return r;
-  const uint32_t lg = heap_lg(h);
-  const uint32_t tsh = lg * (h.nlevels - 1);
-  const uint32_t sh = tsh >= 30 ? tsh - 30 : tsh;  // the top level's digit (as level_digit)
-  const uint32_t span = (1u << lg) >> 3;                  // an eighth of its values
-  const uint32_t digit = (blockIdx.x & 7u) * span + ((r >> sh) & (span - 1u));
-  return (r & ~(((1u << lg) - 1u) << sh)) | (digit << sh);
+  const uint32_t keep = h.search_keep;
+  if (!keep) return r;
+  return (r & ~keep) | (((blockIdx.x & 7u) << __builtin_ctz(keep)) & keep);
 }
 
 // Alg. 1 for all lanes of this wavefront that call it with the same `type`
@@ -1094,7 +1108,7 @@ __device__ __forceinline__ void new_many(const H& h, uint32_t type, uint32_t k, 
           gained += gc;
         }
         if (gained) act_hint = (uint32_t)aw;
-        if (gained == 0 && cur == kFail) start = hash32(start + it + 1);
+        if (gained == 0 && cur == kFail) start = restart(start, it + 1, h.search_keep);
         continue;
       }
     }
@@ -1109,7 +1123,7 @@ __device__ __forceinline__ void new_many(const H& h, uint32_t type, uint32_t k, 
         // fails only when no block has room (Sec. 2.2).
         const int64_t nfree = free_block_count(h);
         active_first = true;
-        start = hash32(start + it + 1);
+        start = restart(start, it + 1, h.search_keep);
         if (nfree != 0) {
           // A block is free or about to become findable: look again.
           if (++wait_rounds >= kFreeWaitLimit) {
@@ -1167,7 +1181,7 @@ __device__ __forceinline__ void new_many(const H& h, uint32_t type, uint32_t k, 
       }
       if (got != take) ++retries;
       if (got == 0) {
-        if (cur == kFail) start = hash32(start + it + 1);
+        if (cur == kFail) start = restart(start, it + 1, h.search_keep);
         continue;
       }
     }

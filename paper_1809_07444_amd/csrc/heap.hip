@@ -535,7 +535,7 @@ struct LevelOffsets {
 
 __global__ void bitmap_ops_kernel(uint32_t* units, uint32_t nbits, uint32_t lg, LevelOffsets lv, const uint32_t* ops,
                                   uint32_t n, const uint32_t* starts, int32_t* results, uint64_t* retry_flag) {
-  const Bitmap b{units, nbits, num_levels(nbits, lg), lg, retry_flag, lv.off};
+  const Bitmap b{units, nbits, num_levels(nbits, lg), lg, retry_flag, lv.off, 0u};
   // One wavefront per operation, with the grid's stride in wavefronts.
   const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
   for (uint64_t op = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; op < n; op += waves) {
@@ -868,6 +868,7 @@ int dsoar_heap_create(const dsoar_heap_desc* desc, void* dev_mem, size_t dev_byt
   d.bm_units = (uint32_t)(p.L.bitmap_stride / 4);
   for (uint32_t l = 0; l < kMaxLevels; ++l) d.bm_off[l] = level_offset(d.num_blocks, d.bm_lg, l);
   d.search_start = kStartHashed;
+  d.search_keep = 0;
   for (uint32_t t = 0; t < desc->num_types; ++t)
     for (uint32_t f = 0; f < desc->types[t].num_fields; ++f) {
       d.field_loc[t][f] = p.L.field_offset[t][f] | ((desc->types[t].field_bytes[f] == 8 ? 3u : 2u) << 24);
@@ -1022,6 +1023,8 @@ int dsoar_heap_set_search(dsoar_heap* h, uint32_t policy) {
                     DSOAR_SEARCH_XCD == kStartXcd,
                 "search policy numbering");
   h->dev.search_start = policy;
+  const uint32_t lg = h->dev.bm_lg, top = lg * (h->dev.nlevels - 1);  // the top level's digit, as level_digit
+  h->dev.search_keep = policy == kStartXcd ? 7u << ((top >= 30 ? top - 30 : top) + lg - 3) : 0u;
   h->config_epoch++;
   return DSOAR_OK;
 }

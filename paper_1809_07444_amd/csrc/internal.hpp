@@ -457,7 +457,7 @@ __device__ __forceinline__ void doall_split64(const H& h, uint32_t type, const u
 // returning true to delete self, or the load / apply pair described above.
 // One wavefront's share of a do-all over one list: entries gw, gw + nw, ...
 // (or passes of several entries), visit and free counts accumulated.
-template <class Method, bool kOnlyThis, class H>
+template <class Method, bool kOnlyThis, bool kRun = false, class H>
 __device__ __forceinline__ void doall_list(const H& h, uint32_t type, const uint32_t* __restrict__ R,
                                            const uint64_t* __restrict__ S, uint32_t count, uint32_t gw,
                                            uint32_t nw, const typename Method::Args& args, uint32_t& visits,
@@ -507,10 +507,15 @@ __device__ __forceinline__ void doall_list(const H& h, uint32_t type, const uint
     // This wavefront's first entry of the single-object loop, loaded before
     // the count is known (R and S hold num_blocks entries, so the load stays
     // in bounds): on lists of about one entry per wavefront the count's load
-    // and the entry's then take one round trip instead of two.
-    const uint32_t first = gw < h.num_blocks ? gw : h.num_blocks - 1;
-    const uint32_t first_bid = R[first];
-    const uint64_t first_snap = S[first];
+    // and the entry's then take one round trip instead of two.  (Not on a run
+    // of the list, which starts where the count says.)
+    uint32_t first_bid = 0;
+    uint64_t first_snap = 0;
+    if constexpr (!kRun) {
+      const uint32_t first = gw < h.num_blocks ? gw : h.num_blocks - 1;
+      first_bid = R[first];
+      first_snap = S[first];
+    }
     bool pairs = false;
     if constexpr (HasPair<Method>::value) pairs = count >= 2 * nw;
     if (pairs) {
@@ -534,8 +539,9 @@ __device__ __forceinline__ void doall_list(const H& h, uint32_t type, const uint
       }
     } else {
       for (uint32_t e = gw; e < count; e += nw) {
-        const uint32_t bid = e == gw ? first_bid : R[e];
-        const uint64_t snap = e == gw ? first_snap : S[e];
+        const bool have = !kRun && e == gw;
+        const uint32_t bid = have ? first_bid : R[e];
+        const uint64_t snap = have ? first_snap : S[e];
         visits += (uint32_t)__popcll(snap);
         settle();
         const bool del = run_slot<Method>(h, type, make_obj(bid, lane), (snap >> lane) & 1ull, args);
@@ -566,22 +572,51 @@ __device__ __forceinline__ void doall_list(const H& h, uint32_t type, const uint
   }
 }
 
+// Adds a wavefront's visits and deletes to the counters.
+template <class Method, class H>
+__device__ __forceinline__ void doall_count(const H& h, uint32_t type, uint32_t visits, uint32_t freed) {
+  if (Phases<Method>::value && visits) lead_add(shard(h) + kCntVisits + type, visits * Phases<Method>::value);
+  if (freed) lead_add(shard(h) + kCntFrees + type, freed);
+}
+
 // Wave-uniform index of this wavefront in the grid.
 __device__ __forceinline__ uint32_t grid_wave() {
   return blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 }
+
+// A method may declare
+//   static constexpr bool kXcdRuns = true;
+// when its objects read and write planes laid out like the list (a grid, with
+// the objects of neighbouring cells near each other in the heap): under the
+// per-XCD search policy its lists are then cut into eight runs, one per XCD
+// (workgroups go to the XCDs round-robin), as the allocations of an XCD's
+// wavefronts are in its eighth of the heap, so each XCD's L2 sees one part of
+// the planes.
+template <class M, class = void>
+struct XcdRuns : std::false_type {};
+template <class M>
+struct XcdRuns<M, std::void_t<decltype(M::kXcdRuns)>> : std::integral_constant<bool, M::kXcdRuns> {};
 
 template <class Method, uint32_t LG, bool kMany = false>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kMany ? MinWaves<Method>::value : 1)))
 doall_kernel(DevHeapW<LG> h, uint32_t type, const uint32_t* __restrict__ R,
                                                       const uint64_t* __restrict__ S, const uint32_t* count_ptr,
                                                       typename Method::Args args) {
-  const uint32_t nw = gridDim.x * (blockDim.x >> 6);
+  const uint32_t wpb = blockDim.x >> 6, nw = gridDim.x * wpb;
   uint32_t visits = 0, freed = 0;
-  doall_list<Method, DeletesOnlyThis<Method>::value>(h, type, R, S, bcast32(*count_ptr), grid_wave(), nw, args,
-                                                      visits, freed);
-  if (visits) lead_add(shard(h) + kCntVisits + type, visits * Phases<Method>::value);
-  if (freed) lead_add(shard(h) + kCntFrees + type, freed);
+  constexpr bool kOnlyThis = DeletesOnlyThis<Method>::value;
+  if constexpr (XcdRuns<Method>::value) {
+    if (h.search_start == kStartXcd && !(gridDim.x & 7u)) {
+      const uint32_t x = blockIdx.x & 7u, count = bcast32(*count_ptr);
+      const uint32_t lo = (uint32_t)(((uint64_t)count * x) >> 3), hi = (uint32_t)(((uint64_t)count * (x + 1)) >> 3);
+      const uint32_t gw = (blockIdx.x >> 3) * wpb + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+      doall_list<Method, kOnlyThis, true>(h, type, R + lo, S + lo, hi - lo, gw, nw >> 3, args, visits, freed);
+      doall_count<Method>(h, type, visits, freed);
+      return;
+    }
+  }
+  doall_list<Method, kOnlyThis>(h, type, R, S, bcast32(*count_ptr), grid_wave(), nw, args, visits, freed);
+  doall_count<Method>(h, type, visits, freed);
 }
 
 // Two do-alls in one launch, over the lists of two types: every wavefront
@@ -603,12 +638,10 @@ doall2_kernel(DevHeapW<LG> h, uint32_t t1, const uint32_t* __restrict__ R1,
   uint32_t visits = 0, freed = 0;
   constexpr bool kOnlyThis = DeletesOnlyThis<M1>::value && DeletesOnlyThis<M2>::value;
   doall_list<M1, kOnlyThis>(h, t1, R1, S1, bcast32(*c1), gw, nw, a1, visits, freed);
-  if (visits) lead_add(shard(h) + kCntVisits + t1, visits * Phases<M1>::value);
-  if (freed) lead_add(shard(h) + kCntFrees + t1, freed);
+  doall_count<M1>(h, t1, visits, freed);
   visits = freed = 0;
   doall_list<M2, kOnlyThis>(h, t2, R2, S2, bcast32(*c2), gw, nw, a2, visits, freed);
-  if (visits) lead_add(shard(h) + kCntVisits + t2, visits * Phases<M2>::value);
-  if (freed) lead_add(shard(h) + kCntFrees + t2, freed);
+  doall_count<M2>(h, t2, visits, freed);
 }
 
 // Large heaps: those whose enumeration takes wide tiles (more than

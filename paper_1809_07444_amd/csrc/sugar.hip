@@ -193,6 +193,7 @@ __device__ __forceinline__ uint32_t seen_cell(const Where& c, uint32_t p, uint32
 
 struct Choose {
   static constexpr uint32_t kKind = 40;
+  static constexpr bool kXcdRuns = true;
   using Args = Grid;
   // The best of the cells in sight: most sugar, then nearest, then lowest
   // index.  The order in which the candidates are compared does not matter
@@ -235,6 +236,7 @@ struct Choose {
 // 82), 84 fused (Choose 68), 90 with the requests (Choose 50).
 struct MoveEat {
   static constexpr uint32_t kKind = 41;
+  static constexpr bool kXcdRuns = true;
   static constexpr uint32_t kPhases = 2;
   static constexpr uint32_t kMinWaves = 8;
   static constexpr bool kDeletesOnlyThis = true;
@@ -289,6 +291,7 @@ struct MoveEat {
 
 struct Request {
   static constexpr uint32_t kKind = 43;
+  static constexpr bool kXcdRuns = true;
   using Args = Grid;
   template <class H>
   static __device__ bool run(const H& h, uint32_t, uint32_t self, const Args& g) {
@@ -319,6 +322,7 @@ struct Request {
 
 struct Birth {
   static constexpr uint32_t kKind = 44;
+  static constexpr bool kXcdRuns = true;
   static constexpr uint32_t kMinWaves = 8;
   using Args = Grid;
   template <class H>
@@ -416,7 +420,7 @@ template <uint32_t LG>
 __global__ void sugar_admit_kernel(DevHeapW<LG> h, Grid g, uint32_t slot, uint32_t off, uint32_t n, const int32_t* sugar,
                                    const int32_t* cap, const uint8_t* occ, const int32_t* as, const int32_t* am,
                                    const int32_t* av, const int32_t* aa) {
-  const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t c = creation_wg(h) * blockDim.x + threadIdx.x;
   if (c >= n) return;
   const uint32_t q = off + c;
   const uint32_t b = byte_here(where(g, slot, q));
