@@ -80,28 +80,19 @@ def parse():
 
 def gol_kernel_bytes(kind, launches, st, M, init_alive):
     A, K = 1, 2  # Alive, Candidate type ids
-    va, vk = st["visits"][A] / 2, st["visits"][K] / 2     # each type is visited by two do-alls
+    va, vk = st["visits"][A] / 2, st["visits"][K] / 2     # each type's do-all is two phases
     cands = st["allocs"][K]
     births, deaths = st["allocs"][A] - init_alive, st["frees"][A]
-    if kind == "gol_alive_prep":
-        # this: cell and world read, action written; new Candidates: their
-        # three fields; other: the live bits of the 24 surrounding cells and
-        # the world's offset and side.
-        return va * 12 + cands * 12 + va / 64 * 12, va * (3 + 8)
-    if kind == "gol_cand_prep":
-        return vk * 12 + vk / 64 * 12, vk * (1 + 8)
-    if kind == "gol_alive_update":
-        # this: action read, and the cell of a dying one; other: its Cell's
-        # index word and field and its live byte.
-        return va * 4 + deaths * 4 + va / 64 * 12, deaths * (4 + 4 + 1)
-    if kind == "gol_cand_update":
-        # this: cell, world and action read; new Alive objects: three fields;
-        # other: the born cell's index word, Cell field and live byte.
-        return vk * 12 + births * 12 + vk / 64 * 12, births * (4 + 4 + 1)
-    if kind == "gol_update":  # phases 3 and 4 in one launch
-        a = gol_kernel_bytes("gol_alive_update", launches, st, M, init_alive)
-        c = gol_kernel_bytes("gol_cand_update", launches, st, M, init_alive)
-        return a[0] + c[0], a[1] + c[1]
+    if kind == "gol_alive_prep":  # and the dying cells
+        # this: cell and world read; new Candidates: two fields; other: the
+        # live bits of the 24 surrounding cells, the world's offset and side,
+        # and a dying cell's index word, Cell field and live bit.
+        return va * 8 + cands * 8 + va / 64 * 12, va * (3 + 8) + deaths * (4 + 4 + 1)
+    if kind == "gol_update":  # the Candidates
+        # this: cell and world read; new Alive objects: three fields; other:
+        # eight live bits, the world's offset and side, and a born cell's
+        # index word, Cell field and live bit.
+        return vk * 8 + births * 12 + vk / 64 * 12, vk * (1 + 8) + births * (4 + 4 + 1)
     if kind == "enumerate":
         return launches * (M / 8) + (va + vk) / 64 * 20
     return None
@@ -124,7 +115,7 @@ def sugar_kernel_bytes(kind, launches, st, M, init_agents, cells):
     request or birth touches."""
     v = st["visits"][0] / 5  # five phases per step
     births = st["allocs"][0] - init_agents
-    per = {"sugar_choose": (16, 25 + 8 + 4), "sugar_move_eat": (36, 8 + 4),
+    per = {"sugar_choose": (16, 25 + 8 + 4), "sugar_eat": (36, 8 + 4),
            "sugar_request": (12, 8 + 16 + 4), "sugar_birth": (12, 4)}
     if kind in per:
         this, other = per[kind]
@@ -425,7 +416,7 @@ class TrafficWorkload(GolWorkload):
     def kernel_bytes(self, kind, launches, st):
         v = st["visits"][0] / 2  # two phases per step visit every car
         cars0 = int((self.inp.vel >= 0).sum())
-        if kind == "traffic_step":
+        if kind == "traffic_entry":  # the whole step
             # (this + new objects, other).  Cell and speed read, cell, speed
             # and next speed written; new cars: three fields each; other (two
             # bytes per road cell): up to vmax cells ahead read and one

@@ -241,12 +241,12 @@ int dsoar_heap_set_unroll(dsoar_heap* heap, uint32_t blocks_per_pass);
  * dsoar_heap_timing synchronises on the last event, aggregates the recorded
  * launches by kernel kind into kinds/counts/total_ms, and clears the records.
  * Kinds: 1 enumeration; do-alls 10 visit count, 11 delete-if-mod, 12 gather,
- * 20/21 micro update/cull, 30..33 Game of Life phases 1..4 (35: phases 3 and
- * 4 in one launch, 34 world deletion), 40..45 Sugarscape phases (41: move and
- * eat) and world deletion, 51 traffic step, 60..64 collisions, 70..76 wa-tor;
- * other kernels 22 micro creation, 36/37 Game of Life initial cells and
- * admission, 46/47 Sugarscape regrow and admission, 48
- * Sugarscape readout, 53 traffic initial cars, 66 collisions initial bodies, 77/78 wa-tor initial sea and
+ * 20/21 micro update/cull, 30/35 Game of Life, the Alive and the Candidate
+ * objects (34 world deletion), 40 and 42..45 Sugarscape choose, move and eat,
+ * request, birth and world deletion, 48 readout, 60..64 collisions, 70..76
+ * wa-tor; other kernels 22 micro creation, 36/37 Game of Life initial cells
+ * and admission, 46/47 Sugarscape regrow and admission, 52/53 traffic step and
+ * initial cars, 66 collisions initial bodies, 77/78 wa-tor initial sea and
  * step tick. */
 int dsoar_heap_set_timing(dsoar_heap* heap, int enable);
 int dsoar_heap_timing(dsoar_heap* heap, uint32_t* kinds, uint32_t* counts, double* total_ms,

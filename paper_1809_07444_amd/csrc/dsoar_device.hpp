@@ -926,19 +926,15 @@ __device__ __forceinline__ uint32_t search_start(const H& h) {
 // whose OR fills the block clears active[type] (Alg. 1, FULL).
 // Requests are numbered by lane order (exclusive prefix sums from bit-sliced
 // ballots, exact under any divergence) and handed out in that order.
-template <class F, class H>
-__device__ __forceinline__ void new_many(const H& h, uint32_t type, uint32_t k, F&& f) {
-  uint32_t prefix = 0, n = 0;
-#pragma unroll
-  for (uint32_t b = 0; b < 8; ++b) {
-    const uint64_t m = __ballot((k >> b) & 1u);
-    prefix += lanes_below(m) << b;
-    n += (uint32_t)__popcll(m) << b;
-  }
-  if (n == 0) return;
+//
+// new_core serves both forms below: n requests of the wavefront, handed out by
+// hand(from, cnt, obj_of), which calls f for requests from .. from + cnt - 1
+// with the handles obj_of(0) .. obj_of(cnt - 1).
+template <class Hand, class H>
+__device__ __forceinline__ void new_core(const H& h, uint32_t type, uint32_t n, Hand&& hand) {
   const Bitmap active = active_bm(h, type);
   const uint32_t rot = search_start(h);
-  const uint32_t c = cap_of(h, type);
+  const uint32_t c = cap_of(h, type), csh = (uint32_t)__builtin_ctz(c);  // a power of two
   const uint64_t cap = capmask_of(h, type);
   uint32_t start = rot;
   uint32_t served = 0, retries = 0, slow = 0, fails = 0, oom_rounds = 0, wait_rounds = 0;
@@ -971,7 +967,7 @@ __device__ __forceinline__ void new_many(const H& h, uint32_t type, uint32_t k, 
       // rest of the request right after: that block is taken in the same
       // atomic and published holding only the rest (and marked active).
       uint32_t word = 0;
-      const uint32_t full = want / c, rest = want - full * c;
+      const uint32_t full = want >> csh, rest = want & (c - 1u);
       const bool with_rest = fresh && rest != 0 && full < 64;
       const uint32_t nb = full < 64 ? full + (with_rest ? 1u : 0u) : 64u;
       const uint64_t blocks = bm_take_word(free_bm(h), start, nb, &word, free_hint);
@@ -1012,12 +1008,9 @@ __device__ __forceinline__ void new_many(const H& h, uint32_t type, uint32_t k, 
       // Counted as taken once nothing of them is left to publish.
       lead_add(shard(h) + kCntBlocksTaken, cnt_b);
       slow += cnt_b;
-      const uint32_t lo = prefix > served ? prefix : served;
-      const uint32_t hi = prefix + k < served + span ? prefix + k : served + span;
-      for (uint32_t r = lo; r < hi; ++r) {
-        const uint32_t q = r - served;
-        f(r - prefix, make_obj(word * 64 + nth_set_bit(blocks, q / c), q % c));
-      }
+      hand(served, span, [&](uint32_t q) __attribute__((always_inline)) {
+        return make_obj(word * 64 + nth_set_bit(blocks, q >> csh), q & (c - 1u));
+      });
       served += span;
       continue;
     }
@@ -1101,9 +1094,7 @@ __device__ __forceinline__ void new_many(const H& h, uint32_t type, uint32_t k, 
           if (!g) continue;
           const uint32_t gb = (uint32_t)__builtin_amdgcn_readlane(my_bid, l);
           const uint32_t gc = (uint32_t)__popcll(g);
-          const uint32_t lo = prefix > served ? prefix : served;
-          const uint32_t hi = prefix + k < served + gc ? prefix + k : served + gc;
-          for (uint32_t r = lo; r < hi; ++r) f(r - prefix, make_obj(gb, nth_set_bit(g, r - served)));
+          hand(served, gc, [&](uint32_t q) __attribute__((always_inline)) { return make_obj(gb, nth_set_bit(g, q)); });
           served += gc;
           gained += gc;
         }
@@ -1186,9 +1177,7 @@ __device__ __forceinline__ void new_many(const H& h, uint32_t type, uint32_t k, 
       }
     }
     const uint32_t cnt = (uint32_t)__popcll(got);
-    const uint32_t lo = prefix > served ? prefix : served;
-    const uint32_t hi = prefix + k < served + cnt ? prefix + k : served + cnt;
-    for (uint32_t r = lo; r < hi; ++r) f(r - prefix, make_obj((uint32_t)bid, nth_set_bit(got, r - served)));
+    hand(served, cnt, [&](uint32_t q) __attribute__((always_inline)) { return make_obj((uint32_t)bid, nth_set_bit(got, q)); });
     served += cnt;
   }
   if (is_first_active()) {
@@ -1196,13 +1185,42 @@ __device__ __forceinline__ void new_many(const H& h, uint32_t type, uint32_t k, 
     hints[type] = act_hint;
   }
   if (oom) lead_flag(h.ctrl + kCtlOom);
-  if (oom || gave_up)
-    for (uint32_t r = prefix > served ? prefix : served; r < prefix + k; ++r) f(r - prefix, kNull);
+  if (oom || gave_up) hand(served, n - served, [&](uint32_t) { return kNull; });
   uint64_t* sh = shard(h);
   if (served) lead_add(sh + kCntAllocs + type, served);
   if (retries) lead_add(sh + kCntReserveRetries, retries);
   if (slow) lead_add(sh + kCntSlowPaths, slow);
   if (fails) lead_add(sh + kCntFindFails, fails);
+}
+
+template <class F, class H>
+__device__ __forceinline__ void new_many(const H& h, uint32_t type, uint32_t k, F&& f) {
+  uint32_t prefix = 0, n = 0;
+#pragma unroll
+  for (uint32_t b = 0; b < 8; ++b) {
+    const uint64_t m = __ballot((k >> b) & 1u);
+    prefix += lanes_below(m) << b;
+    n += (uint32_t)__popcll(m) << b;
+  }
+  if (n == 0) return;
+  new_core(h, type, n, [&](uint32_t from, uint32_t cnt, auto&& obj_of) __attribute__((always_inline)) {
+    const uint32_t lo = prefix > from ? prefix : from;
+    const uint32_t hi = prefix + k < from + cnt ? prefix + k : from + cnt;
+    for (uint32_t r = lo; r < hi; ++r) f(r - prefix, obj_of(r - from));
+  });
+}
+
+// The same for n objects (wave-uniform) that the wavefront creates as a whole,
+// every lane active: f(r, obj) is called by lane r % 64 for the r-th of them.
+// Where the requests of a wavefront are a queue of items, this spreads them
+// evenly over the lanes, and neighbouring lanes write neighbouring slots.
+template <class F, class H>
+__device__ __forceinline__ void new_items(const H& h, uint32_t type, uint32_t n, F&& f) {
+  if (n == 0) return;
+  const uint32_t lane = lane_id();
+  new_core(h, type, n, [&](uint32_t from, uint32_t cnt, auto&& obj_of) __attribute__((always_inline)) {
+    for (uint32_t r = from + ((lane - from) & 63u); r < from + cnt; r += 64) f(r, obj_of(r - from));
+  });
 }
 
 // Device `new`: every calling lane gets one object of `type`.  Lanes may pass

@@ -5,17 +5,22 @@
 // position -> handle index (a plane of live bits beside it copies the flags
 // for the neighbour reads); Alive {cell, world, action} exists for every live
 // cell; Candidate {cell, world, action} exists during a generation for every
-// dead cell next to a live one.  One generation is four do-alls:
-//   1 Alive:     count live neighbours -> action (die unless 2 or 3); create
-//                the Candidate of each dead neighbour whose first live
-//                neighbour (in a fixed direction order) is this cell, so
-//                that every such cell gets exactly one, without atomics.
-//   2 Candidate: action = born iff exactly 3 live neighbours.
-//   3 Alive:     dying ones clear their Cell's alive flag and delete themselves.
-//   4 Candidate: born ones set their Cell's alive flag and create an Alive;
-//                every Candidate deletes itself.
-// Live flags are only read in phases 1-2 and only written in 3-4, so the
-// kernel boundaries make the update synchronous.
+// dead cell next to a live one.  One generation is two do-alls over two planes
+// of live bits, the state that it reads and the one it makes (a copy of the
+// former, made beside the first enumeration, in which only the cells that die
+// or are born are changed):
+//   1 Alive:     count live neighbours: die unless 2 or 3 (clear the Cell's
+//                flag and the new plane's bit, delete this); create the
+//                Candidate of each dead neighbour whose first live neighbour
+//                (in a fixed direction order) is this cell, so that every such
+//                cell gets exactly one, without atomics.
+//   2 Candidate: born iff exactly 3 live neighbours (set the Cell's flag and
+//                the new plane's bit, create an Alive); every Candidate
+//                deletes itself.
+// Neither do-all writes what it reads of other cells, so the update is
+// synchronous.  (With one plane the four phases - both preparations before
+// both updates - took a pass over each list more and passed the decision on in
+// the objects' action fields.)
 #include <string.h>
 
 #include <new>
@@ -27,33 +32,37 @@ namespace {
 
 enum : uint32_t { kCell = 0, kAlive = 1, kCand = 2 };
 enum : uint32_t { kCAlive = 0 };
-enum : uint32_t { kACell = 0, kAWorld = 1, kAAction = 2 };
-constexpr uint32_t kKindGolUpdate = 35;  // timing id of the fused phases 3 and 4
+enum : uint32_t { kACell = 0, kAWorld = 1, kAAction = 2 };  // action: 0 between generations
 
-// Beside the position -> Cell handle index, a live-bit plane holds a copy of
-// every Cell's live flag, one bit per cell in the index's order (bit g % 32
-// of word g / 32; a cell whose Cell is missing, only after an out-of-memory
-// init, reads dead).  The neighbourhood reads of phases 1 and 2 load it: a
-// row's five cells are one pair of dword loads, and the plane of all 256
-// batched worlds (48.8 M cells) is 6 MB, so the rows that the neighbourhoods
-// of a wavefront's scattered cells touch are few cache lines, many of them
-// shared with other wavefronts.  Phases 3 and 4 (which read no neighbours)
-// flip the bits of the cells that die or are born with atomic AND / OR.
+// Beside the position -> Cell handle index, two live-bit planes, one bit per
+// cell in the index's order (bit g % 32 of word g / 32; a cell whose Cell is
+// missing, only after an out-of-memory init, reads dead): the clock's epoch
+// names the one that holds the current state.  A neighbourhood row's five
+// cells are one pair of dword loads, and the plane of all 256 batched worlds
+// (48.8 M cells) is 6 MB, so the rows that the neighbourhoods of a wavefront's
+// scattered cells touch are few cache lines, many of them shared with other
+// wavefronts.
 struct World {
   const uint32_t* cells;  // global cell index -> Cell handle (kNull if missing)
-  const uint32_t* bits;   // live bits
+  uint32_t* plane[2];     // live bits
   const uint32_t* off;    // world -> first global cell index (num_worlds + 1 entries)
   const uint32_t* side;   // world -> side length
+  const StepClock* clock; // epoch: any value, its low bit names the current plane
 };
 
-// Sets the live state of the Cell at global index g, whose handle is wd
-// (its field and its bit); only the cell's own Alive or Candidate does this.
-// False if the Cell is missing (after an out-of-memory init).
+// The plane of the state that `epoch` names.
+__device__ __forceinline__ uint32_t* plane_at(const World& w, uint32_t epoch) {
+  return (epoch & 1u) ? w.plane[1] : w.plane[0];
+}
+
+// Sets the live state of the Cell at global index g, whose handle is wd (its
+// field and its bit in plane `bits`); only the cell's own Alive or Candidate
+// does this.  False if the Cell is missing (after an out-of-memory init).
 template <class H>
-__device__ __forceinline__ bool set_cell_live(const H& h, const World& w, uint32_t g, uint32_t wd, uint32_t live) {
+__device__ __forceinline__ bool set_cell_live(const H& h, uint32_t* bits, uint32_t g, uint32_t wd, uint32_t live) {
   if (wd == kNull) return false;
   *field_ptr<uint32_t>(h, wd, kCell, kCAlive) = live;
-  uint32_t* word = const_cast<uint32_t*>(w.bits) + (g >> 5);
+  uint32_t* word = bits + (g >> 5);
   const uint32_t bit = 1u << (g & 31u);
   if (live)
     __hip_atomic_fetch_or(word, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -160,12 +169,11 @@ __device__ __forceinline__ uint32_t neighbourhood(const uint32_t* bits, uint32_t
   return al & ~(1u << (R * D + R));
 }
 
-// A listed object's cell position.  The do-all methods take two blocks per
-// wavefront pass (run_pair): each lane reads both of its slots' fields and
-// then both positions' neighbourhoods before it uses any of them (a
-// wavefront whose second block is absent skips its reads).  A slot that is
-// not live reads as world 0's corner (side 1 stands in when the world
-// table's slot 0 is empty), so no index is ever formed from its fields.
+// A listed object's cell position.  The do-all methods take one or two list
+// entries per pass: each lane reads its slots' fields and then the positions'
+// neighbourhoods before it uses any of them.  A slot that is not live reads as
+// world 0's corner (side 1 stands in when the world table's slot 0 is empty),
+// so no index is ever formed from its fields.
 struct CellPos {
   uint32_t wid, off, side, x, y;
 };
@@ -182,222 +190,124 @@ __device__ __forceinline__ CellPos cell_pos(const World& w, uint32_t g, uint32_t
   return p;
 }
 
-struct AlivePrep {
+// What a new Candidate or Alive is made from.  The words are kept inverted:
+// workgroups of later kernels read what is left in LDS as search hints
+// (wave_hints), and small numbers such as world 0 would send them all to the
+// same few groups (the initial cells' kernel took 128 instead of 73 us).
+struct NewCell {
+  uint32_t not_g, not_wid;
+};
+
+// The positions a pass holds, and the new cells that each lane claims: bit 8 u
+// + d for direction d of object u (births: bit 8 u).
+struct Cells {
+  uint32_t claims;
+  CellPos p[2];
+};
+
+// Phases 1 and 3.  A wavefront queues the Candidates of its entries: about 200
+// per entry pair on random worlds, handed to the lanes evenly (lane by lane,
+// the lane with the most held the others up, and its slots lay apart).
+struct AliveStep {
   static constexpr uint32_t kKind = 30;
+  static constexpr uint32_t kPhases = 2;
+  static constexpr bool kDeletesOnlyThis = true;
   using Args = World;
-  template <class H>
-  static __device__ __forceinline__ void run_pair(const H& h, uint32_t type, uint32_t s0, bool l0, uint32_t s1,
-                                                  bool l1, const Args& w, bool& d0, bool& d1) {
-    const uint32_t self[2] = {s0, s1};
-    const bool lv[2] = {l0, l1};
-    const uint32_t n = __ballot(l1) ? 2u : 1u;  // objects this wavefront holds per lane
-    uint32_t g[2] = {0, 0}, wid[2] = {0, 0};
+  using Item = NewCell;
+  static constexpr uint32_t kItemType = kCand;
+  static constexpr uint32_t kItems = 256, kClaimBits = 16;
+  using Found = Cells;
+  template <uint32_t N, class H>
+  static __device__ __forceinline__ void find(const H& h, uint32_t type, const uint32_t (&self)[2],
+                                              const bool (&lv)[2], const Args& w, Found& found, bool (&del)[2]) {
+    const uint32_t epoch = w.clock->epoch;
+    const uint32_t* now = plane_at(w, epoch);
+    uint32_t g[N], wid[N], alive[N];
+    CellPos (&p)[2] = found.p;
 #pragma unroll
-    for (uint32_t u = 0; u < 2; ++u) {
-      if (u >= n) break;
+    for (uint32_t u = 0; u < N; ++u) {
       g[u] = *field_ptr<uint32_t>(h, self[u], type, kACell);
       wid[u] = *field_ptr<uint32_t>(h, self[u], type, kAWorld);
     }
-    CellPos p[2];
-    uint32_t alive[2] = {0, 0};
 #pragma unroll
-    for (uint32_t u = 0; u < 2; ++u) p[u] = cell_pos(w, g[u], wid[u], lv[u] && u < n);
-    // Live states of the 24 surrounding cells.  (A cell whose Cell is
-    // missing reads as dead; its Candidate never becomes an Alive.)
+    for (uint32_t u = 0; u < N; ++u) p[u] = cell_pos(w, g[u], wid[u], lv[u]);
+    // Live states of the 24 surrounding cells.  (A cell whose Cell is missing
+    // reads as dead; its Candidate never becomes an Alive.)
 #pragma unroll
-    for (uint32_t u = 0; u < 2; ++u) {
-      if (u >= n) break;
-      alive[u] = neighbourhood<2>(w.bits, p[u].off, p[u].side, p[u].x, p[u].y);
+    for (uint32_t u = 0; u < N; ++u) alive[u] = neighbourhood<2>(now, p[u].off, p[u].side, p[u].x, p[u].y);
+#pragma unroll
+    for (uint32_t u = 0; u < N; ++u) {
+      const uint32_t live = (uint32_t)__popc(alive[u] & ring_mask());
+      del[u] = lv[u] && live != 2 && live != 3;
+      if (del[u]) set_cell_live(h, plane_at(w, epoch + 1), g[u], w.cells[g[u]], 0);
     }
-    uint32_t claim[2];
 #pragma unroll
-    for (uint32_t u = 0; u < 2; ++u) {
-      claim[u] = 0;
+    for (uint32_t u = 0; u < N; ++u) {
+      uint32_t claim = 0;
 #pragma unroll
       for (uint32_t d = 0; d < 8; ++d) {
         const uint32_t b = nb_bit(kDirX[d], kDirY[d]);
         const bool dead = (~alive[u] >> b) & 1u;
-        if (dead && !(alive[u] & owner_mask(d))) claim[u] |= 1u << d;
+        if (dead && !(alive[u] & owner_mask(d))) claim |= 1u << d;
       }
-      if (!lv[u]) claim[u] = 0;
+      if (lv[u]) found.claims |= claim << (8 * u);
     }
-    // One coalesced allocation for the new Candidates of both blocks.
-    const uint32_t k0 = (uint32_t)__popc(claim[0]);
-    new_many(h, kCand, k0 + (uint32_t)__popc(claim[1]), [&](uint32_t j, uint32_t o) {
-      if (o == kNull) return;
-      const uint32_t u = j < k0 ? 0u : 1u;
-      const CellPos& q = u ? p[1] : p[0];
-      const uint32_t n = neighbour(q.off, q.side, q.x, q.y, nth_set_bit(claim[u], u ? j - k0 : j));
-      *field_ptr<uint32_t>(h, o, kCand, kACell) = n;
-      *field_ptr<uint32_t>(h, o, kCand, kAWorld) = q.wid;
-      *field_ptr<uint32_t>(h, o, kCand, kAAction) = 0;
-    });
-#pragma unroll
-    for (uint32_t u = 0; u < 2; ++u) {
-      const uint32_t live = (uint32_t)__popc(alive[u] & ring_mask());
-      if (lv[u]) *field_ptr<uint32_t>(h, self[u], type, kAAction) = (live == 2 || live == 3) ? 0u : 1u;
-    }
-    d0 = d1 = false;
+  }
+  static __device__ __forceinline__ Item item(const Found& f, uint32_t b) {
+    const CellPos& p = b < 8 ? f.p[0] : f.p[1];
+    return {~neighbour(p.off, p.side, p.x, p.y, b & 7u), ~p.wid};
   }
   template <class H>
-  static __device__ __forceinline__ bool run(const H& h, uint32_t type, uint32_t self, const Args& w) {
-    const uint32_t g = *field_ptr<uint32_t>(h, self, type, kACell);
-    const uint32_t wid = *field_ptr<uint32_t>(h, self, type, kAWorld);
-    const uint32_t off = w.off[wid], side = w.side[wid];
-    const uint32_t local = g - off;
-    const uint32_t y = local / side, x = local - y * side;
-    const uint32_t alive = neighbourhood<2>(w.bits, off, side, x, y);
-    uint32_t claim = 0;
-#pragma unroll
-    for (uint32_t d = 0; d < 8; ++d) {
-      const uint32_t b = nb_bit(kDirX[d], kDirY[d]);
-      const bool dead = (~alive >> b) & 1u;
-      if (dead && !(alive & owner_mask(d))) claim |= 1u << d;
-    }
-    const uint32_t live = (uint32_t)__popc(alive & ring_mask());
-    new_many(h, kCand, (uint32_t)__popc(claim), [&](uint32_t j, uint32_t o) {
-      if (o == kNull) return;
-      const uint32_t n = neighbour(off, side, x, y, nth_set_bit(claim, j));
-      *field_ptr<uint32_t>(h, o, kCand, kACell) = n;
-      *field_ptr<uint32_t>(h, o, kCand, kAWorld) = wid;
-      *field_ptr<uint32_t>(h, o, kCand, kAAction) = 0;
-    });
-    *field_ptr<uint32_t>(h, self, type, kAAction) = (live == 2 || live == 3) ? 0u : 1u;
-    return false;
+  static __device__ __forceinline__ void make(const H& h, const Args&, const Item& it, uint32_t o) {
+    *field_ptr<uint32_t>(h, o, kCand, kACell) = ~it.not_g;
+    *field_ptr<uint32_t>(h, o, kCand, kAWorld) = ~it.not_wid;
   }
 };
 
-struct CandPrep {
-  static constexpr uint32_t kKind = 31;
+// Phases 2 and 4.
+struct CandStep {
+  static constexpr uint32_t kKind = 35;
+  static constexpr uint32_t kPhases = 2;
+  static constexpr uint32_t kMinWaves = 8;
+  static constexpr bool kDeletesOnlyThis = true;
   using Args = World;
-  template <class H>
-  static __device__ __forceinline__ void run_pair(const H& h, uint32_t type, uint32_t s0, bool l0, uint32_t s1,
-                                                  bool l1, const Args& w, bool& d0, bool& d1) {
-    const uint32_t self[2] = {s0, s1};
-    const bool lv[2] = {l0, l1};
-    const uint32_t n = __ballot(l1) ? 2u : 1u;
-    uint32_t g[2] = {0, 0}, wid[2] = {0, 0}, alive[2] = {0, 0};
-    CellPos p[2];
+  using Item = NewCell;
+  static constexpr uint32_t kItemType = kAlive;
+  static constexpr uint32_t kItems = 128, kClaimBits = 2;
+  using Found = Cells;
+  template <uint32_t N, class H>
+  static __device__ __forceinline__ void find(const H& h, uint32_t type, const uint32_t (&self)[2],
+                                              const bool (&lv)[2], const Args& w, Found& found, bool (&del)[2]) {
+    const uint32_t then = w.clock->epoch;  // the enumeration of the Candidates has advanced it
+    uint32_t g[N], wid[N], alive[N];
+    CellPos (&p)[2] = found.p;
 #pragma unroll
-    for (uint32_t u = 0; u < 2; ++u) {
-      if (u >= n) break;
+    for (uint32_t u = 0; u < N; ++u) {
       g[u] = *field_ptr<uint32_t>(h, self[u], type, kACell);
       wid[u] = *field_ptr<uint32_t>(h, self[u], type, kAWorld);
     }
 #pragma unroll
-    for (uint32_t u = 0; u < 2; ++u) p[u] = cell_pos(w, g[u], wid[u], lv[u] && u < n);
+    for (uint32_t u = 0; u < N; ++u) p[u] = cell_pos(w, g[u], wid[u], lv[u]);
 #pragma unroll
-    for (uint32_t u = 0; u < 2; ++u) {
-      if (u >= n) break;
-      alive[u] = neighbourhood<1>(w.bits, p[u].off, p[u].side, p[u].x, p[u].y);
+    for (uint32_t u = 0; u < N; ++u)
+      alive[u] = neighbourhood<1>(plane_at(w, then + 1), p[u].off, p[u].side, p[u].x, p[u].y);
+#pragma unroll
+    for (uint32_t u = 0; u < N; ++u) {
+      bool born = lv[u] && __popc(alive[u]) == 3;
+      if (born) born = set_cell_live(h, plane_at(w, then), g[u], w.cells[g[u]], 1);
+      if (born) found.claims |= 1u << (8 * u);
+      del[u] = lv[u];
     }
-#pragma unroll
-    for (uint32_t u = 0; u < 2; ++u)
-      if (lv[u]) *field_ptr<uint32_t>(h, self[u], type, kAAction) = __popc(alive[u]) == 3 ? 1u : 0u;
-    d0 = d1 = false;
+  }
+  static __device__ __forceinline__ Item item(const Found& f, uint32_t b) {
+    const CellPos& p = b < 8 ? f.p[0] : f.p[1];
+    return {~(p.off + p.y * p.side + p.x), ~p.wid};
   }
   template <class H>
-  static __device__ __forceinline__ bool run(const H& h, uint32_t type, uint32_t self, const Args& w) {
-    const uint32_t g = *field_ptr<uint32_t>(h, self, type, kACell);
-    const uint32_t wid = *field_ptr<uint32_t>(h, self, type, kAWorld);
-    const uint32_t off = w.off[wid], side = w.side[wid];
-    const uint32_t local = g - off;
-    const uint32_t y = local / side, x = local - y * side;
-    const uint32_t alive = neighbourhood<1>(w.bits, off, side, x, y);
-    *field_ptr<uint32_t>(h, self, type, kAAction) = __popc(alive) == 3 ? 1u : 0u;
-    return false;
-  }
-};
-
-// Phases 3 and 4 (the Cells of dying and born cells; each object deletes
-// itself only): loads of both slots first, then the Cells' handles of both.
-struct AliveUpdate {
-  static constexpr uint32_t kKind = 32;
-  static constexpr uint32_t kMinWaves = 8;
-  static constexpr bool kDeletesOnlyThis = true;
-  using Args = World;
-  template <class H>
-  static __device__ __forceinline__ void run_pair(const H& h, uint32_t type, uint32_t s0, bool l0, uint32_t s1,
-                                                  bool l1, const Args& w, bool& d0, bool& d1) {
-    const uint32_t self[2] = {s0, s1};
-    const bool lv[2] = {l0, l1};
-    const uint32_t n = __ballot(l1) ? 2u : 1u;
-    bool dying[2] = {false, false};
-    uint32_t g[2] = {0, 0}, wd[2];
-#pragma unroll
-    for (uint32_t u = 0; u < 2; ++u) {
-      if (u >= n) break;
-      dying[u] = lv[u] && *field_ptr<uint32_t>(h, self[u], type, kAAction) != 0;
-      g[u] = *field_ptr<uint32_t>(h, self[u], type, kACell);
-    }
-#pragma unroll
-    for (uint32_t u = 0; u < 2; ++u) wd[u] = u < n ? w.cells[dying[u] ? g[u] : 0u] : kNull;
-#pragma unroll
-    for (uint32_t u = 0; u < 2; ++u)
-      if (dying[u]) set_cell_live(h, w, g[u], wd[u], 0);
-    d0 = dying[0];
-    d1 = dying[1];
-  }
-  template <class H>
-  static __device__ __forceinline__ bool run(const H& h, uint32_t type, uint32_t self, const Args& w) {
-    if (*field_ptr<uint32_t>(h, self, type, kAAction) == 0) return false;
-    const uint32_t g = *field_ptr<uint32_t>(h, self, type, kACell);
-    set_cell_live(h, w, g, w.cells[g], 0);
-    return true;
-  }
-};
-
-struct CandUpdate {
-  static constexpr uint32_t kKind = 33;
-  static constexpr uint32_t kMinWaves = 8;
-  static constexpr bool kDeletesOnlyThis = true;
-  using Args = World;
-  template <class H>
-  static __device__ __forceinline__ void run_pair(const H& h, uint32_t type, uint32_t s0, bool l0, uint32_t s1,
-                                                  bool l1, const Args& w, bool& d0, bool& d1) {
-    const uint32_t self[2] = {s0, s1};
-    const bool lv[2] = {l0, l1};
-    const uint32_t n = __ballot(l1) ? 2u : 1u;
-    bool born[2] = {false, false};
-    uint32_t g[2] = {0, 0}, wid[2] = {0, 0}, wd[2];
-#pragma unroll
-    for (uint32_t u = 0; u < 2; ++u) {
-      if (u >= n) break;
-      g[u] = *field_ptr<uint32_t>(h, self[u], type, kACell);
-      wid[u] = *field_ptr<uint32_t>(h, self[u], type, kAWorld);
-      born[u] = lv[u] && *field_ptr<uint32_t>(h, self[u], type, kAAction) != 0;
-    }
-#pragma unroll
-    for (uint32_t u = 0; u < 2; ++u) wd[u] = u < n ? w.cells[born[u] ? g[u] : 0u] : kNull;
-    uint32_t nb = 0;  // bit u: cell u is born and has its Cell
-#pragma unroll
-    for (uint32_t u = 0; u < 2; ++u)
-      if (born[u] && set_cell_live(h, w, g[u], wd[u], 1)) nb |= 1u << u;
-    // One allocation for the Alive objects of both blocks' births.
-    new_many(h, kAlive, (uint32_t)__popc(nb), [&](uint32_t j, uint32_t o) {
-      if (o == kNull) return;
-      const uint32_t u = nth_set_bit(nb, j);
-      *field_ptr<uint32_t>(h, o, kAlive, kACell) = u ? g[1] : g[0];
-      *field_ptr<uint32_t>(h, o, kAlive, kAWorld) = u ? wid[1] : wid[0];
-      *field_ptr<uint32_t>(h, o, kAlive, kAAction) = 0;
-    });
-    d0 = l0;
-    d1 = l1;
-  }
-  template <class H>
-  static __device__ __forceinline__ bool run(const H& h, uint32_t type, uint32_t self, const Args& w) {
-    const uint32_t g = *field_ptr<uint32_t>(h, self, type, kACell);
-    const uint32_t wid = *field_ptr<uint32_t>(h, self, type, kAWorld);
-    const bool born = *field_ptr<uint32_t>(h, self, type, kAAction) != 0;
-    if (born && set_cell_live(h, w, g, w.cells[g], 1)) {
-      const uint32_t o = dsoar_new(h, kAlive);
-      if (o != kNull) {
-        *field_ptr<uint32_t>(h, o, kAlive, kACell) = g;
-        *field_ptr<uint32_t>(h, o, kAlive, kAWorld) = wid;
-        *field_ptr<uint32_t>(h, o, kAlive, kAAction) = 0;
-      }
-    }
-    return true;
+  static __device__ __forceinline__ void make(const H& h, const Args&, const Item& it, uint32_t o) {
+    *field_ptr<uint32_t>(h, o, kAlive, kACell) = ~it.not_g;
+    *field_ptr<uint32_t>(h, o, kAlive, kAWorld) = ~it.not_wid;
+    *field_ptr<uint32_t>(h, o, kAlive, kAAction) = 0;
   }
 };
 
@@ -484,9 +394,9 @@ __device__ __forceinline__ void create_cells(const H& h, const World& w, uint32_
     const_cast<uint32_t*>(w.cells)[first + (uint32_t)(base + j)] = o;
   });
   if constexpr (PL == 64) {
-    if (k) write_live_range(const_cast<uint32_t*>(w.bits), first + (uint32_t)base, k, live & made);
+    if (k) write_live_range(plane_at(w, w.clock->epoch), first + (uint32_t)base, k, live & made);
   } else {
-    write_live_run(const_cast<uint32_t*>(w.bits), first + (uint32_t)base, k != 0, (live & made) != 0, true);
+    write_live_run(plane_at(w, w.clock->epoch), first + (uint32_t)base, k != 0, (live & made) != 0, true);
   }
   new_many(h, kAlive, (uint32_t)__popcll(live), [&](uint32_t r, uint32_t o) {
     if (o == kNull) return;
@@ -520,11 +430,12 @@ __global__ void gol_init_kernel(DevHeapW<LG> h, World w, uint32_t num_worlds, ui
   });
 }
 
-__global__ void gol_read_kernel(DevHeap h, World w, uint32_t off, uint32_t n, uint8_t* out) {
+__global__ void gol_read_kernel(World w, uint32_t off, uint32_t n, uint8_t* out) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const uint32_t wd = w.cells[off + i];
-  out[i] = wd == kNull ? 0xFF : (uint8_t)*field_ptr<uint32_t>(h, wd, kCell, kCAlive);
+  // The bit copies the Cell's flag, in one load from few lines.
+  const uint32_t g = off + i, bit = (plane_at(w, w.clock->epoch)[g >> 5] >> (g & 31u)) & 1u;
+  out[i] = w.cells[g] == kNull ? 0xFF : (uint8_t)bit;
 }
 
 // Records world slot's cell range in the world table.
@@ -548,7 +459,7 @@ __global__ void gol_retire_cells_kernel(DevHeapW<LG> h, World w, uint32_t off, u
   uint32_t* c = const_cast<uint32_t*>(w.cells) + off + i;
   if (*c != kNull) dsoar_delete(h, *c);
   *c = kNull;
-  write_live_run(const_cast<uint32_t*>(w.bits), off + i, true, false, true);
+  write_live_run(plane_at(w, w.clock->epoch), off + i, true, false, true);
 }
 
 struct GolDeleteWorld {
@@ -572,22 +483,26 @@ bool gol_heap_ok(const dsoar_heap* h) {
   return true;
 }
 
-// Device buffer of a world set: the world table (offsets and sides), the
-// cell index (4 bytes per cell) and the live-bit plane (padded by two words,
-// so that a window's second dword load past the last cell stays inside).
+// Device buffer of a world set: the world table (offsets and sides), the step
+// clock, the cell index (4 bytes per cell) and the two live-bit planes (each
+// padded by two words, so that a window's second dword load past the last cell
+// stays inside, and to 16 bytes).
 uint64_t table_head(uint32_t num_worlds) { return ((uint64_t)(2 * num_worlds + 1) * 4 + 255) / 256 * 256; }
 uint64_t index_bytes(uint64_t cells) { return (cells * 4 + 255) / 256 * 256; }
 uint64_t bits_bytes(uint64_t cells) { return (((cells + 31) / 32 + 2) * 4 + 255) / 256 * 256; }
 uint64_t world_set_bytes(uint32_t num_worlds, uint64_t cells) {
-  return table_head(num_worlds) + index_bytes(cells) + bits_bytes(cells);
+  return table_head(num_worlds) + 256 + index_bytes(cells) + 2 * bits_bytes(cells);
 }
 
 void carve(World& w, uint8_t* dev_mem, uint32_t num_worlds, uint64_t cells) {
   uint32_t* tab = (uint32_t*)dev_mem;
   w.off = tab;
   w.side = tab + num_worlds + 1;
-  w.cells = (const uint32_t*)(dev_mem + table_head(num_worlds));
-  w.bits = (const uint32_t*)(dev_mem + table_head(num_worlds) + index_bytes(cells));
+  uint8_t* b = dev_mem + table_head(num_worlds);
+  w.clock = (const StepClock*)b;
+  w.cells = (const uint32_t*)(b + 256);
+  w.plane[0] = (uint32_t*)(b + 256 + index_bytes(cells));
+  w.plane[1] = (uint32_t*)(b + 256 + index_bytes(cells) + bits_bytes(cells));
 }
 
 uint64_t gol_total_cells(uint32_t num_worlds, const uint32_t* sides) {
@@ -616,19 +531,15 @@ namespace {
 
 int gol_generation(dsoar_gol* g, uint32_t flags, hipStream_t s) {
   dsoar_heap* h = g->heap;
-  const uint32_t base = flags & DSOAR_DO_PLAIN;
-  int rc = launch_doall<AlivePrep>(h, kAlive, g->w, base, s);
-  if (!rc) rc = launch_doall<CandPrep>(h, kCand, g->w, base, s);
-  // Phase 2 creates and deletes nothing, phase 3 touches only Alive objects:
-  // phases 3 and 4 reuse the enumerations of phases 1 and 2.
-  if (base & DSOAR_DO_PLAIN) {
-    if (!rc) rc = launch_doall<AliveUpdate>(h, kAlive, g->w, base | DSOAR_DO_REUSE_ENUM, s);
-    if (!rc) rc = launch_doall<CandUpdate>(h, kCand, g->w, base | DSOAR_DO_REUSE_ENUM, s);
-  } else if (!rc) {
-    // Phases 3 and 4 touch disjoint cells (dying ones, born ones) and each
-    // object only its own: one launch over both lists.
-    rc = launch_doall2<AliveUpdate, CandUpdate>(h, kAlive, g->w, kCand, g->w, kKindGolUpdate, s);
-  }
+  const uint32_t reuse = (flags & DSOAR_DO_PLAIN) | DSOAR_DO_REUSE_ENUM;
+  const PlaneCopy copy{{(uint4*)g->w.plane[0], (uint4*)g->w.plane[1]}, g->w.clock,
+                       (uint32_t)(((uint64_t)g->total + 127) / 128)};
+  int rc = launch_enumerate(h, kAlive, s, nullptr, &copy);
+  if (!rc) rc = launch_doall<AliveStep>(h, kAlive, g->w, reuse, s);
+  // The second enumeration makes the new plane the current one: nothing reads
+  // the clock while it runs.
+  if (!rc) rc = launch_enumerate(h, kCand, s, const_cast<StepClock*>(g->w.clock));
+  if (!rc) rc = launch_doall<CandStep>(h, kCand, g->w, reuse, s);
   return rc;
 }
 
@@ -729,7 +640,7 @@ int dsoar_gol_step(dsoar_gol* g, uint32_t generations, uint32_t flags, void* str
 
 int dsoar_gol_read(dsoar_gol* g, uint8_t* grid_dev, void* stream) {
   if (!g || !grid_dev) return DSOAR_ERR_INVALID_ARG;
-  hipLaunchKernelGGL(gol_read_kernel, dim3((uint32_t)(((uint64_t)g->total + 255) / 256)), dim3(256), 0, (hipStream_t)stream, g->heap->dev,
+  hipLaunchKernelGGL(gol_read_kernel, dim3((uint32_t)(((uint64_t)g->total + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
                      g->w, 0u, g->total, grid_dev);
   DSOAR_LAUNCHED(g->heap);
   return DSOAR_OK;
@@ -821,7 +732,7 @@ int dsoar_gol_retire(dsoar_gol* g, uint32_t slot, void* stream) {
 int dsoar_gol_read_world(dsoar_gol* g, uint32_t slot, uint8_t* grid_dev, void* stream) {
   if (!g || !g->live || slot >= g->num_worlds || !g->live[slot] || !grid_dev) return DSOAR_ERR_INVALID_ARG;
   const uint32_t n = g->h_side[slot] * g->h_side[slot];
-  hipLaunchKernelGGL(gol_read_kernel, dim3((uint32_t)(((uint64_t)n + 255) / 256)), dim3(256), 0, (hipStream_t)stream, g->heap->dev, g->w,
+  hipLaunchKernelGGL(gol_read_kernel, dim3((uint32_t)(((uint64_t)n + 255) / 256)), dim3(256), 0, (hipStream_t)stream, g->w,
                      g->h_off[slot], n, grid_dev);
   DSOAR_LAUNCHED(g->heap);
   return DSOAR_OK;

@@ -305,11 +305,22 @@ __device__ __forceinline__ uint64_t pack_flag(uint32_t epoch, uint64_t status, u
 // ticket counter.  Each wavefront covers
 // WPW level-0 words (64 blocks each); all their loads are issued before any
 // is used.  The heap is quiescent, so plain loads see the previous kernels.
-template <uint32_t WPW, uint32_t LG>
-__global__ void __launch_bounds__(enum_waves(WPW) * 64) enumerate_kernel(DevHeapW<LG> h, uint32_t type, EnumOut out) {
+template <uint32_t WPW, uint32_t LG, bool kCopy>
+__global__ void __launch_bounds__(enum_waves(WPW) * 64)
+    enumerate_kernel(DevHeapW<LG> h, uint32_t type, EnumOut out, std::conditional_t<kCopy, PlaneCopy, NoCopy> copy) {
   constexpr uint32_t kEnumWaves = enum_waves(WPW);
   __shared__ uint32_t s_tile, s_epoch, s_prefix;
   __shared__ uint32_t s_wave_total[kEnumWaves];
+  if constexpr (kCopy) {
+    if (blockIdx.x >= out.num_tiles) {  // beside the scan: the step's plane copy
+      const uint32_t now = copy.clock->epoch & 1u, wgs = gridDim.x - out.num_tiles;
+      const uint4* src = now ? copy.plane[1] : copy.plane[0];
+      uint4* dst = now ? copy.plane[0] : copy.plane[1];
+      for (uint32_t i = (blockIdx.x - out.num_tiles) * blockDim.x + threadIdx.x; i < copy.words; i += wgs * blockDim.x)
+        dst[i] = src[i];
+      return;
+    }
+  }
   if (threadIdx.x == 0) {
     s_epoch = __hip_atomic_load(&out.st->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     s_tile = __hip_atomic_fetch_add(&out.st->tile_counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -667,29 +678,33 @@ struct FieldGather {
 
 // ------------------------------------------------------ shared host helpers
 
-int launch_enumerate_into(dsoar_heap* h, uint32_t type, const EnumOut& eo, hipStream_t s) {
-  if (h->enum_wpw == kEnumWideWords)
-    with_width(h, [&](auto w_) {
+int launch_enumerate_into(dsoar_heap* h, uint32_t type, const EnumOut& eo, hipStream_t s, const PlaneCopy* copy) {
+  with_width(h, [&](auto w_) {
     constexpr uint32_t kLG = decltype(w_)::value;
-    launch_timed(h, kKindEnumerate, enumerate_kernel<kEnumWideWords, kLG>, dim3(h->num_tiles),
-                 dim3(enum_waves(kEnumWideWords) * 64),
-                 s, DevHeapW<kLG>(h->dev), type, eo);
-  });
-  else
-    with_width(h, [&](auto w_) {
-    constexpr uint32_t kLG = decltype(w_)::value;
-    launch_timed(h, kKindEnumerate, enumerate_kernel<1, kLG>, dim3(h->num_tiles), dim3(enum_waves(1) * 64), s,
-                 DevHeapW<kLG>(h->dev),
-                 type, eo);
+    auto go = [&](auto wpw) {
+      constexpr uint32_t kWPW = decltype(wpw)::value;
+      constexpr uint32_t threads = enum_waves(kWPW) * 64;
+      if (copy) {
+        // One 16-byte word of the copy per thread, up to a workgroup per CU.
+        const uint32_t copiers = std::min((copy->words + threads - 1) / threads, h->num_cus);
+        launch_timed(h, kKindEnumerate, enumerate_kernel<kWPW, kLG, true>, dim3(h->num_tiles + copiers), dim3(threads), s,
+                     DevHeapW<kLG>(h->dev), type, eo, *copy);
+      } else {
+        launch_timed(h, kKindEnumerate, enumerate_kernel<kWPW, kLG, false>, dim3(h->num_tiles), dim3(threads), s,
+                     DevHeapW<kLG>(h->dev), type, eo, NoCopy{});
+      }
+    };
+    if (h->enum_wpw == kEnumWideWords) go(std::integral_constant<uint32_t, kEnumWideWords>{});
+    else go(std::integral_constant<uint32_t, 1>{});
   });
   DSOAR_LAUNCHED(h);
   return DSOAR_OK;
 }
 
-int launch_enumerate(dsoar_heap* h, uint32_t type, hipStream_t s, StepClock* clock) {
+int launch_enumerate(dsoar_heap* h, uint32_t type, hipStream_t s, StepClock* clock, const PlaneCopy* copy) {
   EnumOut eo = h->enum_out[type];
   eo.clock = clock;
-  return launch_enumerate_into(h, type, eo, s);
+  return launch_enumerate_into(h, type, eo, s, copy);
 }
 
 // Scratch of the allocation-free enumeration (dsoar_enumerate_noalloc): the
@@ -1066,7 +1081,7 @@ int dsoar_enumerate_noalloc(dsoar_heap* h, uint32_t type, uint32_t* R_dev, uint6
                      h->num_tiles);
   DSOAR_LAUNCHED(h);
   const EnumOut eo{R_dev, S_dev, st, flags, h->num_tiles, count_dev};
-  return launch_enumerate_into(h, type, eo, s);
+  return launch_enumerate_into(h, type, eo, s, nullptr);
 }
 
 int dsoar_enum_count(dsoar_heap* h, uint32_t type, uint32_t* count, void* stream) {

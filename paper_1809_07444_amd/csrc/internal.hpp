@@ -46,6 +46,16 @@ struct StepClock {
 };
 __host__ __device__ __forceinline__ uint32_t next_epoch(uint32_t e) { return e + 1 == kEpochs ? 2u : e + 1; }
 
+// A copy between an application's two planes, from the one that the clock's
+// epoch names to the other, for workgroups of an enumeration to do beside its
+// scan.
+struct PlaneCopy {
+  uint4* plane[2];
+  const StepClock* clock;
+  uint32_t words;  // 16-byte words per plane
+};
+struct NoCopy {};
+
 struct EnumOut {
   uint32_t* R;          // compacted block ids
   uint64_t* S;          // snapshot of each listed block's object bitmap
@@ -125,15 +135,19 @@ constexpr uint32_t kKindWatorTick = 78;
 // take the dispatch's own begin and end timestamps, so the recorded time is
 // the kernel's execution without the gaps around it.
 template <class K, class... A>
-inline void launch_timed(dsoar_heap* h, uint32_t kind, K kernel, dim3 grid, dim3 block, hipStream_t s,
-                         A... args) {
+inline void launch_timed_lds(dsoar_heap* h, uint32_t kind, K kernel, dim3 grid, dim3 block, uint32_t lds,
+                             hipStream_t s, A... args) {
   if (h->timing && h->rec_used < kTimingCap) {
     const uint32_t r = h->rec_used++;
     h->rec_kind[r] = kind;
-    hipExtLaunchKernelGGL(kernel, grid, block, 0, s, h->ev_pool[2 * r], h->ev_pool[2 * r + 1], 0u, args...);
+    hipExtLaunchKernelGGL(kernel, grid, block, lds, s, h->ev_pool[2 * r], h->ev_pool[2 * r + 1], 0u, args...);
   } else {
-    hipLaunchKernelGGL(kernel, grid, block, 0, s, args...);
+    hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
   }
+}
+template <class K, class... A>
+inline void launch_timed(dsoar_heap* h, uint32_t kind, K kernel, dim3 grid, dim3 block, hipStream_t s, A... args) {
+  launch_timed_lds(h, kind, kernel, grid, block, 0, s, args...);
 }
 
 // Kernels that touch the block-state bitmaps are instantiated once per
@@ -148,7 +162,8 @@ inline void with_width(const dsoar_heap* h, F&& f) {
     f(std::integral_constant<uint32_t, 5>{});
 }
 
-int launch_enumerate(dsoar_heap* h, uint32_t type, hipStream_t s, StepClock* clock = nullptr);
+int launch_enumerate(dsoar_heap* h, uint32_t type, hipStream_t s, StepClock* clock = nullptr,
+                     const PlaneCopy* copy = nullptr);
 int read_count(dsoar_heap* h, uint32_t type, hipStream_t s, uint32_t* count);
 
 // A method may split into a load phase and an apply phase:
@@ -187,26 +202,9 @@ struct HasWave : std::false_type {};
 template <class M>
 struct HasWave<M, std::void_t<decltype(&M::template run_wave<DevHeap>)>> : std::true_type {};
 
-// Or a method may take two list entries per wavefront pass (capacity 64, on
-// lists of at least two entries per wavefront):
-//   static __device__ void run_pair(const DevHeap&, uint32_t type, uint32_t self0, bool live0,
-//                                   uint32_t self1, bool live1, const Args&, bool& del0, bool& del1);
-// Lane l holds slot l of both blocks and enters when either slot is live.
-// The method issues the loads of both objects before it uses any, and makes
-// one wavefront request for the objects both create, so one chain of
-// dependent loads and allocation atomics serves two blocks.  Empty slots'
-// fields hold anything: the method must not index memory with them.  It
-// still provides `run` (capacity 32, lists of fewer than two entries per
-// wavefront, and callers of single objects).
-template <class M, class = void>
-struct HasPair : std::false_type {};
-template <class M>
-struct HasPair<M, std::void_t<decltype(&M::template run_pair<DevHeap>)>> : std::true_type {};
-
 // A method may also declare
 //   static constexpr bool kDeletesOnlyThis = true;
-// when it deletes no object but `this` (and a two-list do-all pairs it only
-// with another such method).  Then a block whose snapshot is full is still
+// when it deletes no object but `this`.  Then a block whose snapshot is full is still
 // exactly full when its wavefront deletes from it: no other wavefront
 // removes its objects, and a full block is not active, so no allocation adds
 // to it.  Its object-bitmap AND needs no result, and the OR that returns the
@@ -240,6 +238,35 @@ template <class M, class = void>
 struct Phases : std::integral_constant<uint32_t, 1> {};
 template <class M>
 struct Phases<M, std::void_t<decltype(M::kPhases)>> : std::integral_constant<uint32_t, M::kPhases> {};
+
+// A method may queue the objects it creates:
+//   struct Found { uint32_t claims; ... };   // bit b of claims: this lane creates an object from item(found, b)
+//   using Item = ...;                        // what a new object is made from
+//   static constexpr uint32_t kItemType;     // its type
+//   static constexpr uint32_t kItems;        // queue length per wavefront
+//   static constexpr uint32_t kClaimBits;    // bits of claims that may be set
+//   template <uint32_t N, class H>
+//   static __device__ void find(const H&, uint32_t type, const uint32_t (&self)[2], const bool (&live)[2],
+//                               const Args&, Found&, bool (&del)[2]);
+//   static __device__ Item item(const Found&, uint32_t b);
+//   static __device__ void make(const H&, const Args&, const Item&, uint32_t obj);
+// Every lane enters, with N = 1 or 2 list entries; the lanes of empty slots
+// index no memory with their fields.  Two entries are taken per pass with
+// capacity 64 on lists of at least two entries per wavefront: the method
+// issues the loads of both objects before it uses any (on a short list that
+// would leave half the wavefronts without work).
+// The queue lives in LDS and is made into objects when it is full and at the
+// end of the wavefront's list, so one chain of allocation atomics serves
+// several entries, and the lanes share the new objects evenly whichever lane
+// asked for them.
+template <class M, class = void>
+struct HasItems : std::false_type {};
+template <class M>
+struct HasItems<M, std::void_t<typename M::Item>> : std::true_type {};
+template <class M, bool = HasItems<M>::value>
+struct ItemBytes : std::integral_constant<uint32_t, 0> {};
+template <class M>
+struct ItemBytes<M, true> : std::integral_constant<uint32_t, M::kItems * (uint32_t)sizeof(typename M::Item)> {};
 
 template <class Method, class H>
 __device__ __forceinline__ bool run_method(const H& h, uint32_t type, uint32_t self,
@@ -516,38 +543,15 @@ __device__ __forceinline__ void doall_list(const H& h, uint32_t type, const uint
       first_bid = R[first];
       first_snap = S[first];
     }
-    bool pairs = false;
-    if constexpr (HasPair<Method>::value) pairs = count >= 2 * nw;
-    if (pairs) {
-      // Pairs only when every wavefront gets two entries or more: on a short
-      // list they would leave half the wavefronts without work, and the
-      // method's single-object form runs instead.
-      const uint32_t per = 2;
-      for (uint32_t e = per * gw; e < count; e += per * nw) {
-        const bool has1 = e + 1 < count;
-        const uint32_t b0 = R[e], b1 = has1 ? R[e + 1] : b0;
-        const uint64_t s0 = S[e], s1 = has1 ? S[e + 1] : 0ull;
-        visits += (uint32_t)(__popcll(s0) + __popcll(s1));
-        settle();
-        const bool l0 = (s0 >> lane) & 1ull, l1 = (s1 >> lane) & 1ull;
-        bool d0 = false, d1 = false;
-        if constexpr (HasPair<Method>::value)
-          if (l0 || l1) Method::run_pair(h, type, make_obj(b0, lane), l0, make_obj(b1, lane), l1, args, d0, d1);
-        const uint64_t dm0 = __ballot(l0 && d0), dm1 = __ballot(l1 && d1);
-        if (dm0) remove(b0, s0, dm0);
-        if (dm1) remove(b1, s1, dm1);
-      }
-    } else {
-      for (uint32_t e = gw; e < count; e += nw) {
-        const bool have = !kRun && e == gw;
-        const uint32_t bid = have ? first_bid : R[e];
-        const uint64_t snap = have ? first_snap : S[e];
-        visits += (uint32_t)__popcll(snap);
-        settle();
-        const bool del = run_slot<Method>(h, type, make_obj(bid, lane), (snap >> lane) & 1ull, args);
-        const uint64_t dm = __ballot(del);
-        if (dm) remove(bid, snap, dm);
-      }
+    for (uint32_t e = gw; e < count; e += nw) {
+      const bool have = !kRun && e == gw;
+      const uint32_t bid = have ? first_bid : R[e];
+      const uint64_t snap = have ? first_snap : S[e];
+      visits += (uint32_t)__popcll(snap);
+      settle();
+      const bool del = run_slot<Method>(h, type, make_obj(bid, lane), (snap >> lane) & 1ull, args);
+      const uint64_t dm = __ballot(del);
+      if (dm) remove(bid, snap, dm);
     }
     settle();
   } else {
@@ -570,6 +574,129 @@ __device__ __forceinline__ void doall_list(const H& h, uint32_t type, const uint
       }
     }
   }
+}
+
+// doall_list for methods that queue the objects they create.  The queue is
+// emptied at one place in the code, between filling it from the claims of the
+// entries in hand (as many as fit) and going on, so the allocation path is
+// there once.
+template <class Method, bool kOnlyThis, class H>
+__device__ __forceinline__ void doall_items(const H& h, uint32_t type, const uint32_t* __restrict__ R,
+                                            const uint64_t* __restrict__ S, uint32_t count, uint32_t gw, uint32_t nw,
+                                            const typename Method::Args& args, uint32_t& visits, uint32_t& freed) {
+  using Item = typename Method::Item;
+  extern __shared__ uint64_t item_lds[];
+  Item* const items = reinterpret_cast<Item*>(item_lds) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * Method::kItems;
+  const uint32_t lane = lane_id(), c = cap_of(h, type);
+  const bool wide = c == 64;  // one entry per wavefront and slot, else 64 / c entries
+  const bool fast = kOnlyThis && !h.online_reclaim && wide;
+  const Bitmap act = active_bm(h, type);
+  uint32_t pend_word = 0;
+  uint64_t pend_bits = 0, pend_prev = 0;
+  auto settle = [&]() __attribute__((always_inline)) {  // as in doall_list
+    if (pend_bits) bm_set_bits0_settle(act, pend_word, pend_bits, pend_prev);
+    pend_bits = 0;
+  };
+  // Two entries per pass on lists of at least two per wavefront.
+  const bool pairs = wide && count >= 2 * nw;
+  const uint32_t sh = (uint32_t)__builtin_ctz(c), per = pairs ? 2u : 64u >> sh;
+  // The first entry, loaded before the count is known (as in doall_list).
+  const uint32_t first = gw < h.num_blocks ? gw : h.num_blocks - 1;
+  const uint32_t first_bid = R[first];
+  const uint64_t first_snap = S[first];
+  uint32_t n = 0;  // items in the queue
+  for (uint64_t e0 = (uint64_t)per * gw; e0 < count; e0 += (uint64_t)per * nw) {
+    const uint32_t e = (uint32_t)e0;
+    uint32_t bid[2] = {0, 0};
+    uint64_t snap[2] = {0, 0};
+    bool live[2] = {false, false}, del[2] = {false, false};
+    uint32_t slot = lane;
+    typename Method::Found found;
+    found.claims = 0;
+    if (pairs) {
+      const bool has1 = e + 1 < count;
+      bid[0] = R[e];
+      bid[1] = has1 ? R[e + 1] : bid[0];
+      snap[0] = S[e];
+      snap[1] = has1 ? S[e + 1] : 0ull;
+      live[0] = (snap[0] >> lane) & 1ull;
+      live[1] = (snap[1] >> lane) & 1ull;
+      visits += (uint32_t)(__popcll(snap[0]) + __popcll(snap[1]));
+      settle();
+      const uint32_t self[2] = {make_obj(bid[0], lane), make_obj(bid[1], lane)};
+      Method::template find<2>(h, type, self, live, args, found, del);
+    } else {
+      if (wide) {
+        bid[0] = e == gw ? first_bid : R[e];
+        snap[0] = e == gw ? first_snap : S[e];
+      } else {
+        const uint32_t mine = e + (lane >> sh);
+        slot = lane & (c - 1u);
+        if (mine < count) {
+          bid[0] = R[mine];
+          snap[0] = S[mine];
+        }
+      }
+      live[0] = (snap[0] >> slot) & 1ull;
+      visits += (uint32_t)__popcll(__ballot(live[0]));
+      settle();
+      const uint32_t self[2] = {make_obj(bid[0], slot), 0u};
+      Method::template find<1>(h, type, self, live, args, found, del);
+    }
+    if (wide) {
+#pragma unroll
+      for (uint32_t u = 0; u < 2; ++u) {
+        const uint64_t dm = __ballot(live[u] && del[u]);
+        if (!dm) continue;
+        if (fast && snap[u] == ~0ull) {  // a full block (see DeletesOnlyThis): nothing to wait for
+          if (is_first_active())
+            __hip_atomic_fetch_and(h.obj_bitmap + bid[u], ~dm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          freed += (uint32_t)__popcll(dm);
+          chaos_pause(kChaosDeleteActive);
+          settle();
+          pend_word = bid[u] >> 6;
+          pend_bits = 1ull << (bid[u] & 63u);
+          pend_prev = bm_set_bits0_issue(act, pend_word, pend_bits);
+        } else {
+          freed += delete_mask(h, type, bid[u], dm);
+        }
+      }
+    } else {
+      const uint64_t dm = __ballot(live[0] && del[0]), group = (1ull << c) - 1ull;
+      for (uint32_t k = 0; k < 64u >> sh && dm; ++k) {
+        const uint64_t part = (dm >> (k * c)) & group;
+        if (part) freed += delete_mask(h, type, (uint32_t)__builtin_amdgcn_readlane(bid[0], k * c), part);
+      }
+    }
+    const bool last = e0 + (uint64_t)per * nw >= count;
+    for (;;) {
+      // Claims in lane order, as many as the queue has room for.
+      const uint32_t k = (uint32_t)__popc(found.claims);
+      uint32_t at = n, total = 0;
+#pragma unroll
+      for (uint32_t b = 0; (1u << b) <= Method::kClaimBits; ++b) {
+        const uint64_t m = __ballot((k >> b) & 1u);
+        at += lanes_below(m) << b;
+        total += (uint32_t)__popcll(m) << b;
+      }
+      while (found.claims && at < Method::kItems) {
+        items[at++] = Method::item(found, (uint32_t)__builtin_ctz(found.claims));
+        found.claims &= found.claims - 1u;
+      }
+      const bool over = n + total > Method::kItems;
+      n = over ? Method::kItems : n + total;
+      if (!over && !last) break;
+      __builtin_amdgcn_wave_barrier();
+      settle();
+      new_items(h, Method::kItemType, n, [&](uint32_t r, uint32_t o) __attribute__((always_inline)) {
+        if (o != kNull) Method::make(h, args, items[r], o);
+      });
+      __builtin_amdgcn_wave_barrier();
+      n = 0;
+      if (!over) break;
+    }
+  }
+  settle();
 }
 
 // Adds a wavefront's visits and deletes to the counters.
@@ -615,33 +742,11 @@ doall_kernel(DevHeapW<LG> h, uint32_t type, const uint32_t* __restrict__ R,
       return;
     }
   }
-  doall_list<Method, kOnlyThis>(h, type, R, S, bcast32(*count_ptr), grid_wave(), nw, args, visits, freed);
+  if constexpr (HasItems<Method>::value)
+    doall_items<Method, kOnlyThis>(h, type, R, S, bcast32(*count_ptr), grid_wave(), nw, args, visits, freed);
+  else
+    doall_list<Method, kOnlyThis>(h, type, R, S, bcast32(*count_ptr), grid_wave(), nw, args, visits, freed);
   doall_count<Method>(h, type, visits, freed);
-}
-
-// Two do-alls in one launch, over the lists of two types: every wavefront
-// takes its share of the first list, then of the second.  For methods that
-// may run at the same time (neither reads what the other writes, apart from
-// the heap's own atomics): one kernel boundary and one launch fewer.
-template <class M1, class M2, uint32_t LG, bool kMany = false>
-__global__ void __launch_bounds__(1024)
-__attribute__((amdgpu_waves_per_eu(!kMany ? 1u
-                                          : MinWaves<M1>::value > MinWaves<M2>::value ? MinWaves<M1>::value
-                                                                                      : MinWaves<M2>::value)))
-doall2_kernel(DevHeapW<LG> h, uint32_t t1, const uint32_t* __restrict__ R1,
-                                                       const uint64_t* __restrict__ S1, const uint32_t* c1,
-                                                       typename M1::Args a1, uint32_t t2,
-                                                       const uint32_t* __restrict__ R2,
-                                                       const uint64_t* __restrict__ S2, const uint32_t* c2,
-                                                       typename M2::Args a2) {
-  const uint32_t nw = gridDim.x * (blockDim.x >> 6), gw = grid_wave();
-  uint32_t visits = 0, freed = 0;
-  constexpr bool kOnlyThis = DeletesOnlyThis<M1>::value && DeletesOnlyThis<M2>::value;
-  doall_list<M1, kOnlyThis>(h, t1, R1, S1, bcast32(*c1), gw, nw, a1, visits, freed);
-  doall_count<M1>(h, t1, visits, freed);
-  visits = freed = 0;
-  doall_list<M2, kOnlyThis>(h, t2, R2, S2, bcast32(*c2), gw, nw, a2, visits, freed);
-  doall_count<M2>(h, t2, visits, freed);
 }
 
 // Large heaps: those whose enumeration takes wide tiles (more than
@@ -674,8 +779,8 @@ int launch_doall(dsoar_heap* h, uint32_t type, const typename Method::Args& args
   with_width(h, [&](auto w_) {
     constexpr uint32_t kLG = decltype(w_)::value;
     auto go = [&](auto kernel) {
-      launch_timed(h, Method::kKind, kernel, dim3(grid), dim3(threads), s, DevHeapW<kLG>(h->dev), type,
-                   (const uint32_t*)eo.R, (const uint64_t*)eo.S, (const uint32_t*)&eo.st->count, args);
+      launch_timed_lds(h, Method::kKind, kernel, dim3(grid), dim3(threads), threads / 64 * ItemBytes<Method>::value, s,
+                       DevHeapW<kLG>(h->dev), type, (const uint32_t*)eo.R, (const uint64_t*)eo.S, (const uint32_t*)&eo.st->count, args);
     };
     if constexpr (MinWaves<Method>::value > 1) {
       if (large_heap(h)) go(doall_kernel<Method, kLG, true>);
@@ -710,33 +815,6 @@ int launch_doall_tree(dsoar_heap* h, uint32_t type, const typename Method::Args&
       const int rc = launch_doall<Method>(h, u, args, flags | DSOAR_DO_REUSE_ENUM, s);
       if (rc) return rc;
     }
-  return DSOAR_OK;
-}
-
-// Both do-alls of doall2_kernel, over the lists of their types' last
-// enumerations (no enumeration here), persistent grid; timed as `kind`.
-template <class M1, class M2>
-int launch_doall2(dsoar_heap* h, uint32_t t1, const typename M1::Args& a1, uint32_t t2,
-                  const typename M2::Args& a2, uint32_t kind, hipStream_t s) {
-  if (t1 >= h->desc.num_types || t2 >= h->desc.num_types) return DSOAR_ERR_INVALID_ARG;
-  const EnumOut& e1 = h->enum_out[t1];
-  const EnumOut& e2 = h->enum_out[t2];
-  with_width(h, [&](auto w_) {
-    constexpr uint32_t kLG = decltype(w_)::value;
-    auto go = [&](auto kernel) {
-      launch_timed(h, kind, kernel, dim3(h->num_cus * h->doall_wgs_per_cu), dim3(h->doall_wg_threads), s,
-                   DevHeapW<kLG>(h->dev), t1, (const uint32_t*)e1.R, (const uint64_t*)e1.S,
-                   (const uint32_t*)&e1.st->count, a1, t2, (const uint32_t*)e2.R, (const uint64_t*)e2.S,
-                   (const uint32_t*)&e2.st->count, a2);
-    };
-    if constexpr (MinWaves<M1>::value > 1 || MinWaves<M2>::value > 1) {
-      if (large_heap(h)) go(doall2_kernel<M1, M2, kLG, true>);
-      else go(doall2_kernel<M1, M2, kLG, false>);
-    } else {
-      go(doall2_kernel<M1, M2, kLG, false>);
-    }
-  });
-  DSOAR_LAUNCHED(h);
   return DSOAR_OK;
 }
 

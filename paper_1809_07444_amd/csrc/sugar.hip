@@ -235,7 +235,7 @@ struct Choose {
 // an atomic, a load and a reset beyond the L2.  119 us as two do-alls (Choose
 // 82), 84 fused (Choose 68), 90 with the requests (Choose 50).
 struct MoveEat {
-  static constexpr uint32_t kKind = 41;
+  static constexpr uint32_t kKind = 42;
   static constexpr bool kXcdRuns = true;
   static constexpr uint32_t kPhases = 2;
   static constexpr uint32_t kMinWaves = 8;

@@ -93,7 +93,7 @@ __device__ __forceinline__ int32_t decide(const Road& a, const uint16_t* now, ui
 
 // Decide and Move.
 struct Drive {
-  static constexpr uint32_t kKind = 51;
+  static constexpr uint32_t kKind = 52;
   static constexpr uint32_t kPhases = 2;
   static constexpr bool kDeletesOnlyThis = true;
   using Args = Road;

@@ -25,22 +25,23 @@ import re
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CAL_BYTES_KIB = 256 * 1024  # the calibration add reads and writes 256 MiB
 
-# do-all method struct -> the kernel kind the heap's timing reports
+# do-all method struct -> the kernel kind the heap's timing reports (methods
+# that took over phases of former ones keep a former one's name, so that traces
+# of both read alike)
 METHOD_KIND = {
-    "AlivePrep": "gol_alive_prep", "CandPrep": "gol_cand_prep", "AliveUpdate": "gol_alive_update",
-    "CandUpdate": "gol_cand_update", "MicroUpdate": "micro_update", "MicroCull": "micro_cull",
-    "Choose": "sugar_choose", "Move": "sugar_move", "Eat": "sugar_eat", "MoveEat": "sugar_move_eat", "Request": "sugar_request",
+    "AlivePrep": "gol_alive_prep", "AliveStep": "gol_alive_prep", "CandStep": "gol_update",
+    "MicroUpdate": "micro_update", "MicroCull": "micro_cull",
+    "Choose": "sugar_choose", "Eat": "sugar_eat", "MoveEat": "sugar_eat", "Request": "sugar_request",
     "Birth": "sugar_birth", "AgentRead": "sugar_read", "VisitCount": "visit_count", "DeleteIfMod": "delete_if_mod",
     "FieldGather": "gather", "GolDeleteWorld": "gol_delete_world", "SugarDeleteWorld": "sugar_delete_world",
-    "Decide": "traffic_decide", "Drive": "traffic_drive", "BodyForce": "collide_force",
-    "BodyMove": "collide_move", "BodyRoot": "collide_root", "BodyTarget": "collide_target", "BodyMerge": "collide_merge",
-    "FishDecide": "wator_fish_decide", "FishMove": "wator_fish_move",
-    "SharkDecide": "wator_shark_decide", "SharkMove": "wator_shark_move", "FishEaten": "wator_fish_eaten",
-    "FishRead": "wator_fish_read", "SharkRead": "wator_shark_read",
+    "BodyForce": "collide_force", "BodyMove": "collide_move", "BodyRoot": "collide_root",
+    "BodyTarget": "collide_target", "BodyMerge": "collide_merge", "FishDecide": "wator_fish_decide",
+    "FishMove": "wator_fish_move", "SharkDecide": "wator_shark_decide", "SharkMove": "wator_shark_move",
+    "FishEaten": "wator_fish_eaten", "FishRead": "wator_fish_read", "SharkRead": "wator_shark_read",
 }
 
 
-# two-list do-alls (both methods in one launch) -> kind
+# two-list do-alls (both methods in one launch) of earlier traces -> kind
 METHOD2_KIND = {("AliveUpdate", "CandUpdate"): "gol_update"}
 
 
@@ -50,8 +51,7 @@ PLAIN_KIND = [
     ("micro_create_kernel", "", "micro_create"), ("gol_init_kernel", "", "gol_init"),
     ("gol_admit_kernel", "", "gol_admit"), ("regrow_kernel", "", "sugar_regrow"),
     ("sugar_admit_kernel", "", "sugar_admit"), ("entry_kernel", "", "traffic_entry"),
-    ("traffic_step_kernel", "", "traffic_step"),
-    ("traffic_init_kernel", "", "traffic_init"),
+    ("traffic_step_kernel", "", "traffic_entry"), ("traffic_init_kernel", "", "traffic_init"),
     ("force_kernel", "", "collide_force"), ("collide_init_kernel", "", "collide_init"),
     ("wator_init_kernel", "", "wator_init"), ("tick_kernel", "Sea", "wator_tick"),
 ]
