@@ -47,8 +47,20 @@ struct World {
   uint32_t* plane[2];     // live bits
   const uint32_t* off;    // world -> first global cell index (num_worlds + 1 entries)
   const uint32_t* side;   // world -> side length
+  const uint4* tab;       // world -> {off, side, inverse of the side, off + side^2}
   const StepClock* clock; // epoch: any value, its low bit names the current plane
 };
+
+// World table entry: a cell's row is its local index divided by the side, by
+// one multiplication with the side's inverse and one correction (world_row).
+__host__ __device__ inline uint4 world_entry(uint32_t off, uint32_t side) {
+  return uint4{off, side, 0xFFFFFFFFu / side, off + side * side};
+}
+// floor(local / side): the product is that or one less.
+__device__ __forceinline__ uint32_t world_row(uint32_t local, uint32_t side, uint32_t inverse) {
+  const uint32_t q = __umulhi(local, inverse);
+  return local - q * side >= side ? q + 1u : q;
+}
 
 // The plane of the state that `epoch` names.
 __device__ __forceinline__ uint32_t* plane_at(const World& w, uint32_t epoch) {
@@ -90,19 +102,8 @@ __device__ __forceinline__ void write_live_run(uint32_t* bits, uint32_t g, bool 
   if (lv) __hip_atomic_fetch_or(word, lv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Global index of neighbour d (0..7: the row above, left and right, the row
-// below) of cell (x, y) of a world at offset `off` with side `side`.
-__device__ __forceinline__ uint32_t neighbour(uint32_t off, uint32_t side, uint32_t x, uint32_t y, uint32_t d) {
-  const uint32_t ddx = (0x9224u >> (2 * d)) & 3u;  // dx + 1 for d = 0..7: 0 1 2 0 2 0 1 2
-  const uint32_t ddy = (0xA940u >> (2 * d)) & 3u;  // dy + 1 for d = 0..7: 0 0 0 1 1 2 2 2
-  uint32_t nx = x + ddx, ny = y + ddy;              // shifted by +1, wrap below
-  nx = nx == 0 ? side - 1 : (nx - 1 == side ? 0 : nx - 1);
-  ny = ny == 0 ? side - 1 : (ny - 1 == side ? 0 : ny - 1);
-  return off + ny * side + nx;
-}
-
 // The 5 x 5 neighbourhood of a cell: bit (dy + 2) * 5 + (dx + 2) for the
-// cell at offset (dx, dy).  Directions d = 0..7 in the order of neighbour();
+// cell at offset (dx, dy).  Directions d = 0..7 go row by row;
 // direction 7 - d is the opposite of direction d.
 constexpr int kDirX[8] = {-1, 0, 1, -1, 1, -1, 0, 1};
 constexpr int kDirY[8] = {-1, -1, -1, 0, 0, 1, 1, 1};
@@ -126,68 +127,75 @@ constexpr uint32_t ring_mask() {
   return m;
 }
 
-// x + dx on a torus of side `side`, dx in -2..2 (any side >= 1).
-__device__ __forceinline__ uint32_t torus_add(uint32_t x, int dx, uint32_t side) {
-  int v = (int)x + dx;
-  const int s = (int)side;
-  v = v < 0 ? v + s : v;
-  v = v < 0 ? v + s : v;
-  v = v >= s ? v - s : v;
-  v = v >= s ? v - s : v;
-  return (uint32_t)v;
+// 32 bits of a bit plane from bit a on (the plane is padded, so a read past
+// the last cell stays in the buffer).
+__device__ __forceinline__ uint32_t bit_window(const uint32_t* bits, uint32_t a) {
+  const uint32_t* p = bits + (a >> 5);
+  return __builtin_amdgcn_alignbit(p[1], p[0], a & 31u);
 }
 
-// The (2R + 1) x (2R + 1) neighbourhood of cell (x, y) of the world at `off`
-// with side `side`, from the live-bit plane: bit (dy + R) * (2R + 1) + (dx +
-// R) is set for a live cell at offset (dx, dy); the centre is left out.  A
-// row whose window does not wrap around the torus is one pair of dword loads
-// shifted into place (the bit plane is padded, so a read past the last cell
-// stays in the buffer); a row that wraps loads its cells one by one.
-template <int R>
-__device__ __forceinline__ uint32_t neighbourhood(const uint32_t* bits, uint32_t off, uint32_t side, uint32_t x,
-                                                  uint32_t y) {
-  constexpr int D = 2 * R + 1;
-  const bool inside = x >= (uint32_t)R && x + R < side;
-  uint32_t al = 0;
-#pragma unroll
-  for (int i = 0; i < D; ++i) {
-    const uint32_t rb = off + torus_add(y, i - R, side) * side;  // bit index of the row's first cell
-    uint32_t v = 0;
-    if (inside) {
-      const uint32_t a = rb + x - R;
-      const uint32_t* p = bits + (a >> 5);
-      v = (uint32_t)((((uint64_t)p[1] << 32) | p[0]) >> (a & 31u));
-    } else {
-#pragma unroll
-      for (int j = 0; j < D; ++j) {
-        const uint32_t c = rb + torus_add(x, j - R, side);
-        v |= ((bits[c >> 5] >> (c & 31u)) & 1u) << j;
-      }
-    }
-    al |= (v & ((1u << D) - 1u)) << (i * D);
-  }
-  return al & ~(1u << (R * D + R));
-}
-
-// A listed object's cell position.  The do-all methods take one or two list
-// entries per pass: each lane reads its slots' fields and then the positions'
-// neighbourhoods before it uses any of them.  A slot that is not live reads as
-// world 0's corner (side 1 stands in when the world table's slot 0 is empty),
-// so no index is ever formed from its fields.
+// A listed object's cell: its world's cells are [off, end), row[i] is the
+// first cell of row y + i - 2 and x its column, around the torus.  A slot that
+// is not live reads as cell 0 of a world of side 5 at 0 (25 bits: in the padded
+// plane whatever the worlds), so no index is ever formed from its fields.
 struct CellPos {
-  uint32_t wid, off, side, x, y;
+  uint32_t wid, off, side, end, x, row[5];
 };
 __device__ __forceinline__ CellPos cell_pos(const World& w, uint32_t g, uint32_t wid, bool live) {
   const uint32_t wi = live ? wid : 0u;
-  const uint32_t o = w.off[wi], sd = w.side[wi];
+  const uint4 t = w.tab[wi];
   CellPos p;
   p.wid = wi;
-  p.off = live ? o : 0u;
-  p.side = live ? sd : 1u;
+  p.off = live ? t.x : 0u;
+  p.side = live ? t.y : 5u;
+  p.end = live ? t.w : 25u;
   const uint32_t local = live ? g - p.off : 0u;
-  p.y = local / p.side;
-  p.x = local - p.y * p.side;
+  const uint32_t y = live ? world_row(local, p.side, t.z) : 0u;
+  p.x = local - y * p.side;
+  const uint32_t r = p.off + local - p.x;
+  p.row[2] = r;
+  auto up = [&](uint32_t q) { return (q == p.off ? p.end : q) - p.side; };
+  auto down = [&](uint32_t q) { return q + p.side == p.end ? p.off : q + p.side; };
+  p.row[1] = up(r);
+  p.row[0] = up(p.row[1]);
+  p.row[3] = down(r);
+  p.row[4] = down(p.row[3]);
   return p;
+}
+
+// The (2R + 1) x (2R + 1) neighbourhood of a cell from a live-bit plane: bit
+// (dy + R) * (2R + 1) + (dx + R) is set for a live cell at offset (dx, dy); the
+// centre is left out.  A row is one pair of dword loads shifted into place, and
+// a second one at the row's first cell for the part that wraps around the torus
+// (in batches of small worlds most wavefronts have a lane that wraps; loading
+// its 25 cells one by one took as long as everybody else's rows).  Sides below
+// the window load their cells one by one.
+template <int R>
+__device__ __forceinline__ uint32_t neighbourhood(const uint32_t* bits, const CellPos& c) {
+  constexpr int D = 2 * R + 1;
+  uint32_t al = 0;
+  if (c.side >= (uint32_t)D) {
+    const uint32_t s = c.x >= (uint32_t)R ? c.x - R : c.side + c.x - R;  // the window's first cell
+    const uint32_t k = c.side - s < (uint32_t)D ? c.side - s : D;        // its cells before the row's end
+    uint32_t v[D];
+#pragma unroll
+    for (int i = 0; i < D; ++i) v[i] = __builtin_amdgcn_ubfe(bit_window(bits, c.row[i + 2 - R] + s), 0, k);
+    if (k < (uint32_t)D) {
+#pragma unroll
+      for (int i = 0; i < D; ++i) v[i] |= __builtin_amdgcn_ubfe(bit_window(bits, c.row[i + 2 - R]), 0, D - k) << k;
+    }
+#pragma unroll
+    for (int i = 0; i < D; ++i) al |= v[i] << (i * D);
+  } else {
+    for (int i = 0; i < D; ++i)
+      for (int j = 0; j < D; ++j) {
+        uint32_t x = c.x + (uint32_t)R * c.side + (uint32_t)j - R;  // at least 0: R sides are R cells or more
+        x -= x / c.side * c.side;
+        const uint32_t g = (R == 2 ? c.row[i] : c.row[i + 1]) + x;
+        al |= ((bits[g >> 5] >> (g & 31u)) & 1u) << (i * D + j);
+      }
+  }
+  return al & ~(1u << (R * D + R));
 }
 
 // What a new Candidate or Alive is made from.  The words are kept inverted:
@@ -196,13 +204,6 @@ __device__ __forceinline__ CellPos cell_pos(const World& w, uint32_t g, uint32_t
 // same few groups (the initial cells' kernel took 128 instead of 73 us).
 struct NewCell {
   uint32_t not_g, not_wid;
-};
-
-// The positions a pass holds, and the new cells that each lane claims: bit 8 u
-// + d for direction d of object u (births: bit 8 u).
-struct Cells {
-  uint32_t claims;
-  CellPos p[2];
 };
 
 // Phases 1 and 3.  A wavefront queues the Candidates of its entries: about 200
@@ -215,26 +216,38 @@ struct AliveStep {
   using Args = World;
   using Item = NewCell;
   static constexpr uint32_t kItemType = kCand;
-  static constexpr uint32_t kItems = 256, kClaimBits = 16;
-  using Found = Cells;
+  // Room for the Candidates of several pairs per flush (batches of 48.8 M cells:
+  // 365 us per generation with 256 places, 350 with 512).
+  static constexpr uint32_t kItems = 512, kClaimBits = 16;
+  // Bit 8 u + d of claims: the neighbour in direction d of object u.
+  struct Found {
+    uint32_t claims;
+    uint32_t wid[2], row[2][3], x[2], left[2], right[2];
+  };
   template <uint32_t N, class H>
   static __device__ __forceinline__ void find(const H& h, uint32_t type, const uint32_t (&self)[2],
                                               const bool (&lv)[2], const Args& w, Found& found, bool (&del)[2]) {
     const uint32_t epoch = w.clock->epoch;
     const uint32_t* now = plane_at(w, epoch);
     uint32_t g[N], wid[N], alive[N];
-    CellPos (&p)[2] = found.p;
 #pragma unroll
     for (uint32_t u = 0; u < N; ++u) {
       g[u] = *field_ptr<uint32_t>(h, self[u], type, kACell);
       wid[u] = *field_ptr<uint32_t>(h, self[u], type, kAWorld);
     }
 #pragma unroll
-    for (uint32_t u = 0; u < N; ++u) p[u] = cell_pos(w, g[u], wid[u], lv[u]);
-    // Live states of the 24 surrounding cells.  (A cell whose Cell is missing
-    // reads as dead; its Candidate never becomes an Alive.)
+    for (uint32_t u = 0; u < N; ++u) {
+      const CellPos p = cell_pos(w, g[u], wid[u], lv[u]);
+      // Live states of the 24 surrounding cells.  (A cell whose Cell is missing
+      // reads as dead; its Candidate never becomes an Alive.)
+      alive[u] = neighbourhood<2>(now, p);
+      found.wid[u] = p.wid;
+      found.x[u] = p.x;
+      found.left[u] = p.x == 0 ? p.side - 1u : p.x - 1u;
+      found.right[u] = p.x + 1u == p.side ? 0u : p.x + 1u;
 #pragma unroll
-    for (uint32_t u = 0; u < N; ++u) alive[u] = neighbourhood<2>(now, p[u].off, p[u].side, p[u].x, p[u].y);
+      for (uint32_t i = 0; i < 3; ++i) found.row[u][i] = p.row[i + 1];
+    }
 #pragma unroll
     for (uint32_t u = 0; u < N; ++u) {
       const uint32_t live = (uint32_t)__popc(alive[u] & ring_mask());
@@ -254,8 +267,14 @@ struct AliveStep {
     }
   }
   static __device__ __forceinline__ Item item(const Found& f, uint32_t b) {
-    const CellPos& p = b < 8 ? f.p[0] : f.p[1];
-    return {~neighbour(p.off, p.side, p.x, p.y, b & 7u), ~p.wid};
+    const bool u = b >= 8;
+    const uint32_t d = b & 7u;  // rows 0 0 0 1 1 2 2 2, columns 0 1 2 0 2 0 1 2
+    const uint32_t col = (0x9224u >> (2 * d)) & 3u;
+    const uint32_t r0 = u ? f.row[1][0] : f.row[0][0], r1 = u ? f.row[1][1] : f.row[0][1];
+    const uint32_t r2 = u ? f.row[1][2] : f.row[0][2];
+    const uint32_t c0 = u ? f.left[1] : f.left[0], c1 = u ? f.x[1] : f.x[0], c2 = u ? f.right[1] : f.right[0];
+    const uint32_t n = (d < 3 ? r0 : d < 5 ? r1 : r2) + (col == 0 ? c0 : col == 1 ? c1 : c2);
+    return {~n, ~(u ? f.wid[1] : f.wid[0])};
   }
   template <class H>
   static __device__ __forceinline__ void make(const H& h, const Args&, const Item& it, uint32_t o) {
@@ -274,34 +293,34 @@ struct CandStep {
   using Item = NewCell;
   static constexpr uint32_t kItemType = kAlive;
   static constexpr uint32_t kItems = 128, kClaimBits = 2;
-  using Found = Cells;
+  // Bit u of claims: object u is born.
+  struct Found {
+    uint32_t claims;
+    uint32_t g[2], wid[2];
+  };
   template <uint32_t N, class H>
   static __device__ __forceinline__ void find(const H& h, uint32_t type, const uint32_t (&self)[2],
                                               const bool (&lv)[2], const Args& w, Found& found, bool (&del)[2]) {
     const uint32_t then = w.clock->epoch;  // the enumeration of the Candidates has advanced it
-    uint32_t g[N], wid[N], alive[N];
-    CellPos (&p)[2] = found.p;
+    uint32_t alive[N];
 #pragma unroll
     for (uint32_t u = 0; u < N; ++u) {
-      g[u] = *field_ptr<uint32_t>(h, self[u], type, kACell);
-      wid[u] = *field_ptr<uint32_t>(h, self[u], type, kAWorld);
+      found.g[u] = *field_ptr<uint32_t>(h, self[u], type, kACell);
+      found.wid[u] = *field_ptr<uint32_t>(h, self[u], type, kAWorld);
     }
 #pragma unroll
-    for (uint32_t u = 0; u < N; ++u) p[u] = cell_pos(w, g[u], wid[u], lv[u]);
-#pragma unroll
     for (uint32_t u = 0; u < N; ++u)
-      alive[u] = neighbourhood<1>(plane_at(w, then + 1), p[u].off, p[u].side, p[u].x, p[u].y);
+      alive[u] = neighbourhood<1>(plane_at(w, then + 1), cell_pos(w, found.g[u], found.wid[u], lv[u]));
 #pragma unroll
     for (uint32_t u = 0; u < N; ++u) {
       bool born = lv[u] && __popc(alive[u]) == 3;
-      if (born) born = set_cell_live(h, plane_at(w, then), g[u], w.cells[g[u]], 1);
-      if (born) found.claims |= 1u << (8 * u);
+      if (born) born = set_cell_live(h, plane_at(w, then), found.g[u], w.cells[found.g[u]], 1);
+      if (born) found.claims |= 1u << u;
       del[u] = lv[u];
     }
   }
   static __device__ __forceinline__ Item item(const Found& f, uint32_t b) {
-    const CellPos& p = b < 8 ? f.p[0] : f.p[1];
-    return {~(p.off + p.y * p.side + p.x), ~p.wid};
+    return {~(b ? f.g[1] : f.g[0]), ~(b ? f.wid[1] : f.wid[0])};
   }
   template <class H>
   static __device__ __forceinline__ void make(const H& h, const Args&, const Item& it, uint32_t o) {
@@ -442,6 +461,7 @@ __global__ void gol_read_kernel(World w, uint32_t off, uint32_t n, uint8_t* out)
 __global__ void gol_set_slot_kernel(World w, uint32_t slot, uint32_t off, uint32_t side) {
   const_cast<uint32_t*>(w.off)[slot] = off;
   const_cast<uint32_t*>(w.side)[slot] = side;
+  const_cast<uint4*>(w.tab)[slot] = world_entry(off, side);
 }
 
 // Creates the objects of one world admitted into slot `slot`.
@@ -483,11 +503,12 @@ bool gol_heap_ok(const dsoar_heap* h) {
   return true;
 }
 
-// Device buffer of a world set: the world table (offsets and sides), the step
-// clock, the cell index (4 bytes per cell) and the two live-bit planes (each
+// Device buffer of a world set: the world table (offsets, sides and the packed
+// entries), the step clock, the cell index (4 bytes per cell) and the two live-bit planes (each
 // padded by two words, so that a window's second dword load past the last cell
 // stays inside, and to 16 bytes).
-uint64_t table_head(uint32_t num_worlds) { return ((uint64_t)(2 * num_worlds + 1) * 4 + 255) / 256 * 256; }
+uint64_t entries_at(uint32_t num_worlds) { return ((uint64_t)(2 * num_worlds + 1) * 4 + 15) / 16 * 16; }
+uint64_t table_head(uint32_t num_worlds) { return (entries_at(num_worlds) + (uint64_t)num_worlds * 16 + 255) / 256 * 256; }
 uint64_t index_bytes(uint64_t cells) { return (cells * 4 + 255) / 256 * 256; }
 uint64_t bits_bytes(uint64_t cells) { return (((cells + 31) / 32 + 2) * 4 + 255) / 256 * 256; }
 uint64_t world_set_bytes(uint32_t num_worlds, uint64_t cells) {
@@ -498,6 +519,7 @@ void carve(World& w, uint8_t* dev_mem, uint32_t num_worlds, uint64_t cells) {
   uint32_t* tab = (uint32_t*)dev_mem;
   w.off = tab;
   w.side = tab + num_worlds + 1;
+  w.tab = (const uint4*)(dev_mem + entries_at(num_worlds));
   uint8_t* b = dev_mem + table_head(num_worlds);
   w.clock = (const StepClock*)b;
   w.cells = (const uint32_t*)(b + 256);
@@ -572,7 +594,8 @@ int dsoar_gol_create(dsoar_heap* heap, uint32_t num_worlds, const uint32_t* side
   g->total = (uint32_t)gol_total_cells(num_worlds, sides);
   carve(g->w, (uint8_t*)dev_mem, num_worlds, g->total);
   uint32_t* tab = (uint32_t*)dev_mem;
-  uint32_t* host = (uint32_t*)malloc((size_t)(2 * num_worlds + 1) * 4);
+  const size_t bytes = (size_t)(entries_at(num_worlds) + (uint64_t)num_worlds * 16);
+  uint32_t* host = (uint32_t*)calloc(1, bytes);
   if (!host) {
     delete g;
     return DSOAR_ERR_INVALID_ARG;
@@ -581,10 +604,12 @@ int dsoar_gol_create(dsoar_heap* heap, uint32_t num_worlds, const uint32_t* side
   for (uint32_t i = 0; i < num_worlds; ++i) {
     host[i] = acc;
     host[num_worlds + 1 + i] = sides[i];
+    const uint4 entry = world_entry(acc, sides[i]);
+    memcpy((uint8_t*)host + entries_at(num_worlds) + (size_t)i * 16, &entry, 16);
     acc += sides[i] * sides[i];
   }
   host[num_worlds] = acc;
-  hipError_t e = hipMemcpyAsync(tab, host, (size_t)(2 * num_worlds + 1) * 4, hipMemcpyHostToDevice, (hipStream_t)stream);
+  hipError_t e = hipMemcpyAsync(tab, host, bytes, hipMemcpyHostToDevice, (hipStream_t)stream);
   if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);
   free(host);
   if (e != hipSuccess) {

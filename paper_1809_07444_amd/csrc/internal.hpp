@@ -589,13 +589,48 @@ __device__ __forceinline__ void doall_items(const H& h, uint32_t type, const uin
   Item* const items = reinterpret_cast<Item*>(item_lds) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * Method::kItems;
   const uint32_t lane = lane_id(), c = cap_of(h, type);
   const bool wide = c == 64;  // one entry per wavefront and slot, else 64 / c entries
-  const bool fast = kOnlyThis && !h.online_reclaim && wide;
   const Bitmap act = active_bm(h, type);
+  // Deletes of the last pass: the object-bitmap ANDs are issued at its end and
+  // their results used (settle) only when the next pass has made its loads, or
+  // before objects are created; the OR that returns blocks which were full to
+  // active[type] (one, for blocks of one level-0 group) then waits one pass
+  // more.  Blocks whose snapshot is full need no result (see DeletesOnlyThis).
+  const bool defer = wide && !h.online_reclaim;
+  uint32_t del_bid[2] = {0, 0};
+  uint64_t del_mask[2] = {0, 0}, del_prev[2] = {0, 0};
   uint32_t pend_word = 0;
   uint64_t pend_bits = 0, pend_prev = 0;
-  auto settle = [&]() __attribute__((always_inline)) {  // as in doall_list
+  auto settle_active = [&]() __attribute__((always_inline)) {
     if (pend_bits) bm_set_bits0_settle(act, pend_word, pend_bits, pend_prev);
     pend_bits = 0;
+  };
+  auto settle = [&]() __attribute__((always_inline)) {
+    if (!(del_mask[0] | del_mask[1])) return;
+    uint32_t word = 0;
+    uint64_t bits = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < 2; ++u) {
+      if (!del_mask[u]) continue;
+      const uint64_t pv = bcast64(del_prev[u]);
+      if ((pv & del_mask[u]) != del_mask[u]) lead_flag(h.ctrl + kCtlDoubleFree);
+      freed += (uint32_t)__popcll(pv & del_mask[u]);
+      if ((pv & del_mask[u]) && pv == ~0ull) {
+        chaos_pause(kChaosDeleteActive);
+        if (bits && (del_bid[u] >> 6) != word) {
+          bm_set_bits0(act, word, bits);
+          bits = 0;
+        }
+        word = del_bid[u] >> 6;
+        bits |= 1ull << (del_bid[u] & 63u);
+      }
+      del_mask[u] = 0;
+    }
+    settle_active();
+    if (bits) {
+      pend_word = word;
+      pend_bits = bits;
+      pend_prev = bm_set_bits0_issue(act, word, bits);
+    }
   };
   // Two entries per pass on lists of at least two per wavefront.
   const bool pairs = wide && count >= 2 * nw;
@@ -622,7 +657,6 @@ __device__ __forceinline__ void doall_items(const H& h, uint32_t type, const uin
       live[0] = (snap[0] >> lane) & 1ull;
       live[1] = (snap[1] >> lane) & 1ull;
       visits += (uint32_t)(__popcll(snap[0]) + __popcll(snap[1]));
-      settle();
       const uint32_t self[2] = {make_obj(bid[0], lane), make_obj(bid[1], lane)};
       Method::template find<2>(h, type, self, live, args, found, del);
     } else {
@@ -639,33 +673,36 @@ __device__ __forceinline__ void doall_items(const H& h, uint32_t type, const uin
       }
       live[0] = (snap[0] >> slot) & 1ull;
       visits += (uint32_t)__popcll(__ballot(live[0]));
-      settle();
       const uint32_t self[2] = {make_obj(bid[0], slot), 0u};
       Method::template find<1>(h, type, self, live, args, found, del);
     }
-    if (wide) {
+    settle();
+    if (defer) {
 #pragma unroll
       for (uint32_t u = 0; u < 2; ++u) {
         const uint64_t dm = __ballot(live[u] && del[u]);
         if (!dm) continue;
-        if (fast && snap[u] == ~0ull) {  // a full block (see DeletesOnlyThis): nothing to wait for
-          if (is_first_active())
+        del_bid[u] = bid[u];
+        del_mask[u] = dm;
+        if (kOnlyThis && snap[u] == ~0ull) {
+          del_prev[u] = ~0ull;
+          if (lane == 0)
             __hip_atomic_fetch_and(h.obj_bitmap + bid[u], ~dm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          freed += (uint32_t)__popcll(dm);
-          chaos_pause(kChaosDeleteActive);
-          settle();
-          pend_word = bid[u] >> 6;
-          pend_bits = 1ull << (bid[u] & 63u);
-          pend_prev = bm_set_bits0_issue(act, pend_word, pend_bits);
-        } else {
-          freed += delete_mask(h, type, bid[u], dm);
+        } else if (lane == 0) {
+          del_prev[u] = __hip_atomic_fetch_and(h.obj_bitmap + bid[u], ~dm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
       }
     } else {
-      const uint64_t dm = __ballot(live[0] && del[0]), group = (1ull << c) - 1ull;
-      for (uint32_t k = 0; k < 64u >> sh && dm; ++k) {
-        const uint64_t part = (dm >> (k * c)) & group;
-        if (part) freed += delete_mask(h, type, (uint32_t)__builtin_amdgcn_readlane(bid[0], k * c), part);
+      // Online reclamation, or 64 / c blocks per wavefront.
+      const uint32_t per_wave = 64u >> sh;
+      const uint64_t group = wide ? ~0ull : (1ull << c) - 1ull;
+#pragma unroll
+      for (uint32_t u = 0; u < 2; ++u) {
+        const uint64_t dm = __ballot(live[u] && del[u]);
+        for (uint32_t k = 0; k < per_wave && dm; ++k) {
+          const uint64_t part = (dm >> (k * c)) & group;
+          if (part) freed += delete_mask(h, type, (uint32_t)__builtin_amdgcn_readlane(bid[u], k * c), part);
+        }
       }
     }
     const bool last = e0 + (uint64_t)per * nw >= count;
@@ -688,6 +725,7 @@ __device__ __forceinline__ void doall_items(const H& h, uint32_t type, const uin
       if (!over && !last) break;
       __builtin_amdgcn_wave_barrier();
       settle();
+      settle_active();
       new_items(h, Method::kItemType, n, [&](uint32_t r, uint32_t o) __attribute__((always_inline)) {
         if (o != kNull) Method::make(h, args, items[r], o);
       });
@@ -697,6 +735,7 @@ __device__ __forceinline__ void doall_items(const H& h, uint32_t type, const uin
     }
   }
   settle();
+  settle_active();
 }
 
 // Adds a wavefront's visits and deletes to the counters.
