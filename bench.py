@@ -476,13 +476,11 @@ class WatorWorkload(GolWorkload):
 
     def kernel_bytes(self, kind, launches, st):
         vf, vs = st["visits"][0] / 3, st["visits"][1] / 2  # three fish do-alls, two shark do-alls per step
-        # Fields read and written, the four neighbours' kinds, the request
-        # word (an atomic in Decide, a read in Move), the sea cells written,
-        # and the newborns' fields.
-        # (this, other) per visit: the animal's own fields; the four
-        # neighbours' kinds, the request words and the sea cells written.
-        per_f = {"wator_fish_decide": (8, 16 + 8), "wator_fish_move": (12, 8 + 16), "wator_fish_eaten": (8, 0)}
-        per_s = {"wator_shark_decide": (12, 16 + 8), "wator_shark_move": (16, 12 + 20)}
+        # (this, other) per visit: the animal's own fields; the kinds or
+        # requests of a cell and its four neighbours, its own request and the
+        # sea cells written (a byte each).  Newborns' fields apart.
+        per_f = {"wator_fish_decide": (8, 5 + 1), "wator_fish_move": (16, 5 + 2)}
+        per_s = {"wator_shark_decide": (12, 5 + 1), "wator_shark_move": (24, 6 + 2)}
         fish0 = int((self.inp.kind == 1).sum())
         shark0 = int((self.inp.kind == 2).sum())
         if kind in per_f:
@@ -493,10 +491,10 @@ class WatorWorkload(GolWorkload):
             return vs * per_s[kind][0] + vs / 64 * 12 + born, vs * per_s[kind][1]
         if kind == "wator_init":
             # new animals' fields; other: kind, age, energy read, sea byte
-            # and request word written per cell
-            return fish0 * 12 + shark0 * 16 + (fish0 + shark0) / 64 * 12, self.side ** 2 * (12 + 1 + 8)
-        if kind == "wator_tick":
-            return launches * 8
+            # written per cell
+            return fish0 * 12 + shark0 * 16 + (fish0 + shark0) / 64 * 12, self.side ** 2 * (12 + 1)
+        if kind == "wator_fish_eaten":  # after a call's last step
+            return st["live"][0] * 4, st["live"][0]
         if kind == "enumerate":
             return launches * (self.M / 8) + (vf + vs) / 64 * 20
         return None

@@ -1240,7 +1240,8 @@ __device__ inline uint32_t dsoar_new(const H& h, uint32_t type) {
 
 // Online reclamation: the wavefront whose delete left block `bid` of `type`
 // empty frees it at once (the block-state figure's return to free, inside a
-// kernel).  Used when the heap's online_reclaim is set.
+// kernel).  Used when the heap's online_reclaim is set (only then counted), and
+// by do-alls that prune their list.
 //  1 Invalidate: compare-and-swap the object bitmap from 0 to all ones.  If
 //    that fails an allocation got in first and the block stays.  All ones
 //    reads as full, so no reservation can gain a slot from here on.
@@ -1293,7 +1294,7 @@ __device__ inline bool try_release(const H& h, uint32_t type, uint32_t bid) {
   wait_performed();
   chaos_pause(kChaosRelease);
   bm_set(free_bm(h), bid);
-  lead_add(shard(h) + kCntReleases, 1);
+  if (h.online_reclaim) lead_add(shard(h) + kCntReleases, 1);
   return true;
 }
 

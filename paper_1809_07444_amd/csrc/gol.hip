@@ -51,17 +51,10 @@ struct World {
   const StepClock* clock; // epoch: any value, its low bit names the current plane
 };
 
-// World table entry: a cell's row is its local index divided by the side, by
-// one multiplication with the side's inverse and one correction (world_row).
+// World table entry (with the side's inverse, for row_of).
 __host__ __device__ inline uint4 world_entry(uint32_t off, uint32_t side) {
-  return uint4{off, side, 0xFFFFFFFFu / side, off + side * side};
+  return uint4{off, side, inverse_of(side), off + side * side};
 }
-// floor(local / side): the product is that or one less.
-__device__ __forceinline__ uint32_t world_row(uint32_t local, uint32_t side, uint32_t inverse) {
-  const uint32_t q = __umulhi(local, inverse);
-  return local - q * side >= side ? q + 1u : q;
-}
-
 // The plane of the state that `epoch` names.
 __device__ __forceinline__ uint32_t* plane_at(const World& w, uint32_t epoch) {
   return (epoch & 1u) ? w.plane[1] : w.plane[0];
@@ -150,7 +143,7 @@ __device__ __forceinline__ CellPos cell_pos(const World& w, uint32_t g, uint32_t
   p.side = live ? t.y : 5u;
   p.end = live ? t.w : 25u;
   const uint32_t local = live ? g - p.off : 0u;
-  const uint32_t y = live ? world_row(local, p.side, t.z) : 0u;
+  const uint32_t y = live ? row_of(local, p.side, t.z) : 0u;
   p.x = local - y * p.side;
   const uint32_t r = p.off + local - p.x;
   p.row[2] = r;

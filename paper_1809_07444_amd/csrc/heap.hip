@@ -305,13 +305,27 @@ __device__ __forceinline__ uint64_t pack_flag(uint32_t epoch, uint64_t status, u
 // ticket counter.  Each wavefront covers
 // WPW level-0 words (64 blocks each); all their loads are issued before any
 // is used.  The heap is quiescent, so plain loads see the previous kernels.
-template <uint32_t WPW, uint32_t LG, bool kCopy>
+// Beside is PlaneCopy, StepStart or NoCopy.
+template <uint32_t WPW, uint32_t LG, class Beside>
 __global__ void __launch_bounds__(enum_waves(WPW) * 64)
-    enumerate_kernel(DevHeapW<LG> h, uint32_t type, EnumOut out, std::conditional_t<kCopy, PlaneCopy, NoCopy> copy) {
+    enumerate_kernel(DevHeapW<LG> h, uint32_t type, EnumOut out, Beside copy) {
   constexpr uint32_t kEnumWaves = enum_waves(WPW);
   __shared__ uint32_t s_tile, s_epoch, s_prefix;
   __shared__ uint32_t s_wave_total[kEnumWaves];
-  if constexpr (kCopy) {
+  if constexpr (std::is_same_v<Beside, StepStart>) {
+    const uint32_t tiles = out.num_tiles;  // both lists scan the same blocks
+    if (blockIdx.x >= 2 * tiles) {
+      const uint32_t wgs = gridDim.x - 2 * tiles;
+      for (uint32_t i = (blockIdx.x - 2 * tiles) * blockDim.x + threadIdx.x; i < copy.words; i += wgs * blockDim.x)
+        copy.plane[i] = uint4{0, 0, 0, 0};
+      return;
+    }
+    if (blockIdx.x >= tiles) {
+      type = copy.type2;
+      out = copy.out2;
+    }
+  }
+  if constexpr (std::is_same_v<Beside, PlaneCopy>) {
     if (blockIdx.x >= out.num_tiles) {  // beside the scan: the step's plane copy
       const uint32_t now = copy.clock->epoch & 1u, wgs = gridDim.x - out.num_tiles;
       const uint4* src = now ? copy.plane[1] : copy.plane[0];
@@ -687,10 +701,10 @@ int launch_enumerate_into(dsoar_heap* h, uint32_t type, const EnumOut& eo, hipSt
       if (copy) {
         // One 16-byte word of the copy per thread, up to a workgroup per CU.
         const uint32_t copiers = std::min((copy->words + threads - 1) / threads, h->num_cus);
-        launch_timed(h, kKindEnumerate, enumerate_kernel<kWPW, kLG, true>, dim3(h->num_tiles + copiers), dim3(threads), s,
+        launch_timed(h, kKindEnumerate, enumerate_kernel<kWPW, kLG, PlaneCopy>, dim3(h->num_tiles + copiers), dim3(threads), s,
                      DevHeapW<kLG>(h->dev), type, eo, *copy);
       } else {
-        launch_timed(h, kKindEnumerate, enumerate_kernel<kWPW, kLG, false>, dim3(h->num_tiles), dim3(threads), s,
+        launch_timed(h, kKindEnumerate, enumerate_kernel<kWPW, kLG, NoCopy>, dim3(h->num_tiles), dim3(threads), s,
                      DevHeapW<kLG>(h->dev), type, eo, NoCopy{});
       }
     };
@@ -705,6 +719,27 @@ int launch_enumerate(dsoar_heap* h, uint32_t type, hipStream_t s, StepClock* clo
   EnumOut eo = h->enum_out[type];
   eo.clock = clock;
   return launch_enumerate_into(h, type, eo, s, copy);
+}
+
+int launch_enumerate_pair(dsoar_heap* h, uint32_t type, uint32_t type2, hipStream_t s, StepClock* clock, uint4* plane,
+                          uint32_t words) {
+  EnumOut eo = h->enum_out[type];
+  eo.clock = clock;
+  const StepStart start{plane, words, type2, h->enum_out[type2]};
+  with_width(h, [&](auto w_) {
+    constexpr uint32_t kLG = decltype(w_)::value;
+    auto go = [&](auto wpw) {
+      constexpr uint32_t kWPW = decltype(wpw)::value;
+      constexpr uint32_t threads = enum_waves(kWPW) * 64;
+      const uint32_t clearers = std::min((words + threads - 1) / threads, h->num_cus);
+      launch_timed(h, kKindEnumerate, enumerate_kernel<kWPW, kLG, StepStart>, dim3(2 * h->num_tiles + clearers),
+                   dim3(threads), s, DevHeapW<kLG>(h->dev), type, eo, start);
+    };
+    if (h->enum_wpw == kEnumWideWords) go(std::integral_constant<uint32_t, kEnumWideWords>{});
+    else go(std::integral_constant<uint32_t, 1>{});
+  });
+  DSOAR_LAUNCHED(h);
+  return DSOAR_OK;
 }
 
 // Scratch of the allocation-free enumeration (dsoar_enumerate_noalloc): the

@@ -56,6 +56,14 @@ struct PlaneCopy {
 };
 struct NoCopy {};
 
+// floor(local / side) for inverse = 0xFFFFFFFF / side: one multiplication,
+// whose high half is that or one less, and one correction.
+__host__ __device__ inline uint32_t inverse_of(uint32_t side) { return 0xFFFFFFFFu / side; }
+__device__ __forceinline__ uint32_t row_of(uint32_t local, uint32_t side, uint32_t inverse) {
+  const uint32_t q = __umulhi(local, inverse);
+  return local - q * side >= side ? q + 1u : q;
+}
+
 struct EnumOut {
   uint32_t* R;          // compacted block ids
   uint64_t* S;          // snapshot of each listed block's object bitmap
@@ -64,6 +72,15 @@ struct EnumOut {
   uint32_t num_tiles;
   uint32_t* count_out;  // where the count also goes (nullptr: only st->count)
   StepClock* clock;     // advanced by one step (nullptr: none)
+};
+
+// What an application's step starts with, in one launch of the enumeration:
+// the lists of two types, and a plane cleared by more workgroups beside them.
+struct StepStart {
+  uint4* plane;
+  uint32_t words;  // 16-byte words to clear
+  uint32_t type2;
+  EnumOut out2;
 };
 
 struct StatsOut {
@@ -128,7 +145,7 @@ constexpr uint32_t kKindSugarAdmit = 47;
 constexpr uint32_t kKindTrafficInit = 53;
 constexpr uint32_t kKindCollideInit = 66;
 constexpr uint32_t kKindWatorInit = 77;
-constexpr uint32_t kKindWatorTick = 78;
+constexpr uint32_t kKindWatorTick = 78;  // of earlier traces: the enumeration advances the step
 
 // Launches `kernel` on stream s.  With timing on (and room in the record), the
 // launch itself carries a start and a stop event (hipExtLaunchKernel): they
@@ -164,6 +181,9 @@ inline void with_width(const dsoar_heap* h, F&& f) {
 
 int launch_enumerate(dsoar_heap* h, uint32_t type, hipStream_t s, StepClock* clock = nullptr,
                      const PlaneCopy* copy = nullptr);
+// The lists of two types at once; clears `words` 16-byte words of `plane`.
+int launch_enumerate_pair(dsoar_heap* h, uint32_t type, uint32_t type2, hipStream_t s, StepClock* clock, uint4* plane,
+                          uint32_t words);
 int read_count(dsoar_heap* h, uint32_t type, hipStream_t s, uint32_t* count);
 
 // A method may split into a load phase and an apply phase:
@@ -238,6 +258,18 @@ template <class M, class = void>
 struct Phases : std::integral_constant<uint32_t, 1> {};
 template <class M>
 struct Phases<M, std::void_t<decltype(M::kPhases)>> : std::integral_constant<uint32_t, M::kPhases> {};
+
+// A method whose deletes belong before the do-alls that reuse its list declares
+//   static constexpr bool kPrunes = true;
+// (it creates nothing): the slots it deletes leave the list's snapshots, so
+// that a later do-all over the list visits neither them nor objects made in
+// their place, blocks that they leave empty are free at once, as after the
+// enumeration that would otherwise stand between the two, and only the objects
+// that stay count as visited.
+template <class M, class = void>
+struct Prunes : std::false_type {};
+template <class M>
+struct Prunes<M, std::void_t<decltype(M::kPrunes)>> : std::integral_constant<bool, M::kPrunes> {};
 
 // A method may queue the objects it creates:
 //   struct Found { uint32_t claims; ... };   // bit b of claims: this lane creates an object from item(found, b)
@@ -551,7 +583,33 @@ __device__ __forceinline__ void doall_list(const H& h, uint32_t type, const uint
       settle();
       const bool del = run_slot<Method>(h, type, make_obj(bid, lane), (snap >> lane) & 1ull, args);
       const uint64_t dm = __ballot(del);
-      if (dm) remove(bid, snap, dm);
+      if constexpr (Prunes<Method>::value) {
+        if (dm) {
+          if (lane == 0) const_cast<uint64_t*>(S)[e] = snap & ~dm;
+          if (h.online_reclaim) {
+            freed += delete_mask(h, type, bid, dm);
+          } else {
+            // Nothing but this wavefront changes the block meanwhile, so its
+            // snapshot is what the delete finds: no result to wait for.
+            if (lane == 0)
+              __hip_atomic_fetch_and(h.obj_bitmap + bid, ~dm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            freed += (uint32_t)__popcll(dm);
+            if (snap == ~0ull) {
+              chaos_pause(kChaosDeleteActive);
+              settle();
+              pend_word = bid >> 6;
+              pend_bits = 1ull << (bid & 63u);
+              pend_prev = bm_set_bits0_issue(act, pend_word, pend_bits);
+            }
+            if (snap == dm) {
+              settle();
+              try_release(h, type, bid);
+            }
+          }
+        }
+      } else {
+        if (dm) remove(bid, snap, dm);
+      }
     }
     settle();
   } else {
@@ -568,9 +626,17 @@ __device__ __forceinline__ void doall_list(const H& h, uint32_t type, const uint
       visits += (uint32_t)__popcll(__ballot((snap >> slot) & 1ull));
       const bool del = run_slot<Method>(h, type, make_obj(bid, slot), (snap >> slot) & 1ull, args);
       const uint64_t dm = __ballot(del);
+      uint64_t emptied = 0;  // the lanes of the blocks that the deletes leave empty
+      if constexpr (Prunes<Method>::value) {
+        const uint64_t mine = (dm >> (sub << sh)) & group;
+        if (valid && mine && slot == 0) const_cast<uint64_t*>(S)[e] = snap & ~mine;
+        if (!h.online_reclaim) emptied = __ballot(valid && mine && snap == mine);
+      }
       for (uint32_t k = 0; k < bpw && dm; ++k) {
         const uint64_t part = (dm >> (k * c)) & group;
-        if (part) freed += delete_mask(h, type, (uint32_t)__builtin_amdgcn_readlane(bid, k * c), part);
+        const uint32_t b = (uint32_t)__builtin_amdgcn_readlane(bid, k * c);
+        if (part) freed += delete_mask(h, type, b, part);
+        if (Prunes<Method>::value && ((emptied >> (k * c)) & 1ull)) try_release(h, type, b);
       }
     }
   }
@@ -741,6 +807,7 @@ __device__ __forceinline__ void doall_items(const H& h, uint32_t type, const uin
 // Adds a wavefront's visits and deletes to the counters.
 template <class Method, class H>
 __device__ __forceinline__ void doall_count(const H& h, uint32_t type, uint32_t visits, uint32_t freed) {
+  if (Prunes<Method>::value) visits -= freed;
   if (Phases<Method>::value && visits) lead_add(shard(h) + kCntVisits + type, visits * Phases<Method>::value);
   if (freed) lead_add(shard(h) + kCntFrees + type, freed);
 }

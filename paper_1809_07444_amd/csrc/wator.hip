@@ -2,10 +2,15 @@
 // application, Fig. 6h; Dewdney's rules, read as a synchronous step).  Fish
 // {pos, age, target} and Shark {pos, age, energy, target} objects live in the
 // heap; the sea is a plain cell -> kind array (0 empty, 1 fish, 2 shark) and a
-// cell -> request word array.  One step t:
-//   FishDecide (do-all Fish): on the sea at the start of the phase, pick the
-//     k-th empty neighbour (up, right, down, left), k = U{0..n-1} from
-//     hash(seed, 40, cell, t); request it (atomicMin of the phase key).
+// cell -> request array.  One step t:
+//   Both lists are enumerated at once; beside them the requests are cleared and
+//     t goes up by one (the step index lives on the device, so a captured step
+//     replays correctly).
+//   FishDecide (do-all Fish): a fish whose cell the sharks took in the step
+//     before deletes itself; the others pick, on the sea at the start of the
+//     phase, the k-th empty neighbour (up, right, down, left), k = U{0..n-1}
+//     from hash(seed, 40, cell, t), and leave the direction in their own cell
+//     of the request array.
 //   FishMove (same list): the lowest requesting cell wins; the winner moves
 //     and, at age >= fish_breed, leaves a new Fish behind (both age 0).
 //     Every fish ages by one.
@@ -15,13 +20,9 @@
 //   SharkMove (same list): the lowest requesting cell wins; a winner that
 //     lands on a fish eats it (energy = starve), any other shark loses one
 //     unit and deletes itself at 0; breeding as for fish.
-//   FishEaten (do-all Fish): a fish whose cell now holds a shark deletes
-//     itself.
-//   Tick: t += 1 (the step index lives on the device, so a captured step
-//     replays correctly).
-// Request words carry the phase in their high half (larger for earlier
-// phases), so a phase's atomicMin always replaces what earlier phases left
-// and the array never needs clearing.
+// After the last step of a call FishEaten (do-all Fish) deletes the fish whose
+// cells the sharks took: nothing between SharkMove and the next FishDecide
+// looks at them, so in between the check rides on FishDecide's pass.
 #include <string.h>
 
 #include <new>
@@ -57,28 +58,95 @@ __device__ __forceinline__ uint32_t pick(uint64_t h, uint32_t n) {
 }
 
 struct Sea {
-  uint8_t* kind;    // cell -> kEmpty, kIsFish or kIsShark (one byte: the sea of 2048^2 fits an L2)
-  uint64_t* req;    // cell -> smallest request key of the latest phase that asked for it
-  uint32_t* step;   // [0]: index of the step in progress
-  uint32_t side;
+  uint8_t* kind;     // kEmpty, kIsFish or kIsShark
+  uint8_t* want;     // this step's requests: 0, kFishWants + d or kSharkWants + d for a move in direction d
+  StepClock* clock;  // t: index of the step in progress
+  uint32_t side, inverse;
   uint64_t seed;
   int32_t fish_breed, shark_breed, starve;
 };
+constexpr uint32_t kFishWants = 1, kSharkWants = 5;
 
-// Request key of cell c in phase `tag` (2t: fish, 2t + 1: sharks).
-__device__ __forceinline__ uint64_t req_key(uint32_t tag, uint32_t c) {
-  return ((uint64_t)(0xFFFFFFFFu - tag) << 32) | c;
+// The planes keep the rows in groups of four, each group column by column (the
+// last group of a side that is not a multiple of four has the rows that are
+// left): a cell and its neighbours are three adjacent dwords and, for the
+// outer rows of a group, one byte more, from 1.5 lines instead of three.
+// (With an 8-byte word per target, an atomic minimum over the requesters and the
+// kinds row by row, a step's FishDecide, FishMove, SharkDecide, SharkMove and
+// FishEaten took 52 + 93 + 20 + 41 + 26 us on average over 50 steps of 2048^2,
+// 1.75 M fish; now 44 + 80 + 13 + 44 and FishEaten once per call.  The lists in
+// runs per XCD do not help: 10.04 ms per 50 steps against 10.07.)
+__device__ __forceinline__ uint32_t byte_at(const Sea& a, uint32_t x, uint32_t y) {
+  const uint32_t r = y & 3u, g = y - r;
+  return g * a.side + x * (g + 4u <= a.side ? 4u : a.side & 3u) + r;
 }
 
-// Neighbour d of cell c: up, right, down, left.
-__device__ __forceinline__ uint32_t nb(uint32_t side, uint32_t c, uint32_t d) {
-  const uint32_t y = c / side, x = c - y * side;
-  uint32_t nx = x, ny = y;
-  if (d == 0) ny = y == 0 ? side - 1 : y - 1;
-  if (d == 1) nx = x + 1 == side ? 0 : x + 1;
-  if (d == 2) ny = y + 1 == side ? 0 : y + 1;
-  if (d == 3) nx = x == 0 ? side - 1 : x - 1;
-  return ny * side + nx;
+// A cell, its place in the planes and its four neighbours' coordinates.
+struct Spot {
+  uint32_t x, y, up, right, down, left;
+};
+__device__ __forceinline__ Spot spot(const Sea& a, uint32_t c) {
+  Spot p;
+  p.y = row_of(c, a.side, a.inverse);
+  p.x = c - p.y * a.side;
+  p.up = (p.y == 0 ? a.side : p.y) - 1u;
+  p.right = p.x + 1u == a.side ? 0u : p.x + 1u;
+  p.down = p.y + 1u == a.side ? 0u : p.y + 1u;
+  p.left = (p.x == 0 ? a.side : p.x) - 1u;
+  return p;
+}
+// Neighbour d of a cell: up, right, down, left.
+__device__ __forceinline__ uint32_t nb(const Sea& a, const Spot& p, uint32_t d) {
+  // Values first: a choice among the members would index the struct in scratch.
+  const uint32_t x = p.x, y = p.y, up = p.up, right = p.right, down = p.down, left = p.left;
+  uint32_t ny = y, nx = x;
+  if (d == 0) ny = up;
+  if (d == 1) nx = right;
+  if (d == 2) ny = down;
+  if (d == 3) nx = left;
+  return ny * a.side + nx;
+}
+
+// The bytes of a cell's four neighbours (v[0..3]: up, right, down, left) and
+// its own (v[4]).
+__device__ __forceinline__ void around(const uint8_t* plane, const Sea& a, const Spot& p, uint32_t (&v)[5]) {
+  const uint32_t r = p.y & 3u;
+  if (p.x - 1u < a.side - 2u && (p.y | 3u) < a.side) {
+    const uint32_t* d = (const uint32_t*)(plane + (p.y - r) * a.side + 4u * (p.x - 1u));
+    const uint32_t left = d[0], mid = d[1], right = d[2];
+    uint32_t other = 0;
+    if (r == 0 || r == 3) other = plane[byte_at(a, p.x, r == 0 ? p.up : p.down)];
+    const uint32_t sh = 8u * r;
+    v[0] = r == 0 ? other : (mid >> (sh - 8u)) & 0xFFu;
+    v[1] = (right >> sh) & 0xFFu;
+    v[2] = r == 3 ? other : (mid >> (sh + 8u)) & 0xFFu;
+    v[3] = (left >> sh) & 0xFFu;
+    v[4] = (mid >> sh) & 0xFFu;
+  } else {
+    v[0] = plane[byte_at(a, p.x, p.up)];
+    v[1] = plane[byte_at(a, p.right, p.y)];
+    v[2] = plane[byte_at(a, p.x, p.down)];
+    v[3] = plane[byte_at(a, p.left, p.y)];
+    v[4] = plane[byte_at(a, p.x, p.y)];
+  }
+}
+
+// The k-th direction of a mask of directions.
+__device__ __forceinline__ uint32_t nth_direction(uint32_t mask, uint32_t k) {
+  for (; k > 0; --k) mask &= mask - 1u;
+  return (uint32_t)__builtin_ctz(mask);
+}
+
+// The lowest cell that asks for cell q (requests of one kind from `first` on):
+// an animal moving in direction d comes from the neighbour opposite to d.
+__device__ __forceinline__ uint32_t lowest_asker(const Sea& a, const Spot& q, const uint32_t (&v)[5], uint32_t first) {
+  uint32_t best = kNone;
+#pragma unroll
+  for (uint32_t d = 0; d < 4; ++d) {
+    const uint32_t from = (d + 2u) & 3u, c = nb(a, q, from);
+    if (v[from] == first + d && c < best) best = c;
+  }
+  return best;
 }
 
 template <class F, class H>
@@ -92,51 +160,95 @@ __device__ __forceinline__ F& shark(const H& h, uint32_t self, uint32_t field) {
 
 struct FishDecide {
   static constexpr uint32_t kKind = 70;
+  static constexpr bool kPrunes = true;
   using Args = Sea;
   template <class H>
   static __device__ bool run(const H& h, uint32_t, uint32_t self, const Args& a) {
-    const uint32_t t = a.step[0];
     const uint32_t c = fish<uint32_t>(h, self, kPos);
-    uint32_t opt[4], m = 0;
+    const Spot p = spot(a, c);
+    uint32_t v[5];
+    around(a.kind, a, p, v);
+    if (v[4] != kIsFish) return true;  // eaten in the step before
+    uint32_t empty = 0;
 #pragma unroll
-    for (uint32_t d = 0; d < 4; ++d) {
-      const uint32_t q = nb(a.side, c, d);
-      if (a.kind[q] == kEmpty) opt[m++] = q;
-    }
+    for (uint32_t d = 0; d < 4; ++d) empty |= v[d] == kEmpty ? 1u << d : 0u;
     uint32_t target = kNone;
-    if (m > 0) {
-      target = opt[pick(draw(a.seed, kStreamFish, c, t), m)];
-      atomicMin((unsigned long long*)(a.req + target), (unsigned long long)req_key(2 * t, c));
+    if (empty) {
+      const uint32_t d = nth_direction(empty, pick(draw(a.seed, kStreamFish, c, a.clock->t), (uint32_t)__popc(empty)));
+      target = nb(a, p, d);
+      a.want[byte_at(a, p.x, p.y)] = (uint8_t)(kFishWants + d);
     }
     fish<uint32_t>(h, self, kFTarget) = target;
     return false;
   }
 };
 
+// What a newborn is made from, inverted: the words are left in LDS, where
+// later kernels read search hints, and small ones would send many wavefronts
+// to the same groups.
+struct Newborn {
+  uint32_t not_c;
+};
+
 struct FishMove {
   static constexpr uint32_t kKind = 71;
-  static constexpr uint32_t kMinWaves = 8;
+  // Its own visits and, of the fish that FishEaten or FishDecide looks over
+  // after the step, those that are not newborn (make counts these).
+  static constexpr uint32_t kPhases = 2;
   using Args = Sea;
-  template <class H>
-  static __device__ bool run(const H& h, uint32_t, uint32_t self, const Args& a) {
-    const uint32_t t = a.step[0];
-    const uint32_t c = fish<uint32_t>(h, self, kPos), target = fish<uint32_t>(h, self, kFTarget);
-    const int32_t age = fish<int32_t>(h, self, kAge) + 1;
-    const bool won = target != kNone && a.req[target] == req_key(2 * t, c);
-    const bool breed = won && age >= a.fish_breed;
-    if (won) {
-      a.kind[target] = kIsFish;
-      fish<uint32_t>(h, self, kPos) = target;
-      if (!breed) a.kind[c] = kEmpty;  // else the newborn keeps the cell
+  using Item = Newborn;
+  static constexpr uint32_t kItemType = kFish;
+  static constexpr uint32_t kMinWaves = 8;
+  static constexpr uint32_t kItems = 256, kClaimBits = 2;
+  struct Found {
+    uint32_t claims;  // bit u: object u breeds
+    uint32_t c[2];
+  };
+  template <uint32_t N, class H>
+  static __device__ __forceinline__ void find(const H& h, uint32_t, const uint32_t (&self)[2], const bool (&lv)[2],
+                                              const Args& a, Found& found, bool (&)[2]) {
+    uint32_t q[N];
+    int32_t age[N];
+    bool won[N];
+#pragma unroll
+    for (uint32_t u = 0; u < N; ++u) {
+      const uint32_t c = fish<uint32_t>(h, self[u], kPos), target = fish<uint32_t>(h, self[u], kFTarget);
+      age[u] = fish<int32_t>(h, self[u], kAge) + 1;
+      found.c[u] = lv[u] ? c : 0u;
+      won[u] = lv[u] && target != kNone;
+      q[u] = won[u] ? target : found.c[u];
     }
-    fish<int32_t>(h, self, kAge) = breed ? 0 : age;
-    new_many(h, kFish, breed ? 1u : 0u, [&](uint32_t, uint32_t o) {
-      if (o == kNull) return;
-      fish<uint32_t>(h, o, kPos) = c;
-      fish<int32_t>(h, o, kAge) = 0;
-      fish<uint32_t>(h, o, kFTarget) = kNone;
-    });
-    return false;
+    Spot to[N];
+    uint32_t v[N][5];
+#pragma unroll
+    for (uint32_t u = 0; u < N; ++u) {
+      to[u] = spot(a, q[u]);
+      around(a.want, a, to[u], v[u]);
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < N; ++u) {
+      const uint32_t c = found.c[u];
+      won[u] = won[u] && lowest_asker(a, to[u], v[u], kFishWants) == c;
+      const bool breed = won[u] && age[u] >= a.fish_breed;
+      if (won[u]) {
+        a.kind[byte_at(a, to[u].x, to[u].y)] = kIsFish;
+        fish<uint32_t>(h, self[u], kPos) = q[u];
+        if (!breed) {  // else the newborn keeps the cell
+          const uint32_t y = row_of(c, a.side, a.inverse);
+          a.kind[byte_at(a, c - y * a.side, y)] = kEmpty;
+        }
+      }
+      if (lv[u]) fish<int32_t>(h, self[u], kAge) = breed ? 0 : age[u];
+      if (breed) found.claims |= 1u << u;
+    }
+  }
+  static __device__ __forceinline__ Item item(const Found& f, uint32_t b) { return {~(b ? f.c[1] : f.c[0])}; }
+  template <class H>
+  static __device__ __forceinline__ void make(const H& h, const Args&, const Item& it, uint32_t o) {
+    fish<uint32_t>(h, o, kPos) = ~it.not_c;
+    fish<int32_t>(h, o, kAge) = 0;
+    fish<uint32_t>(h, o, kFTarget) = kNone;
+    lead_add(shard(h) + kCntVisits + kFish, (uint64_t)__popcll(__ballot(true)));
   }
 };
 
@@ -145,24 +257,23 @@ struct SharkDecide {
   using Args = Sea;
   template <class H>
   static __device__ bool run(const H& h, uint32_t, uint32_t self, const Args& a) {
-    const uint32_t t = a.step[0];
     const uint32_t c = shark<uint32_t>(h, self, kPos);
-    uint32_t fishn[4], empty[4], nf = 0, ne = 0;
+    const bool strong = shark<int32_t>(h, self, kEnergy) > 1;
+    const Spot p = spot(a, c);
+    uint32_t v[5], fishes = 0, empty = 0;
+    around(a.kind, a, p, v);
 #pragma unroll
     for (uint32_t d = 0; d < 4; ++d) {
-      const uint32_t q = nb(a.side, c, d);
-      const uint8_t k = a.kind[q];
-      if (k == kIsFish) fishn[nf++] = q;
-      if (k == kEmpty) empty[ne++] = q;
+      fishes |= v[d] == kIsFish ? 1u << d : 0u;
+      empty |= v[d] == kEmpty ? 1u << d : 0u;
     }
-    const uint64_t hs = draw(a.seed, kStreamShark, c, t);
+    const uint32_t from = fishes ? fishes : strong ? empty : 0u;
     uint32_t target = kNone;
-    if (nf > 0)
-      target = fishn[pick(hs, nf)];
-    else if (ne > 0 && shark<int32_t>(h, self, kEnergy) > 1)
-      target = empty[pick(hs, ne)];
-    if (target != kNone)
-      atomicMin((unsigned long long*)(a.req + target), (unsigned long long)req_key(2 * t + 1, c));
+    if (from) {
+      const uint32_t d = nth_direction(from, pick(draw(a.seed, kStreamShark, c, a.clock->t), (uint32_t)__popc(from)));
+      target = nb(a, p, d);
+      a.want[byte_at(a, p.x, p.y)] = (uint8_t)(kSharkWants + d);
+    }
     shark<uint32_t>(h, self, kSTarget) = target;
     return false;
   }
@@ -175,23 +286,29 @@ struct SharkMove {
   using Args = Sea;
   template <class H>
   static __device__ bool run(const H& h, uint32_t, uint32_t self, const Args& a) {
-    const uint32_t t = a.step[0];
     const uint32_t c = shark<uint32_t>(h, self, kPos), target = shark<uint32_t>(h, self, kSTarget);
-    const bool won = target != kNone && a.req[target] == req_key(2 * t + 1, c);
-    // Only the winner writes its target cell, and no shark targets a shark's
-    // cell, so this read sees the sea as the fish phase left it.
-    const bool ate = won && a.kind[target] == kIsFish;
-    const int32_t energy = ate ? a.starve : shark<int32_t>(h, self, kEnergy) - 1;
     const int32_t age = shark<int32_t>(h, self, kAge) + 1;
-    if (energy <= 0) {  // starved (a shark that eats never does)
-      a.kind[c] = kEmpty;
-      return true;
+    int32_t energy = shark<int32_t>(h, self, kEnergy) - 1;
+    bool won = target != kNone;
+    const Spot to = spot(a, won ? target : c);
+    const uint32_t there = byte_at(a, to.x, to.y);
+    // Only the winner writes its target cell, and no shark targets a shark's
+    // cell, so a winner's read sees the sea as the fish phase left it.
+    const uint32_t kind = a.kind[there];
+    uint32_t v[5];
+    around(a.want, a, to, v);
+    won = won && lowest_asker(a, to, v, kSharkWants) == c;
+    if (won && kind == kIsFish) energy = a.starve;
+    const bool starved = energy <= 0;  // a shark that eats never does
+    const bool breed = won && !starved && age >= a.shark_breed;
+    if (starved || (won && !breed)) {  // else a newborn keeps the cell
+      const uint32_t y = row_of(c, a.side, a.inverse);
+      a.kind[byte_at(a, c - y * a.side, y)] = kEmpty;
     }
-    const bool breed = won && age >= a.shark_breed;
+    if (starved) return true;
     if (won) {
-      a.kind[target] = kIsShark;
+      a.kind[there] = kIsShark;
       shark<uint32_t>(h, self, kPos) = target;
-      if (!breed) a.kind[c] = kEmpty;
     }
     shark<int32_t>(h, self, kEnergy) = energy;
     shark<int32_t>(h, self, kAge) = breed ? 0 : age;
@@ -209,10 +326,12 @@ struct SharkMove {
 struct FishEaten {
   static constexpr uint32_t kKind = 74;
   static constexpr bool kDeletesOnlyThis = true;
+  static constexpr uint32_t kPhases = 0;  // counted by FishMove
   using Args = Sea;
   template <class H>
   static __device__ bool run(const H& h, uint32_t, uint32_t self, const Args& a) {
-    return a.kind[fish<uint32_t>(h, self, kPos)] != kIsFish;
+    const Spot p = spot(a, fish<uint32_t>(h, self, kPos));
+    return a.kind[byte_at(a, p.x, p.y)] != kIsFish;
   }
 };
 
@@ -243,27 +362,36 @@ struct SharkRead {
   }
 };
 
-__global__ void tick_kernel(Sea a) { a.step[0] += 1; }
-
-// Creates the objects of the initial sea, in cell order.
+// Creates the objects of the initial sea, in cell order: four cells of a row
+// of cells per lane, so that one request of a wavefront serves 256.
+constexpr uint32_t kInitCells = 4;
 template <uint32_t LG>
 __global__ void wator_init_kernel(DevHeapW<LG> h, Sea a, const int32_t* kind, const int32_t* age, const int32_t* energy,
                                   uint32_t step0) {
-  const uint64_t n = (uint64_t)a.side * a.side;
-  const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c == 0) a.step[0] = step0;
-  if (c >= n) return;
-  const int32_t k = kind[c];
-  a.kind[c] = (uint8_t)k;
-  a.req[c] = ~0ull;
-  new_many(h, kFish, k == kIsFish ? 1u : 0u, [&](uint32_t, uint32_t o) {
+  const uint32_t n = a.side * a.side;  // at most 2^30
+  const uint32_t c0 = (blockIdx.x * blockDim.x + threadIdx.x) * kInitCells;
+  if (c0 == 0) *a.clock = StepClock{step0 - 1u, 2u};  // the step's enumeration advances it
+  uint32_t fishes = 0, sharks = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < kInitCells; ++i) {
+    const uint32_t c = c0 + i;
+    if (c >= n) continue;
+    const int32_t k = kind[c];
+    const uint32_t y = row_of(c, a.side, a.inverse);
+    a.kind[byte_at(a, c - y * a.side, y)] = (uint8_t)k;
+    fishes |= k == kIsFish ? 1u << i : 0u;
+    sharks |= k == kIsShark ? 1u << i : 0u;
+  }
+  new_many(h, kFish, (uint32_t)__popc(fishes), [&](uint32_t i, uint32_t o) __attribute__((always_inline)) {
     if (o == kNull) return;
+    const uint32_t c = c0 + nth_direction(fishes, i);
     fish<uint32_t>(h, o, kPos) = c;
     fish<int32_t>(h, o, kAge) = age[c];
     fish<uint32_t>(h, o, kFTarget) = kNone;
   });
-  new_many(h, kShark, k == kIsShark ? 1u : 0u, [&](uint32_t, uint32_t o) {
+  new_many(h, kShark, (uint32_t)__popc(sharks), [&](uint32_t i, uint32_t o) __attribute__((always_inline)) {
     if (o == kNull) return;
+    const uint32_t c = c0 + nth_direction(sharks, i);
     shark<uint32_t>(h, o, kPos) = c;
     shark<int32_t>(h, o, kAge) = age[c];
     shark<int32_t>(h, o, kEnergy) = energy[c];
@@ -276,7 +404,8 @@ __global__ void wator_read_kernel(Sea a, int32_t* kind, int32_t* age, int32_t* e
   const uint64_t n = (uint64_t)a.side * a.side;
   const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= n) return;
-  kind[c] = a.kind[c];
+  const uint32_t y = row_of(c, a.side, a.inverse);
+  kind[c] = a.kind[byte_at(a, c - y * a.side, y)];
   age[c] = 0;
   energy[c] = 0;
 }
@@ -306,23 +435,22 @@ struct dsoar_wator {
 
 namespace {
 
+size_t round256(uint64_t b) { return (size_t)((b + 255) / 256 * 256); }
+
 int wator_one_step(dsoar_wator* w, uint32_t flags, hipStream_t st) {
   dsoar_heap* h = w->heap;
-  const uint32_t base = flags & DSOAR_DO_PLAIN, reuse = base | DSOAR_DO_REUSE_ENUM;
-  // Decide creates and deletes nothing, so Move reuses its list; the newborns
-  // of a Move are not visited by it (snapshot semantics).
-  int rc = launch_doall<FishDecide>(h, kFish, w->a, base, st);
+  const uint32_t reuse = (flags & DSOAR_DO_PLAIN) | DSOAR_DO_REUSE_ENUM;
+  // The fish phase neither creates nor deletes sharks, so both lists hold from
+  // the start; the newborns of a Move are not visited by it (snapshot
+  // semantics).
+  const uint64_t n = (uint64_t)w->a.side * w->a.side;
+  int rc = launch_enumerate_pair(h, kFish, kShark, st, w->a.clock, (uint4*)w->a.want, (uint32_t)(round256(n) / 16));
+  if (!rc) rc = launch_doall<FishDecide>(h, kFish, w->a, reuse, st);
   if (!rc) rc = launch_doall<FishMove>(h, kFish, w->a, reuse, st);
-  if (!rc) rc = launch_doall<SharkDecide>(h, kShark, w->a, base, st);
+  if (!rc) rc = launch_doall<SharkDecide>(h, kShark, w->a, reuse, st);
   if (!rc) rc = launch_doall<SharkMove>(h, kShark, w->a, reuse, st);
-  if (!rc) rc = launch_doall<FishEaten>(h, kFish, w->a, base, st);
-  if (rc) return rc;
-  launch_timed(w->heap, kKindWatorTick, tick_kernel, dim3(1), dim3(1), st, w->a);
-  DSOAR_LAUNCHED(h);
-  return DSOAR_OK;
+  return rc;
 }
-
-size_t round256(uint64_t b) { return (size_t)((b + 255) / 256 * 256); }
 
 }  // namespace
 
@@ -350,10 +478,11 @@ int dsoar_wator_create(dsoar_heap* heap, uint32_t side, const dsoar_wator_rules*
   const uint64_t n = (uint64_t)side * side;
   uint8_t* b = (uint8_t*)dev_mem;
   w->heap = heap;
-  w->a.step = (uint32_t*)b;
+  w->a.clock = (StepClock*)b;
   w->a.kind = b + 256;
-  w->a.req = (uint64_t*)(b + 256 + round256(n));
+  w->a.want = b + 256 + round256(n);
   w->a.side = side;
+  w->a.inverse = inverse_of(side);
   w->a.seed = rules->seed;
   w->a.fish_breed = rules->fish_breed;
   w->a.shark_breed = rules->shark_breed;
@@ -375,7 +504,7 @@ int dsoar_wator_init(dsoar_wator* w, const int32_t* kind_dev, const int32_t* age
   const uint64_t n = (uint64_t)w->a.side * w->a.side;
   with_width(w->heap, [&](auto w_) {
     constexpr uint32_t kLG = decltype(w_)::value;
-    launch_timed(w->heap, kKindWatorInit, wator_init_kernel<kLG>, dim3((uint32_t)((n + 255) / 256)), dim3(256), (hipStream_t)stream,
+    launch_timed(w->heap, kKindWatorInit, wator_init_kernel<kLG>, dim3((uint32_t)((n + 256 * kInitCells - 1) / (256 * kInitCells))), dim3(256), (hipStream_t)stream,
                      DevHeapW<kLG>(w->heap->dev), w->a, kind_dev, age_dev, energy_dev, step0);
   });
   DSOAR_LAUNCHED(w->heap);
@@ -388,13 +517,15 @@ int dsoar_wator_step(dsoar_wator* w, uint32_t steps, uint32_t flags, void* strea
   dsoar_heap* h = w->heap;
   if (flags & DSOAR_GRAPH) {
     if (flags & DSOAR_DO_PLAIN) return DSOAR_ERR_INVALID_ARG;
-    return step_graphs_run(h, w->graphs, steps, st, [&](hipStream_t gs) { return wator_one_step(w, 0, gs); });
-  }
-  for (uint32_t i = 0; i < steps; ++i) {
-    const int rc = wator_one_step(w, flags, st);
+    const int rc = step_graphs_run(h, w->graphs, steps, st, [&](hipStream_t gs) { return wator_one_step(w, 0, gs); });
     if (rc) return rc;
+  } else {
+    for (uint32_t i = 0; i < steps; ++i) {
+      const int rc = wator_one_step(w, flags, st);
+      if (rc) return rc;
+    }
   }
-  return DSOAR_OK;
+  return steps ? launch_doall<FishEaten>(h, kFish, w->a, flags & DSOAR_DO_PLAIN, st) : DSOAR_OK;
 }
 
 int dsoar_wator_read(dsoar_wator* w, int32_t* kind_dev, int32_t* age_dev, int32_t* energy_dev, void* stream) {

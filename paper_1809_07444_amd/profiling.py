@@ -53,7 +53,8 @@ PLAIN_KIND = [
     ("sugar_admit_kernel", "", "sugar_admit"), ("entry_kernel", "", "traffic_entry"),
     ("traffic_step_kernel", "", "traffic_entry"), ("traffic_init_kernel", "", "traffic_init"),
     ("force_kernel", "", "collide_force"), ("collide_init_kernel", "", "collide_init"),
-    ("wator_init_kernel", "", "wator_init"), ("tick_kernel", "Sea", "wator_tick"),
+    ("wator_init_kernel", "", "wator_init"),
+    ("tick_kernel", "Sea", "wator_tick"),  # of earlier traces
 ]
 
 
