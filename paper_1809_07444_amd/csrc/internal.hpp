@@ -646,7 +646,7 @@ __device__ __forceinline__ void doall_list(const H& h, uint32_t type, const uint
 // emptied at one place in the code, between filling it from the claims of the
 // entries in hand (as many as fit) and going on, so the allocation path is
 // there once.
-template <class Method, bool kOnlyThis, class H>
+template <class Method, bool kOnlyThis, bool kRun = false, class H>
 __device__ __forceinline__ void doall_items(const H& h, uint32_t type, const uint32_t* __restrict__ R,
                                             const uint64_t* __restrict__ S, uint32_t count, uint32_t gw, uint32_t nw,
                                             const typename Method::Args& args, uint32_t& visits, uint32_t& freed) {
@@ -702,9 +702,13 @@ __device__ __forceinline__ void doall_items(const H& h, uint32_t type, const uin
   const bool pairs = wide && count >= 2 * nw;
   const uint32_t sh = (uint32_t)__builtin_ctz(c), per = pairs ? 2u : 64u >> sh;
   // The first entry, loaded before the count is known (as in doall_list).
-  const uint32_t first = gw < h.num_blocks ? gw : h.num_blocks - 1;
-  const uint32_t first_bid = R[first];
-  const uint64_t first_snap = S[first];
+  uint32_t first_bid = 0;
+  uint64_t first_snap = 0;
+  if constexpr (!kRun) {
+    const uint32_t first = gw < h.num_blocks ? gw : h.num_blocks - 1;
+    first_bid = R[first];
+    first_snap = S[first];
+  }
   uint32_t n = 0;  // items in the queue
   for (uint64_t e0 = (uint64_t)per * gw; e0 < count; e0 += (uint64_t)per * nw) {
     const uint32_t e = (uint32_t)e0;
@@ -727,8 +731,9 @@ __device__ __forceinline__ void doall_items(const H& h, uint32_t type, const uin
       Method::template find<2>(h, type, self, live, args, found, del);
     } else {
       if (wide) {
-        bid[0] = e == gw ? first_bid : R[e];
-        snap[0] = e == gw ? first_snap : S[e];
+        const bool have = !kRun && e == gw;
+        bid[0] = have ? first_bid : R[e];
+        snap[0] = have ? first_snap : S[e];
       } else {
         const uint32_t mine = e + (lane >> sh);
         slot = lane & (c - 1u);
@@ -843,7 +848,10 @@ doall_kernel(DevHeapW<LG> h, uint32_t type, const uint32_t* __restrict__ R,
       const uint32_t x = blockIdx.x & 7u, count = bcast32(*count_ptr);
       const uint32_t lo = (uint32_t)(((uint64_t)count * x) >> 3), hi = (uint32_t)(((uint64_t)count * (x + 1)) >> 3);
       const uint32_t gw = (blockIdx.x >> 3) * wpb + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-      doall_list<Method, kOnlyThis, true>(h, type, R + lo, S + lo, hi - lo, gw, nw >> 3, args, visits, freed);
+      if constexpr (HasItems<Method>::value)
+        doall_items<Method, kOnlyThis, true>(h, type, R + lo, S + lo, hi - lo, gw, nw >> 3, args, visits, freed);
+      else
+        doall_list<Method, kOnlyThis, true>(h, type, R + lo, S + lo, hi - lo, gw, nw >> 3, args, visits, freed);
       doall_count<Method>(h, type, visits, freed);
       return;
     }

@@ -320,39 +320,70 @@ struct Request {
   }
 };
 
+// What a child is made from (inverted words: they are left in LDS, where later
+// kernels read search hints).
+struct Child {
+  uint32_t not_p, not_wid, not_give;
+};
+
+// The winners' children are queued, so a wavefront's entries share one chain
+// of allocation atomics (50 -> 38 us for 1.05 M agents of 2048^2).
 struct Birth {
   static constexpr uint32_t kKind = 44;
   static constexpr bool kXcdRuns = true;
   static constexpr uint32_t kMinWaves = 8;
   using Args = Grid;
-  template <class H>
-  static __device__ bool run(const H& h, uint32_t, uint32_t self, const Args& g) {
-    const uint32_t n = af<uint32_t>(h, self, kTarget);
-    const uint32_t p = af<uint32_t>(h, self, kPos);
-    const uint32_t wid = af<uint32_t>(h, self, kWorld);
-    const bool wins = n != kNull && __hip_atomic_load(g.breq + n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == p;
-    int32_t give = 0;
-    if (wins) {
-      const int32_t sugar = af<int32_t>(h, self, kSugar);
-      give = sugar / 2;
-      af<int32_t>(h, self, kSugar) = sugar - give;
-      __hip_atomic_store(g.breq + n, kInf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  using Item = Child;
+  static constexpr uint32_t kItemType = kAgent;
+  static constexpr uint32_t kItems = 128, kClaimBits = 2;
+  struct Found {
+    uint32_t claims;  // bit u: object u gives birth
+    uint32_t n[2], wid[2], give[2];
+  };
+  template <uint32_t N, class H>
+  static __device__ __forceinline__ void find(const H& h, uint32_t, const uint32_t (&self)[2], const bool (&lv)[2],
+                                              const Args& g, Found& found, bool (&)[2]) {
+    uint32_t p[N], asked[N];
+    bool asks[N];
+#pragma unroll
+    for (uint32_t u = 0; u < N; ++u) {
+      found.n[u] = af<uint32_t>(h, self[u], kTarget);
+      p[u] = af<uint32_t>(h, self[u], kPos);
+      found.wid[u] = af<uint32_t>(h, self[u], kWorld);
+      asks[u] = lv[u] && found.n[u] != kNull;
     }
-    new_many(h, kAgent, wins ? 1u : 0u, [&](uint32_t, uint32_t o) {
-      if (o == kNull) return;
-      const uint64_t seed = g.w_seed[wid];
-      const uint32_t t = g.w_step[wid], local = n - g.w_off[wid];
-      af<int32_t>(h, o, kSugar) = give;
-      af<int32_t>(h, o, kMetab) = uniform_int(hash4(seed, kStreamChildMetab, t, local), 1, 4);
-      af<int32_t>(h, o, kVision) = uniform_int(hash4(seed, kStreamChildVision, t, local), 1, 6);
-      af<int32_t>(h, o, kAge) = 0;
-      af<uint32_t>(h, o, kPos) = n;
-      af<uint32_t>(h, o, kTarget) = kNull;
-      af<uint32_t>(h, o, kWorld) = wid;
-      const uint32_t b = byte_here(where(g, wid, n));
-      g.sugar[b] = (uint8_t)(g.sugar[b] | kOccupied);
-    });
-    return false;
+#pragma unroll
+    for (uint32_t u = 0; u < N; ++u) {
+      asked[u] = kNull;
+      if (asks[u]) asked[u] = __hip_atomic_load(g.breq + found.n[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < N; ++u) {
+      if (!asks[u] || asked[u] != p[u]) continue;
+      const int32_t sugar = af<int32_t>(h, self[u], kSugar), give = sugar / 2;
+      found.give[u] = (uint32_t)give;
+      af<int32_t>(h, self[u], kSugar) = sugar - give;
+      __hip_atomic_store(g.breq + found.n[u], kInf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      found.claims |= 1u << u;
+    }
+  }
+  static __device__ __forceinline__ Item item(const Found& f, uint32_t b) {
+    return {~(b ? f.n[1] : f.n[0]), ~(b ? f.wid[1] : f.wid[0]), ~(b ? f.give[1] : f.give[0])};
+  }
+  template <class H>
+  static __device__ __forceinline__ void make(const H& h, const Args& g, const Item& it, uint32_t o) {
+    const uint32_t n = ~it.not_p, wid = ~it.not_wid;
+    const uint64_t seed = g.w_seed[wid];
+    const uint32_t t = g.w_step[wid], local = n - g.w_off[wid];
+    af<int32_t>(h, o, kSugar) = (int32_t)~it.not_give;
+    af<int32_t>(h, o, kMetab) = uniform_int(hash4(seed, kStreamChildMetab, t, local), 1, 4);
+    af<int32_t>(h, o, kVision) = uniform_int(hash4(seed, kStreamChildVision, t, local), 1, 6);
+    af<int32_t>(h, o, kAge) = 0;
+    af<uint32_t>(h, o, kPos) = n;
+    af<uint32_t>(h, o, kTarget) = kNull;
+    af<uint32_t>(h, o, kWorld) = wid;
+    const uint32_t b = byte_here(where(g, wid, n));
+    g.sugar[b] = (uint8_t)(g.sugar[b] | kOccupied);
   }
 };
 
