@@ -62,6 +62,20 @@ micro_create_kernel(DevHeapW<LG> h, uint32_t type, uint32_t n, uint32_t per_lane
   const uint64_t base = wave * (64u * per_lane) + lane;
   uint32_t k = 0;
   for (uint32_t j = 0; j < per_lane; ++j) k += base + j * 64u < n ? 1u : 0u;
+  if constexpr (!kWide) {
+    // One object per lane: its values are on their way while the request runs,
+    // so that the end of the chain of atomics is followed by stores only
+    // (22.8 -> 21.6 us per 21,845 objects).
+    const bool in = base < n;
+    const float x = in ? xs[base] : 0.0f, v = in ? vs[base] : 0.0f;
+    new_many(h, type, k, [&](uint32_t, uint32_t o) {
+      if (o == kNull) return;
+      *field_ptr<int32_t>(h, o, type, kId) = (int32_t)(id_mul * (uint32_t)base);
+      *field_ptr<float>(h, o, type, kX) = x;
+      *field_ptr<float>(h, o, type, kV) = v;
+    });
+    return;
+  }
   new_many(h, type, k, [&](uint32_t j, uint32_t o) {
     if (o == kNull) return;
     const uint32_t i = (uint32_t)(base + j * 64u);
