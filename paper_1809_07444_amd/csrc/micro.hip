@@ -39,14 +39,11 @@ struct MicroCull {
 };
 
 // Object i gets id = id_mul * i and the i-th input values.  A wavefront
-// creates per_lane * 64 consecutive objects, lane l those at offsets l,
-// l + 64, ... (coalesced input reads), as one request of up to per_lane
-// objects per lane: a wavefront asking for four blocks' worth takes them with
-// one atomic on the free bitmap.  Large creations use four per lane (fewer,
-// longer requests); below kCreateWideMin objects one per lane keeps enough
-// wavefronts in flight to hide the allocation latency.
-constexpr uint32_t kCreatePerLane = 4;
-constexpr uint32_t kCreateWideMin = 1u << 22;
+// creates per_lane * 64 consecutive objects as one request (one per lane for
+// small creations, see creations_per_lane) whose r-th object goes to lane
+// r % 64, so that both the inputs read and the slots written are coalesced
+// (four per lane handed out lane by lane took 825 us per creation of 22 to 67 M
+// objects, four this way 530, 16 less than 400).
 constexpr uint32_t kCreateThreads = 256;
 
 // Large creations are compiled for 8 wavefronts per SIMD (the allocation
@@ -57,32 +54,31 @@ template <uint32_t LG, bool kWide>
 __global__ void __attribute__((amdgpu_waves_per_eu(kWide ? 8 : 1)))
 micro_create_kernel(DevHeapW<LG> h, uint32_t type, uint32_t n, uint32_t per_lane, uint32_t id_mul, const float* xs,
                     const float* vs) {
-  const uint32_t lane = threadIdx.x & 63u;
   const uint64_t wave = (uint64_t)blockIdx.x * (kCreateThreads / 64) + (threadIdx.x >> 6);
-  const uint64_t base = wave * (64u * per_lane) + lane;
-  uint32_t k = 0;
-  for (uint32_t j = 0; j < per_lane; ++j) k += base + j * 64u < n ? 1u : 0u;
-  if constexpr (!kWide) {
-    // One object per lane: its values are on their way while the request runs,
-    // so that the end of the chain of atomics is followed by stores only
-    // (22.8 -> 21.6 us per 21,845 objects).
-    const bool in = base < n;
-    const float x = in ? xs[base] : 0.0f, v = in ? vs[base] : 0.0f;
-    new_many(h, type, k, [&](uint32_t, uint32_t o) {
-      if (o == kNull) return;
-      *field_ptr<int32_t>(h, o, type, kId) = (int32_t)(id_mul * (uint32_t)base);
-      *field_ptr<float>(h, o, type, kX) = x;
-      *field_ptr<float>(h, o, type, kV) = v;
-    });
-    return;
-  }
-  new_many(h, type, k, [&](uint32_t j, uint32_t o) {
-    if (o == kNull) return;
-    const uint32_t i = (uint32_t)(base + j * 64u);
+  const uint64_t base = wave * (64u * per_lane);
+  auto fill = [&](uint32_t o, uint32_t i, float x, float v) __attribute__((always_inline)) {
     *field_ptr<int32_t>(h, o, type, kId) = (int32_t)(id_mul * i);
-    *field_ptr<float>(h, o, type, kX) = xs[i];
-    *field_ptr<float>(h, o, type, kV) = vs[i];
-  });
+    *field_ptr<float>(h, o, type, kX) = x;
+    *field_ptr<float>(h, o, type, kV) = v;
+  };
+  if constexpr (kWide) {
+    const uint64_t left = base < n ? n - base : 0u;
+    new_items(h, type, (uint32_t)(left < 64u * per_lane ? left : 64u * per_lane), [&](uint32_t r, uint32_t o)
+              __attribute__((always_inline)) {
+      const uint32_t i = (uint32_t)base + r;
+      if (o != kNull) fill(o, i, xs[i], vs[i]);
+    });
+  } else {
+    // The values are on their way while the request runs, so that the end of
+    // the chain of atomics is followed by stores only (22.8 -> 21.6 us per
+    // 21,845 objects).
+    const uint64_t i = base + (threadIdx.x & 63u);
+    const bool in = i < n;
+    const float x = in ? xs[i] : 0.0f, v = in ? vs[i] : 0.0f;
+    new_many(h, type, in ? 1u : 0u, [&](uint32_t, uint32_t o) {
+      if (o != kNull) fill(o, (uint32_t)i, x, v);
+    });
+  }
 }
 
 bool micro_type_ok(const dsoar_heap* h, uint32_t type) {
@@ -94,7 +90,7 @@ bool micro_type_ok(const dsoar_heap* h, uint32_t type) {
 int launch_create(dsoar_heap* h, uint32_t type, uint32_t n, uint32_t id_mul, const float* xs, const float* vs,
                   hipStream_t s) {
   if (n == 0) return DSOAR_OK;
-  const uint32_t per_lane = n >= kCreateWideMin ? kCreatePerLane : 1u;
+  const uint32_t per_lane = creations_per_lane(h, type, n, n >= 1u << 22 ? 4u : 1u);
   const uint64_t per_block = (uint64_t)kCreateThreads * per_lane;
   with_width(h, [&](auto w_) {
     constexpr uint32_t kLG = decltype(w_)::value;
