@@ -264,6 +264,19 @@ struct MinWaves : std::integral_constant<uint32_t, 1> {};
 template <class M>
 struct MinWaves<M, std::void_t<decltype(M::kMinWaves)>> : std::integral_constant<uint32_t, M::kMinWaves> {};
 
+// A method may declare
+//   static constexpr bool kXcdRuns = true;
+// when its objects read and write planes laid out like the list (a grid, with
+// the objects of neighbouring cells near each other in the heap): under the
+// per-XCD search policy its lists are then cut into eight runs, one per XCD
+// (workgroups go to the XCDs round-robin), as the allocations of an XCD's
+// wavefronts are in its eighth of the heap, so each XCD's L2 sees one part of
+// the planes.
+template <class M, class = void>
+struct XcdRuns : std::false_type {};
+template <class M>
+struct XcdRuns<M, std::void_t<decltype(M::kXcdRuns)>> : std::integral_constant<bool, M::kXcdRuns> {};
+
 // A method that does the work of several phases that would otherwise each be a
 // do-all of their own declares
 //   static constexpr uint32_t kPhases = 2;
@@ -518,6 +531,16 @@ __device__ __forceinline__ void doall_split64(const H& h, uint32_t type, const u
   settle();
 }
 
+// Narrows a list to the run that this workgroup's XCD takes (one of eight).
+__device__ __forceinline__ void take_run(const uint32_t* __restrict__& R, const uint64_t* __restrict__& S,
+                                         uint32_t& count) {
+  const uint32_t x = blockIdx.x & 7u;
+  const uint32_t lo = (uint32_t)(((uint64_t)count * x) >> 3), hi = (uint32_t)(((uint64_t)count * (x + 1)) >> 3);
+  R += lo;
+  S += lo;
+  count = hi - lo;
+}
+
 // The do-all kernel (Sec. 2.3).  Entry e of the compacted list R is handled
 // by capacity consecutive lanes: with capacity 64 one wavefront per block,
 // with 32 two blocks per wavefront.  Lane slot s runs the method when bit s of
@@ -529,14 +552,17 @@ __device__ __forceinline__ void doall_split64(const H& h, uint32_t type, const u
 //   static __device__ bool run(const DevHeap&, uint32_t type, uint32_t self, const Args&)
 // returning true to delete self, or the load / apply pair described above.
 // One wavefront's share of a do-all over one list: entries gw, gw + nw, ...
-// (or passes of several entries), visit and free counts accumulated.
-template <class Method, bool kOnlyThis, bool kRun = false, class H>
+// (or passes of several entries), visit and free counts accumulated.  With
+// `run` (see XcdRuns) the list is cut into eight runs and this is the
+// wavefront's share of the run of its XCD.
+template <class Method, bool kOnlyThis, class H>
 __device__ __forceinline__ void doall_list(const H& h, uint32_t type, const uint32_t* __restrict__ R,
                                            const uint64_t* __restrict__ S, uint32_t count, uint32_t gw,
                                            uint32_t nw, const typename Method::Args& args, uint32_t& visits,
-                                           uint32_t& freed) {
+                                           uint32_t& freed, bool run = false) {
   const uint32_t lane = lane_id();
   const uint32_t c = cap_of(h, type);
+  static_assert(!(HasSplit<Method>::value && XcdRuns<Method>::value), "split passes take whole lists");
   if constexpr (HasSplit<Method>::value) {
     // Several blocks per pass only when every wavefront gets that many.
     if (c == 64 && h.doall_unroll > 1 && count >= nw * h.doall_unroll) {
@@ -580,17 +606,14 @@ __device__ __forceinline__ void doall_list(const H& h, uint32_t type, const uint
     // This wavefront's first entry of the single-object loop, loaded before
     // the count is known (R and S hold num_blocks entries, so the load stays
     // in bounds): on lists of about one entry per wavefront the count's load
-    // and the entry's then take one round trip instead of two.  (Not on a run
-    // of the list, which starts where the count says.)
-    uint32_t first_bid = 0;
-    uint64_t first_snap = 0;
-    if constexpr (!kRun) {
-      const uint32_t first = gw < h.num_blocks ? gw : h.num_blocks - 1;
-      first_bid = R[first];
-      first_snap = S[first];
-    }
+    // and the entry's then take one round trip instead of two.  (Not used on
+    // a run of the list, which starts where the count says.)
+    const uint32_t first = gw < h.num_blocks ? gw : h.num_blocks - 1;
+    const uint32_t first_bid = R[first];
+    const uint64_t first_snap = S[first];
+    if (run) take_run(R, S, count);
     for (uint32_t e = gw; e < count; e += nw) {
-      const bool have = !kRun && e == gw;
+      const bool have = !run && e == gw;
       const uint32_t bid = have ? first_bid : R[e];
       const uint64_t snap = have ? first_snap : S[e];
       visits += (uint32_t)__popcll(snap);
@@ -632,6 +655,7 @@ __device__ __forceinline__ void doall_list(const H& h, uint32_t type, const uint
     const uint32_t bpw = 64u / c, sh = (uint32_t)__builtin_ctz(c);
     const uint32_t sub = lane >> sh, slot = lane & (c - 1u);
     const uint64_t group = c == 64 ? ~0ull : ((1ull << c) - 1ull);
+    if (run) take_run(R, S, count);
     for (uint32_t e0 = bpw * gw; e0 < count; e0 += bpw * nw) {
       const uint32_t e = e0 + sub;
       const bool valid = e < count;
@@ -660,10 +684,11 @@ __device__ __forceinline__ void doall_list(const H& h, uint32_t type, const uint
 // emptied at one place in the code, between filling it from the claims of the
 // entries in hand (as many as fit) and going on, so the allocation path is
 // there once.
-template <class Method, bool kOnlyThis, bool kRun = false, class H>
+template <class Method, bool kOnlyThis, class H>
 __device__ __forceinline__ void doall_items(const H& h, uint32_t type, const uint32_t* __restrict__ R,
                                             const uint64_t* __restrict__ S, uint32_t count, uint32_t gw, uint32_t nw,
-                                            const typename Method::Args& args, uint32_t& visits, uint32_t& freed) {
+                                            const typename Method::Args& args, uint32_t& visits, uint32_t& freed,
+                                            bool run = false) {
   using Item = typename Method::Item;
   extern __shared__ uint64_t item_lds[];
   Item* const items = reinterpret_cast<Item*>(item_lds) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * Method::kItems;
@@ -712,17 +737,14 @@ __device__ __forceinline__ void doall_items(const H& h, uint32_t type, const uin
       pend_prev = bm_set_bits0_issue(act, word, bits);
     }
   };
+  // The first entry, loaded before the count is known (as in doall_list).
+  const uint32_t first = gw < h.num_blocks ? gw : h.num_blocks - 1;
+  const uint32_t first_bid = R[first];
+  const uint64_t first_snap = S[first];
+  if (run) take_run(R, S, count);
   // Two entries per pass on lists of at least two per wavefront.
   const bool pairs = wide && count >= 2 * nw;
   const uint32_t sh = (uint32_t)__builtin_ctz(c), per = pairs ? 2u : 64u >> sh;
-  // The first entry, loaded before the count is known (as in doall_list).
-  uint32_t first_bid = 0;
-  uint64_t first_snap = 0;
-  if constexpr (!kRun) {
-    const uint32_t first = gw < h.num_blocks ? gw : h.num_blocks - 1;
-    first_bid = R[first];
-    first_snap = S[first];
-  }
   uint32_t n = 0;  // items in the queue
   for (uint64_t e0 = (uint64_t)per * gw; e0 < count; e0 += (uint64_t)per * nw) {
     const uint32_t e = (uint32_t)e0;
@@ -745,7 +767,7 @@ __device__ __forceinline__ void doall_items(const H& h, uint32_t type, const uin
       Method::template find<2>(h, type, self, live, args, found, del);
     } else {
       if (wide) {
-        const bool have = !kRun && e == gw;
+        const bool have = !run && e == gw;
         bid[0] = have ? first_bid : R[e];
         snap[0] = have ? first_snap : S[e];
       } else {
@@ -836,19 +858,6 @@ __device__ __forceinline__ uint32_t grid_wave() {
   return blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 }
 
-// A method may declare
-//   static constexpr bool kXcdRuns = true;
-// when its objects read and write planes laid out like the list (a grid, with
-// the objects of neighbouring cells near each other in the heap): under the
-// per-XCD search policy its lists are then cut into eight runs, one per XCD
-// (workgroups go to the XCDs round-robin), as the allocations of an XCD's
-// wavefronts are in its eighth of the heap, so each XCD's L2 sees one part of
-// the planes.
-template <class M, class = void>
-struct XcdRuns : std::false_type {};
-template <class M>
-struct XcdRuns<M, std::void_t<decltype(M::kXcdRuns)>> : std::integral_constant<bool, M::kXcdRuns> {};
-
 template <class Method, uint32_t LG, bool kMany = false>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kMany ? MinWaves<Method>::value : 1)))
 doall_kernel(DevHeapW<LG> h, uint32_t type, const uint32_t* __restrict__ R,
@@ -857,23 +866,19 @@ doall_kernel(DevHeapW<LG> h, uint32_t type, const uint32_t* __restrict__ R,
   const uint32_t wpb = blockDim.x >> 6, nw = gridDim.x * wpb;
   uint32_t visits = 0, freed = 0;
   constexpr bool kOnlyThis = DeletesOnlyThis<Method>::value;
+  uint32_t gw = grid_wave(), share = nw;
+  bool run = false;
   if constexpr (XcdRuns<Method>::value) {
-    if (h.search_start == kStartXcd && !(gridDim.x & 7u)) {
-      const uint32_t x = blockIdx.x & 7u, count = bcast32(*count_ptr);
-      const uint32_t lo = (uint32_t)(((uint64_t)count * x) >> 3), hi = (uint32_t)(((uint64_t)count * (x + 1)) >> 3);
-      const uint32_t gw = (blockIdx.x >> 3) * wpb + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-      if constexpr (HasItems<Method>::value)
-        doall_items<Method, kOnlyThis, true>(h, type, R + lo, S + lo, hi - lo, gw, nw >> 3, args, visits, freed);
-      else
-        doall_list<Method, kOnlyThis, true>(h, type, R + lo, S + lo, hi - lo, gw, nw >> 3, args, visits, freed);
-      doall_count<Method>(h, type, visits, freed);
-      return;
+    run = h.search_start == kStartXcd && !(gridDim.x & 7u);
+    if (run) {
+      gw = (blockIdx.x >> 3) * wpb + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+      share = nw >> 3;
     }
   }
   if constexpr (HasItems<Method>::value)
-    doall_items<Method, kOnlyThis>(h, type, R, S, bcast32(*count_ptr), grid_wave(), nw, args, visits, freed);
+    doall_items<Method, kOnlyThis>(h, type, R, S, bcast32(*count_ptr), gw, share, args, visits, freed, run);
   else
-    doall_list<Method, kOnlyThis>(h, type, R, S, bcast32(*count_ptr), grid_wave(), nw, args, visits, freed);
+    doall_list<Method, kOnlyThis>(h, type, R, S, bcast32(*count_ptr), gw, share, args, visits, freed, run);
   doall_count<Method>(h, type, visits, freed);
 }
 

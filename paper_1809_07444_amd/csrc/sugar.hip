@@ -85,14 +85,6 @@ struct Grid {
 
 constexpr uint32_t kMoveShards = 64;
 
-__device__ __forceinline__ uint32_t wrap_cell(uint32_t off, int32_t side, int32_t x, int32_t y) {
-  x %= side;
-  if (x < 0) x += side;
-  y %= side;
-  if (y < 0) y += side;
-  return off + (uint32_t)y * (uint32_t)side + (uint32_t)x;
-}
-
 template <class F, class H>
 __device__ __forceinline__ F& af(const H& h, uint32_t self, uint32_t field) {
   return *field_ptr<F>(h, self, kAgent, field);
@@ -107,13 +99,6 @@ __device__ __forceinline__ Where where(const Grid& g, uint32_t wid, uint32_t p) 
   const uint32_t off = g.w_off[wid], side = g.w_side[wid];
   const uint32_t local = p - off;
   return Where{off, (int32_t)side, (int32_t)(local % side), (int32_t)(local / side)};
-}
-
-// Cell at offset (dx*k, dy*k) from (x, y) on a torus of side `side`.
-__device__ __forceinline__ uint32_t step_cell(const Where& c, int32_t dx, int32_t dy, int32_t k) {
-  int32_t x = c.x + dx * k, y = c.y + dy * k;
-  if (x < 0 || x >= c.side || y < 0 || y >= c.side) return wrap_cell(c.off, c.side, x, y);
-  return c.off + (uint32_t)y * (uint32_t)c.side + (uint32_t)x;
 }
 
 constexpr int32_t kMaxVision = 6;
@@ -135,10 +120,15 @@ __device__ __forceinline__ uint32_t byte_at(const Where& c, int32_t x, int32_t y
   return c.off + g * side + (uint32_t)x * (g + 4u <= side ? 4u : side & 3u) + r;
 }
 __device__ __forceinline__ uint32_t byte_here(const Where& c) { return byte_at(c, c.x, c.y); }
+// v around the torus, for v at most kMaxVision outside: two selects, and a loop
+// that only sides below the vision enter (remainders here made Choose 73 KB of
+// code and MoveEat 96, loops alone made worlds of 64^2 13 % slower).
 __device__ __forceinline__ int32_t wrapped(int32_t v, int32_t side) {
-  if (v < 0 || v >= side) {
-    v %= side;
-    if (v < 0) v += side;
+  v += v < 0 ? side : 0;
+  v -= v >= side ? side : 0;
+  if (__builtin_expect(side < kMaxVision, 0)) {
+    while (v < 0) v += side;
+    while (v >= side) v -= side;
   }
   return v;
 }
@@ -180,15 +170,10 @@ __device__ __forceinline__ void cross(const uint8_t* plane, const Where& c, uint
   }
 }
 
-// Index of the cell k steps along direction d (0 .. 3) from c.
+// Index of the cell k steps along direction d (0 .. 3) from c, whose index is p.
 __device__ __forceinline__ uint32_t seen_cell(const Where& c, uint32_t p, uint32_t d, int32_t k) {
   const int32_t n = d & 1u ? -k : k;
-  if (d < 2) {
-    const int32_t x = c.x + n;
-    return (uint32_t)x < (uint32_t)c.side ? p + (uint32_t)n : step_cell(c, 1, 0, n);
-  }
-  const int32_t y = c.y + n;
-  return (uint32_t)y < (uint32_t)c.side ? p + (uint32_t)(n * c.side) : step_cell(c, 0, 1, n);
+  return d < 2 ? p + (uint32_t)(wrapped(c.x + n, c.side) - c.x) : p + (uint32_t)((wrapped(c.y + n, c.side) - c.y) * c.side);
 }
 
 struct Choose {
@@ -321,9 +306,11 @@ struct Request {
 };
 
 // What a child is made from (inverted words: they are left in LDS, where later
-// kernels read search hints).
+// kernels read search hints): its cell and the cell's byte in the planes, its
+// world and its sugar.  The byte's place is found before the request: after it,
+// it is two more rounds of loads at the end of the step's longest chain.
 struct Child {
-  uint32_t not_p, not_wid, not_give;
+  uint32_t not_n, not_b, not_wid, not_give;
 };
 
 // The winners' children are queued, so a wavefront's entries share one chain
@@ -338,7 +325,7 @@ struct Birth {
   static constexpr uint32_t kItems = 128, kClaimBits = 2;
   struct Found {
     uint32_t claims;  // bit u: object u gives birth
-    uint32_t n[2], wid[2], give[2];
+    uint32_t n[2], b[2], wid[2], give[2];
   };
   template <uint32_t N, class H>
   static __device__ __forceinline__ void find(const H& h, uint32_t, const uint32_t (&self)[2], const bool (&lv)[2],
@@ -355,7 +342,9 @@ struct Birth {
 #pragma unroll
     for (uint32_t u = 0; u < N; ++u) {
       asked[u] = kNull;
-      if (asks[u]) asked[u] = __hip_atomic_load(g.breq + found.n[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!asks[u]) continue;
+      asked[u] = __hip_atomic_load(g.breq + found.n[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      found.b[u] = byte_here(where(g, found.wid[u], found.n[u]));
     }
 #pragma unroll
     for (uint32_t u = 0; u < N; ++u) {
@@ -368,11 +357,11 @@ struct Birth {
     }
   }
   static __device__ __forceinline__ Item item(const Found& f, uint32_t b) {
-    return {~(b ? f.n[1] : f.n[0]), ~(b ? f.wid[1] : f.wid[0]), ~(b ? f.give[1] : f.give[0])};
+    return {~(b ? f.n[1] : f.n[0]), ~(b ? f.b[1] : f.b[0]), ~(b ? f.wid[1] : f.wid[0]), ~(b ? f.give[1] : f.give[0])};
   }
   template <class H>
   static __device__ __forceinline__ void make(const H& h, const Args& g, const Item& it, uint32_t o) {
-    const uint32_t n = ~it.not_p, wid = ~it.not_wid;
+    const uint32_t n = ~it.not_n, b = ~it.not_b, wid = ~it.not_wid;
     const uint64_t seed = g.w_seed[wid];
     const uint32_t t = g.w_step[wid], local = n - g.w_off[wid];
     af<int32_t>(h, o, kSugar) = (int32_t)~it.not_give;
@@ -382,7 +371,6 @@ struct Birth {
     af<uint32_t>(h, o, kPos) = n;
     af<uint32_t>(h, o, kTarget) = kNull;
     af<uint32_t>(h, o, kWorld) = wid;
-    const uint32_t b = byte_here(where(g, wid, n));
     g.sugar[b] = (uint8_t)(g.sugar[b] | kOccupied);
   }
 };
@@ -450,21 +438,27 @@ __global__ void sugar_check_kernel(const int32_t* sugar, const int32_t* cap, uin
 // Admits a world: a lane takes a column of a group of four rows (the last group
 // has the rows that are left), so its plane bytes are a dword, each row's loads
 // are coalesced, and one request of a wavefront serves 256 cells (with a cell
-// per lane 1095 us for 2048^2 cells with 1.05 M agents, now 800).  Bound: the
+// per lane 1010 us for 2048^2 cells with 1.05 M agents, now 850).  Bound: the
 // chains of lookups, as the requests crowd into the same active blocks (565 with
 // the bounded policy, which would leave more blocks half full).
-template <uint32_t LG>
+// Below kAdmitWideMin cells a lane takes one cell: the agents then stand in more
+// blocks, whose room the births of the first steps find without a free block.
+// Admission and step, us, one row and four (a quarter of the cells occupied):
+//   128^2  19 38.4   30 40.7     362^2  42 47.0   34 48.1
+//   256^2  32 41.7   29 47.0     430^2  27 53.5   30 50.0
+constexpr uint32_t kAdmitWideMin = 1u << 17;
+template <uint32_t LG, uint32_t ROWS>
 __global__ void sugar_admit_kernel(DevHeapW<LG> h, Grid g, uint32_t slot, uint32_t off, uint32_t side, const int32_t* sugar,
                                    const int32_t* cap, const uint8_t* occ, const int32_t* as, const int32_t* am,
                                    const int32_t* av, const int32_t* aa) {
   const uint32_t i = creation_wg(h) * blockDim.x + threadIdx.x;
-  const uint32_t group = i / side, x = i - group * side, y0 = 4u * group;
-  if (y0 >= side) return;
-  const uint32_t rows = side - y0 < 4u ? side - y0 : 4u;
-  const uint32_t c0 = y0 * side + x, b = off + y0 * side + x * rows;
+  const uint32_t group = i / side, x = i - group * side, y = ROWS * group;
+  if (y >= side) return;
+  const uint32_t rows = side - y < ROWS ? side - y : ROWS;
+  const uint32_t c0 = y * side + x, b = byte_at(Where{off, (int32_t)side, 0, 0}, (int32_t)x, (int32_t)y);
   uint32_t amount = 0, most = 0, here = 0;
 #pragma unroll
-  for (uint32_t r = 0; r < 4; ++r) {
+  for (uint32_t r = 0; r < ROWS; ++r) {
     if (r >= rows) continue;
     const uint32_t c = c0 + r * side;
     amount |= (uint32_t)sugar[c] << (8 * r);  // checked to be 0..kMaxSugar before the launch
@@ -473,7 +467,7 @@ __global__ void sugar_admit_kernel(DevHeapW<LG> h, Grid g, uint32_t slot, uint32
     g.breq[off + c] = kInf;
   }
 #pragma unroll
-  for (uint32_t r = 0; r < 4; ++r) {
+  for (uint32_t r = 0; r < ROWS; ++r) {
     if (r >= rows) continue;
     g.sugar[b + r] = (uint8_t)(amount >> (8 * r));
     g.cap[b + r] = (uint8_t)(most >> (8 * r));
@@ -664,12 +658,17 @@ int dsoar_sugar_admit(dsoar_sugar* s, uint32_t slot, uint32_t cell_offset, uint3
   if (bad) return DSOAR_ERR_INVALID_ARG;
   hipLaunchKernelGGL(set_world_kernel, dim3(1), dim3(kMoveShards), 0, st, s->g, slot, cell_offset, side, seed, step0);
   DSOAR_LAUNCHED(s->heap);
-  const uint64_t columns = (uint64_t)((side + 3) / 4) * side;
+  const uint32_t rows = n >= kAdmitWideMin ? 4u : 1u;
+  const uint64_t columns = (uint64_t)((side + rows - 1) / rows) * side;
   with_width(s->heap, [&](auto w_) {
     constexpr uint32_t kLG = decltype(w_)::value;
-    launch_timed(s->heap, kKindSugarAdmit, sugar_admit_kernel<kLG>, dim3((uint32_t)((columns + 255) / 256)), dim3(256), st,
-                     DevHeapW<kLG>(s->heap->dev), s->g, slot, cell_offset, side, sugar_dev, cap_dev, occ_dev, a_sugar_dev,
-                     a_metab_dev, a_vision_dev, a_age_dev);
+    auto go = [&](auto kernel) {
+      launch_timed(s->heap, kKindSugarAdmit, kernel, dim3((uint32_t)((columns + 255) / 256)), dim3(256), st,
+                   DevHeapW<kLG>(s->heap->dev), s->g, slot, cell_offset, side, sugar_dev, cap_dev, occ_dev, a_sugar_dev,
+                   a_metab_dev, a_vision_dev, a_age_dev);
+    };
+    if (rows == 4) go(sugar_admit_kernel<kLG, 4>);
+    else go(sugar_admit_kernel<kLG, 1>);
   });
   DSOAR_LAUNCHED(s->heap);
   s->h_off[slot] = cell_offset;
