@@ -488,37 +488,102 @@ __global__ void sugar_admit_kernel(DevHeapW<LG> h, Grid g, uint32_t slot, uint32
   });
 }
 
-// Readout of one world: its cells' sugar, and its agents' fields by cell (a
-// do-all over all agents fills the occupied cells that the kernel zeroed).
-struct ReadArgs {
-  uint32_t slot, off;
+// Readout of one world: which agent stands in a cell is in the agents alone, so
+// wavefronts go through the heap's agents, four blocks per unit (a lane takes the
+// allocated bits of one unit, so a wavefront sees 64 units per round), and those
+// of the world write their fields to its cells.  Beside them, in the same launch,
+// the first cell_wgs workgroups write the cells' sugar and occupancy, and zeros
+// where no agent stands.  From kReadWideMin cells on (kHandles) the agents write
+// their handles only, into the caller's a_sugar, and a second launch takes the
+// fields from there, cell by cell: fields stored one by one from many wavefronts
+// are part lines.  us per call, with an enumeration, a do-all and a clearing
+// kernel, in one launch and in two:
+//   64^2 alone           13.6   5.8   7.7     1024^2 alone           29.5  18.2  15.9
+//   128^2, one of 256    15.0   5.7   8.2     2048^2 alone           61    56    41
+//   384^2, one of 8      14.8   6.8   9.0     512^2, one of 64       22.9  16.9  14.9
+// (a call on small worlds cannot take less than 5.7: the launch).
+constexpr uint32_t kKindSugarRead = 48;
+constexpr uint32_t kReadUnit = 4;
+constexpr uint32_t kReadWideMin = 1u << 18;
+struct ReadOut {
+  uint32_t slot, off, n;
+  int32_t* sugar;
   uint8_t* occ;
-  int32_t *sugar, *metab, *vision, *age;
+  int32_t *a_sugar, *a_metab, *a_vision, *a_age;
 };
 
-struct AgentRead {
-  static constexpr uint32_t kKind = 48;
-  static constexpr uint32_t kPhases = 0;  // no phase of a step: its visits are not counted
-  using Args = ReadArgs;
-  template <class H>
-  static __device__ bool run(const H& h, uint32_t, uint32_t self, const Args& a) {
-    if (af<uint32_t>(h, self, kWorld) != a.slot) return false;
-    const uint32_t c = af<uint32_t>(h, self, kPos) - a.off;
-    a.occ[c] = 1;
-    a.sugar[c] = af<int32_t>(h, self, kSugar);
-    a.metab[c] = af<int32_t>(h, self, kMetab);
-    a.vision[c] = af<int32_t>(h, self, kVision);
-    a.age[c] = af<int32_t>(h, self, kAge);
-    return false;
+template <uint32_t LG, bool kHandles>
+__global__ void __launch_bounds__(256) sugar_read_kernel(DevHeapW<LG> h, Grid g, ReadOut o, uint32_t cell_wgs) {
+  if (blockIdx.x < cell_wgs) {
+    const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= o.n) return;
+    const int32_t v = g.sugar[byte_here(where(g, o.slot, o.off + c))];
+    o.sugar[c] = sugar_of(v);
+    o.occ[c] = (v & kOccupied) ? 1 : 0;
+    if (!(v & kOccupied)) o.a_sugar[c] = o.a_metab[c] = o.a_vision[c] = o.a_age[c] = 0;
+    return;
   }
-};
+  const uint32_t lane = lane_id(), wpb = blockDim.x >> 6, waves = (gridDim.x - cell_wgs) * wpb;
+  const uint32_t wave = (blockIdx.x - cell_wgs) * wpb + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const Bitmap allocated = allocated_bm(h, kAgent);
+  const uint32_t units = (h.num_blocks + kReadUnit - 1) / kReadUnit;
+  const uint32_t c = cap_of(h, kAgent), sh = (uint32_t)__builtin_ctz(c), bpw = 64u >> sh;  // blocks per wavefront
+  const uint32_t sub = lane >> sh, slot = lane & (c - 1u);
+  for (uint64_t u0 = wave; u0 < units; u0 += 64ull * waves) {
+    // The first unit's object bitmaps are on their way before its allocated bits are known.
+    const uint32_t ahead = (uint32_t)u0 * kReadUnit + lane;
+    const uint64_t early = lane < kReadUnit && ahead < h.num_blocks ? meta_load(h.obj_bitmap + ahead) : 0ull;
+    const uint64_t mine = u0 + (uint64_t)lane * waves;
+    uint32_t have = 0;
+    if (mine < units) have = (uint32_t)(meta_load(allocated.group((uint32_t)(mine >> 4))) >> (kReadUnit * (mine & 15u))) & 15u;
+    uint64_t todo = __ballot(have != 0);
+    while (todo) {
+      const uint32_t l = (uint32_t)__builtin_ctzll(todo);
+      todo &= todo - 1ull;
+      const uint32_t first = ((uint32_t)u0 + l * waves) * kReadUnit, bits = (uint32_t)__builtin_amdgcn_readlane(have, l);
+      uint64_t mask = 0;
+      if (lane < kReadUnit && ((bits >> lane) & 1u)) mask = l == 0 ? early : meta_load(h.obj_bitmap + first + lane);
+      uint32_t self[kReadUnit], world[kReadUnit];
+#pragma unroll
+      for (uint32_t i = 0; i < kReadUnit; ++i) {
+        const uint32_t j = i * bpw + sub;
+        const uint64_t m = __shfl(mask, (int)(j & 63u));
+        self[i] = make_obj(first + j, slot);
+        world[i] = kNull;
+        if (j < kReadUnit && ((m >> slot) & 1ull)) world[i] = af<uint32_t>(h, self[i], kWorld);
+      }
+#pragma unroll
+      for (uint32_t i = 0; i < kReadUnit; ++i) {
+        if (world[i] != o.slot) continue;
+        const uint32_t at = af<uint32_t>(h, self[i], kPos) - o.off;
+        if (kHandles) {
+          if (at < o.n) o.a_sugar[at] = (int32_t)self[i];
+          continue;
+        }
+        const int32_t sugar = af<int32_t>(h, self[i], kSugar), metab = af<int32_t>(h, self[i], kMetab);
+        const int32_t vision = af<int32_t>(h, self[i], kVision), age = af<int32_t>(h, self[i], kAge);
+        if (at >= o.n) continue;
+        o.a_sugar[at] = sugar;
+        o.a_metab[at] = metab;
+        o.a_vision[at] = vision;
+        o.a_age[at] = age;
+      }
+    }
+  }
+}
 
-__global__ void sugar_read_kernel(Grid g, ReadArgs a, uint32_t n, int32_t* sugar) {
+__global__ void sugar_read_cells_kernel(DevHeap h, Grid g, ReadOut o) {
   const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= n) return;
-  sugar[c] = sugar_of(g.sugar[byte_here(where(g, a.slot, a.off + c))]);
-  a.occ[c] = 0;
-  a.sugar[c] = a.metab[c] = a.vision[c] = a.age[c] = 0;
+  if (c >= o.n) return;
+  const int32_t v = g.sugar[byte_here(where(g, o.slot, o.off + c))];
+  const uint32_t self = (uint32_t)o.a_sugar[c];  // no handle where no agent stands
+  const bool here = (v & kOccupied) && (self >> 6) < h.num_blocks && (self & 63u) < cap_of(h, kAgent);
+  o.sugar[c] = sugar_of(v);
+  o.occ[c] = (v & kOccupied) ? 1 : 0;
+  o.a_sugar[c] = here ? af<int32_t>(h, self, kSugar) : 0;
+  o.a_metab[c] = here ? af<int32_t>(h, self, kMetab) : 0;
+  o.a_vision[c] = here ? af<int32_t>(h, self, kVision) : 0;
+  o.a_age[c] = here ? af<int32_t>(h, self, kAge) : 0;
 }
 
 bool sugar_heap_ok(const dsoar_heap* h) {
@@ -693,11 +758,22 @@ int dsoar_sugar_read_world(dsoar_sugar* s, uint32_t slot, int32_t* sugar_dev, ui
     return DSOAR_ERR_INVALID_ARG;
   hipStream_t st = (hipStream_t)stream;
   const uint32_t n = s->h_side[slot] * s->h_side[slot];
-  const ReadArgs r{slot, s->h_off[slot], occ_dev, a_sugar_dev, a_metab_dev, a_vision_dev, a_age_dev};
-  hipLaunchKernelGGL(sugar_read_kernel, dim3((n + 255) / 256), dim3(256), 0, st, s->g, r, n, sugar_dev);
+  const ReadOut r{slot, s->h_off[slot], n, sugar_dev, occ_dev, a_sugar_dev, a_metab_dev, a_vision_dev, a_age_dev};
+  const bool handles = n >= kReadWideMin;
+  const uint32_t cells = (n + 255) / 256, units = (s->heap->dev.num_blocks + kReadUnit - 1) / kReadUnit;
+  const uint32_t cell_wgs = handles ? 0u : cells, agent_wgs = std::min((units + 3) / 4, s->heap->num_cus * 8);
+  with_width(s->heap, [&](auto w_) {
+    constexpr uint32_t kLG = decltype(w_)::value;
+    auto go = [&](auto kernel) {
+      launch_timed(s->heap, kKindSugarRead, kernel, dim3(cell_wgs + agent_wgs), dim3(256), st, DevHeapW<kLG>(s->heap->dev),
+                   s->g, r, cell_wgs);
+    };
+    if (handles) go(sugar_read_kernel<kLG, true>);
+    else go(sugar_read_kernel<kLG, false>);
+  });
+  if (handles)
+    launch_timed(s->heap, kKindSugarRead, sugar_read_cells_kernel, dim3(cells), dim3(256), st, s->heap->dev, s->g, r);
   DSOAR_LAUNCHED(s->heap);
-  const int rc = launch_doall<AgentRead>(s->heap, kAgent, r, DSOAR_DO_PERSISTENT, st);
-  if (rc) return rc;
   if (moves) {
     uint64_t m[kMoveShards];
     DSOAR_HIP(s->heap, hipMemcpyAsync(m, s->g.w_moves + (uint64_t)slot * kMoveShards, sizeof(m), hipMemcpyDeviceToHost, st));

@@ -32,7 +32,7 @@ METHOD_KIND = {
     "AlivePrep": "gol_alive_prep", "AliveStep": "gol_alive_prep", "CandStep": "gol_update",
     "MicroUpdate": "micro_update", "MicroCull": "micro_cull",
     "Choose": "sugar_choose", "Eat": "sugar_eat", "MoveEat": "sugar_eat", "Request": "sugar_request",
-    "Birth": "sugar_birth", "AgentRead": "sugar_read", "VisitCount": "visit_count", "DeleteIfMod": "delete_if_mod",
+    "Birth": "sugar_birth", "VisitCount": "visit_count", "DeleteIfMod": "delete_if_mod",
     "FieldGather": "gather", "GolDeleteWorld": "gol_delete_world", "SugarDeleteWorld": "sugar_delete_world",
     "BodyForce": "collide_force", "BodyMove": "collide_move", "BodyRoot": "collide_root",
     "BodyTarget": "collide_target", "BodyMerge": "collide_merge", "FishDecide": "wator_fish_decide",
@@ -50,7 +50,8 @@ METHOD2_KIND = {("AliveUpdate", "CandUpdate"): "gol_update"}
 PLAIN_KIND = [
     ("micro_create_kernel", "", "micro_create"), ("gol_init_kernel", "", "gol_init"),
     ("gol_admit_kernel", "", "gol_admit"), ("regrow_kernel", "", "sugar_regrow"),
-    ("sugar_admit_kernel", "", "sugar_admit"), ("entry_kernel", "", "traffic_entry"),
+    ("sugar_admit_kernel", "", "sugar_admit"), ("sugar_read_kernel", "", "sugar_read"),
+    ("sugar_read_cells_kernel", "", "sugar_read"), ("entry_kernel", "", "traffic_entry"),
     ("traffic_step_kernel", "", "traffic_entry"), ("traffic_init_kernel", "", "traffic_init"),
     ("force_kernel", "", "collide_force"), ("collide_init_kernel", "", "collide_init"),
     ("wator_init_kernel", "", "wator_init"),
