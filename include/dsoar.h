@@ -537,11 +537,13 @@ int dsoar_sugar_read(dsoar_sugar* sugar, int32_t* sugar_dev, uint8_t* occ_dev, i
  * `roads` open single-lane roads of `length` cells: Car objects {cell, speed,
  * next speed} (type 0 of the heap: at least three 4-byte fields) advance by
  * the model's rules; cars enter at a road's first cell and are deleted when
- * they pass its last cell.  Per step, in one kernel: every car's speed is decided
+ * they pass its last cell.  Per step: every car's speed is decided
  * (accelerate, brake to the empty cells ahead, dawdle with probability
  * p_slow24 / 2^24 from hash(seed, 32, cell, t)), the cars move (visits count
  * both phases), and a car enters each empty first cell with probability p_in24 /
- * 2^24 from hash(seed, 33, road, t) (the hash of the workload generator). */
+ * 2^24 from hash(seed, 33, road, t) (the hash of the workload generator): in
+ * one kernel on heaps of this type alone with a slot per cell and per road,
+ * else the entries after the moves. */
 typedef struct dsoar_traffic dsoar_traffic;
 typedef struct {
   int32_t vmax;      /* top speed, 1 .. 8 */
