@@ -107,8 +107,8 @@ __device__ __forceinline__ float pair_scale_normal(float r2, float m) {
 // per pair, a reciprocal root counting four), the chains' latency on small
 // ones.  With one wavefront per 64 bodies for everything, 4096 bodies kept 64
 // of the chip's 1024 SIMDs busy with a chain of about 45 slots per pair: 307 us
-// per step; now 37, and 65,536 bodies 4.93 -> 2.76 ms (6.1e9 -> 1.55e12 pairs
-// a second and 8.7e11 -> 1.55e12).  Tiles of 64 bodies cost a barrier twice as
+// per step; now 37, and 65,536 bodies 4.93 -> 2.76 ms (5.5e10 -> 4.5e11 pairs a
+// second and 8.7e11 -> 1.55e12).  Tiles of 64 bodies cost a barrier twice as
 // often (4096 bodies 47, 65,536 2.98 ms), tiles of 256 leave room for two
 // workgroups per CU (4.4 ms); two makers leave SIMDs idle (65,536: 3.1 ms),
 // eight wait for the chains (3.4 ms).
@@ -407,7 +407,11 @@ struct BodyTarget {
 
 // Merge and removal.  A body that merges is read by its root alone (T names
 // it), which marks it dead once it has its values; other roots may pass it in
-// a chain, where only its link counts for them.
+// a chain, where only its link counts for them.  Up to kScanMerge bodies a scan
+// of T is shorter than the walks, of which a root takes one more than it absorbs
+// (us, scan and walks: 64 bodies 4.2 and 6.8, 400 5.5 and 8.4, 1000 9.5 and 10.4,
+// 1500 12.3 and 9.6, 4096 24 and 11).
+constexpr uint32_t kScanMerge = 1024;
 struct BodyMerge {
   static constexpr uint32_t kKind = 64;
   static constexpr uint32_t kPhases = 2;
@@ -435,7 +439,7 @@ struct BodyMerge {
       absorbed = true;
     };
     bool left = root;
-    if (have_cells(a)) {
+    if (n > kScanMerge && have_cells(a)) {
       // The bodies merging into this root, in increasing id order: each walk
       // finds the lowest id from `lo` on.
       bool on = root;
