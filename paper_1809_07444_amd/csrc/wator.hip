@@ -362,18 +362,23 @@ struct SharkRead {
   }
 };
 
-// Creates the objects of the initial sea, in cell order: four cells of a row
-// of cells per lane, so that one request of a wavefront serves 256.
-constexpr uint32_t kInitCells = 4;
-template <uint32_t LG>
+// Creates the objects of the initial sea, in cell order, a cell per lane or, from
+// kInitWideMin cells on, four of a row, so that one request of a wavefront serves
+// 256.  Smaller seas keep the shorter chains, and their animals stand in blocks
+// with more room for the first births.  us of the initial sea, and of it and 20
+// steps, one cell and four (35 % of the cells taken):
+//   64^2   17   787    23   823      724^2   73  1441    61  1570
+//   256^2  24   964    30  1001      2048^2 455  5120   324  4867
+constexpr uint64_t kInitWideMin = 1u << 19;
+template <uint32_t LG, uint32_t CELLS>
 __global__ void wator_init_kernel(DevHeapW<LG> h, Sea a, const int32_t* kind, const int32_t* age, const int32_t* energy,
                                   uint32_t step0) {
   const uint32_t n = a.side * a.side;  // at most 2^30
-  const uint32_t c0 = (blockIdx.x * blockDim.x + threadIdx.x) * kInitCells;
+  const uint32_t c0 = (blockIdx.x * blockDim.x + threadIdx.x) * CELLS;
   if (c0 == 0) *a.clock = StepClock{step0 - 1u, 2u};  // the step's enumeration advances it
   uint32_t fishes = 0, sharks = 0;
 #pragma unroll
-  for (uint32_t i = 0; i < kInitCells; ++i) {
+  for (uint32_t i = 0; i < CELLS; ++i) {
     const uint32_t c = c0 + i;
     if (c >= n) continue;
     const int32_t k = kind[c];
@@ -504,8 +509,13 @@ int dsoar_wator_init(dsoar_wator* w, const int32_t* kind_dev, const int32_t* age
   const uint64_t n = (uint64_t)w->a.side * w->a.side;
   with_width(w->heap, [&](auto w_) {
     constexpr uint32_t kLG = decltype(w_)::value;
-    launch_timed(w->heap, kKindWatorInit, wator_init_kernel<kLG>, dim3((uint32_t)((n + 256 * kInitCells - 1) / (256 * kInitCells))), dim3(256), (hipStream_t)stream,
-                     DevHeapW<kLG>(w->heap->dev), w->a, kind_dev, age_dev, energy_dev, step0);
+    const uint32_t cells = n >= kInitWideMin ? 4u : 1u;
+    auto go = [&](auto kernel) {
+      launch_timed(w->heap, kKindWatorInit, kernel, dim3((uint32_t)((n + 256 * cells - 1) / (256 * cells))), dim3(256),
+                   (hipStream_t)stream, DevHeapW<kLG>(w->heap->dev), w->a, kind_dev, age_dev, energy_dev, step0);
+    };
+    if (cells == 4) go(wator_init_kernel<kLG, 4>);
+    else go(wator_init_kernel<kLG, 1>);
   });
   DSOAR_LAUNCHED(w->heap);
   return DSOAR_OK;
