@@ -189,15 +189,14 @@ int read_count(dsoar_heap* h, uint32_t type, hipStream_t s, uint32_t* count);
 // Objects per lane of a creation of n objects: longer requests serve more
 // objects per chain of atomics, shorter ones keep more wavefronts in flight.
 // us for n objects in an empty heap, and for n / 3 in the holes of a full one,
-// with 1, 4 and 16 per lane (lines at 2^18 and 2^20 objects):
+// with 1, 4 and 16 per lane (lines at four_from and 2^20 objects):
 //   2^17  28 31   19 34   18 50      2^20   62  86   40  68   21  66
 //   2^18  34 38   20 38   17 54      2^24  326 217  108 187   70 124
 // Under the other policies and a bulk_min, whose rules go by the request, its
-// length stays `otherwise`: with 16 per lane twice as many of the last 2 % of
-// a full heap's slots were missed by a bounded type.
-inline uint32_t creations_per_lane(const dsoar_heap* h, uint32_t type, uint32_t n, uint32_t otherwise) {
+// length stays `otherwise`.
+inline uint32_t creations_per_lane(const dsoar_heap* h, uint32_t type, uint32_t n, uint32_t four_from, uint32_t otherwise) {
   if (((h->dev.fresh_types | h->dev.bounded_types) >> type & 1u) || h->dev.bulk_min != 0xFFFFFFFFu) return otherwise;
-  return n >= 1u << 20 ? 16u : n >= 1u << 18 ? 4u : 1u;
+  return n >= 1u << 20 ? 16u : n >= four_from ? 4u : 1u;
 }
 
 // A method may split into a load phase and an apply phase:

@@ -63,7 +63,7 @@ micro_create_kernel(DevHeapW<LG> h, uint32_t type, uint32_t n, uint32_t per_lane
   };
   if constexpr (kWide) {
     const uint64_t left = base < n ? n - base : 0u;
-    new_items(h, type, (uint32_t)(left < 64u * per_lane ? left : 64u * per_lane), [&](uint32_t r, uint32_t o)
+    new_items<true>(h, type, (uint32_t)(left < 64u * per_lane ? left : 64u * per_lane), [&](uint32_t r, uint32_t o)
               __attribute__((always_inline)) {
       const uint32_t i = (uint32_t)base + r;
       if (o != kNull) fill(o, i, xs[i], vs[i]);
@@ -75,7 +75,7 @@ micro_create_kernel(DevHeapW<LG> h, uint32_t type, uint32_t n, uint32_t per_lane
     const uint64_t i = base + (threadIdx.x & 63u);
     const bool in = i < n;
     const float x = in ? xs[i] : 0.0f, v = in ? vs[i] : 0.0f;
-    new_many(h, type, in ? 1u : 0u, [&](uint32_t, uint32_t o) {
+    new_many<true>(h, type, in ? 1u : 0u, [&](uint32_t, uint32_t o) {
       if (o != kNull) fill(o, (uint32_t)i, x, v);
     });
   }
@@ -90,7 +90,7 @@ bool micro_type_ok(const dsoar_heap* h, uint32_t type) {
 int launch_create(dsoar_heap* h, uint32_t type, uint32_t n, uint32_t id_mul, const float* xs, const float* vs,
                   hipStream_t s) {
   if (n == 0) return DSOAR_OK;
-  const uint32_t per_lane = creations_per_lane(h, type, n, n >= 1u << 22 ? 4u : 1u);
+  const uint32_t per_lane = creations_per_lane(h, type, n, 1u << 18, n >= 1u << 22 ? 4u : 1u);
   const uint64_t per_block = (uint64_t)kCreateThreads * per_lane;
   with_width(h, [&](auto w_) {
     constexpr uint32_t kLG = decltype(w_)::value;
