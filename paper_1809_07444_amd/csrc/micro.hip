@@ -90,7 +90,7 @@ bool micro_type_ok(const dsoar_heap* h, uint32_t type) {
 int launch_create(dsoar_heap* h, uint32_t type, uint32_t n, uint32_t id_mul, const float* xs, const float* vs,
                   hipStream_t s) {
   if (n == 0) return DSOAR_OK;
-  const uint32_t per_lane = creations_per_lane(h, type, n, 1u << 18, n >= 1u << 22 ? 4u : 1u);
+  const uint32_t per_lane = creations_per_lane(h, type, n, 1u << 19, n >= 1u << 22 ? 4u : 1u);
   const uint64_t per_block = (uint64_t)kCreateThreads * per_lane;
   with_width(h, [&](auto w_) {
     constexpr uint32_t kLG = decltype(w_)::value;
