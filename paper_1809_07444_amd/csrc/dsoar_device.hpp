@@ -934,15 +934,17 @@ __device__ __forceinline__ uint32_t search_start(const H& h) {
 // either.  Descents also fail where others have just filled the blocks below (one
 // in ten of 3.8 M objects' slots left: 4,011 objects were refused), so requests
 // of more than 64, which would give up all that they still want, and those of
-// kernels that only create (kPatient), where room that is found empty is not
-// coming back, end when the bitmap's top reads empty.  Others may be waiting for
-// slots that are deleted in the same kernel, which no request is promised.
-template <bool kPatient, class Hand, class H>
+// kernels that delete no object of the type (kPatient), where room that is found
+// full is not coming back, end when the bitmap's top reads empty.  Others may be
+// waiting for slots that are deleted in the same kernel, which no request is
+// promised.
+// Repeated searches stay in the XCD's part of the heap, but for kernels that do
+// nothing but create (kRoams): those fill it and would crowd into its last blocks
+// (alloc_n of 236,000 into halves of blocks of 32: 55 us, 107 with every repeat
+// kept there).
+template <bool kPatient, bool kRoams, class Hand, class H>
 __device__ __forceinline__ void new_core(const H& h, uint32_t type, uint32_t n, Hand&& hand) {
-  // Repeated searches stay in the XCD's part of the heap, but for kernels that
-  // only create: those fill it and would crowd into its last blocks (alloc_n of
-  // 236,000 into halves of blocks of 32: 55 us, 107 with every repeat kept there).
-  const uint32_t keep = kPatient ? 0u : h.search_keep;
+  const uint32_t keep = kRoams ? 0u : h.search_keep;
   const bool patient = kPatient || n > 64;
   const Bitmap active = active_bm(h, type);
   Bitmap free_blocks = free_bm(h);
@@ -1214,7 +1216,7 @@ __device__ __forceinline__ void new_core(const H& h, uint32_t type, uint32_t n, 
   if (fails) lead_add(sh + kCntFindFails, fails);
 }
 
-template <bool kPatient = false, class F, class H>
+template <bool kPatient = false, bool kRoams = false, class F, class H>
 __device__ __forceinline__ void new_many(const H& h, uint32_t type, uint32_t k, F&& f) {
   uint32_t prefix = 0, n = 0;
 #pragma unroll
@@ -1224,7 +1226,7 @@ __device__ __forceinline__ void new_many(const H& h, uint32_t type, uint32_t k, 
     n += (uint32_t)__popcll(m) << b;
   }
   if (n == 0) return;
-  new_core<kPatient>(h, type, n, [&](uint32_t from, uint32_t cnt, auto&& obj_of) __attribute__((always_inline)) {
+  new_core<kPatient, kRoams>(h, type, n, [&](uint32_t from, uint32_t cnt, auto&& obj_of) __attribute__((always_inline)) {
     const uint32_t lo = prefix > from ? prefix : from;
     const uint32_t hi = prefix + k < from + cnt ? prefix + k : from + cnt;
     for (uint32_t r = lo; r < hi; ++r) f(r - prefix, obj_of(r - from));
@@ -1235,11 +1237,11 @@ __device__ __forceinline__ void new_many(const H& h, uint32_t type, uint32_t k, 
 // every lane active: f(r, obj) is called by lane r % 64 for the r-th of them.
 // Where the requests of a wavefront are a queue of items, this spreads them
 // evenly over the lanes, and neighbouring lanes write neighbouring slots.
-template <bool kPatient = false, class F, class H>
+template <bool kPatient = false, bool kRoams = false, class F, class H>
 __device__ __forceinline__ void new_items(const H& h, uint32_t type, uint32_t n, F&& f) {
   if (n == 0) return;
   const uint32_t lane = lane_id();
-  new_core<kPatient>(h, type, n, [&](uint32_t from, uint32_t cnt, auto&& obj_of) __attribute__((always_inline)) {
+  new_core<kPatient, kRoams>(h, type, n, [&](uint32_t from, uint32_t cnt, auto&& obj_of) __attribute__((always_inline)) {
     for (uint32_t r = from + ((lane - from) & 63u); r < from + cnt; r += 64) f(r, obj_of(r - from));
   });
 }

@@ -600,11 +600,11 @@ __global__ void alloc_n_kernel(DevHeapW<LG> h, uint32_t type, uint32_t n, uint32
     const uint64_t step = (uint64_t)gridDim.x * (blockDim.x >> 6) * per_wave;
     const uint32_t wave = blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (uint64_t i = wave * per_wave; i < n; i += step)
-      new_items<true>(h, type, (uint32_t)(n - i < per_wave ? n - i : per_wave), [&](uint32_t r, uint32_t o)
+      new_items<true, true>(h, type, (uint32_t)(n - i < per_wave ? n - i : per_wave), [&](uint32_t r, uint32_t o)
                 __attribute__((always_inline)) { out[i + r] = o; });
   } else {
     for (uint64_t i = first_item(); i < n; i += item_stride())
-      new_many<true>(h, type, 1, [&](uint32_t, uint32_t o) { out[i] = o; });
+      new_many<true, true>(h, type, 1, [&](uint32_t, uint32_t o) { out[i] = o; });
   }
 }
 

@@ -319,7 +319,7 @@ struct Prunes<M, std::void_t<decltype(M::kPrunes)>> : std::integral_constant<boo
 // The queue lives in LDS and is made into objects when it is full and at the
 // end of the wavefront's list, so one chain of allocation atomics serves
 // several entries, and the lanes share the new objects evenly whichever lane
-// asked for them.
+// asked for them.  The method deletes no object of the items' type.
 template <class M, class = void>
 struct HasItems : std::false_type {};
 template <class M>
@@ -835,7 +835,7 @@ __device__ __forceinline__ void doall_items(const H& h, uint32_t type, const uin
       __builtin_amdgcn_wave_barrier();
       settle();
       settle_active();
-      new_items(h, Method::kItemType, n, [&](uint32_t r, uint32_t o) __attribute__((always_inline)) {
+      new_items<true>(h, Method::kItemType, n, [&](uint32_t r, uint32_t o) __attribute__((always_inline)) {
         if (o != kNull) Method::make(h, args, items[r], o);
       });
       __builtin_amdgcn_wave_barrier();

@@ -63,7 +63,7 @@ micro_create_kernel(DevHeapW<LG> h, uint32_t type, uint32_t n, uint32_t per_lane
   };
   if constexpr (kWide) {
     const uint64_t left = base < n ? n - base : 0u;
-    new_items<true>(h, type, (uint32_t)(left < 64u * per_lane ? left : 64u * per_lane), [&](uint32_t r, uint32_t o)
+    new_items<true, true>(h, type, (uint32_t)(left < 64u * per_lane ? left : 64u * per_lane), [&](uint32_t r, uint32_t o)
               __attribute__((always_inline)) {
       const uint32_t i = (uint32_t)base + r;
       if (o != kNull) fill(o, i, xs[i], vs[i]);
@@ -75,7 +75,7 @@ micro_create_kernel(DevHeapW<LG> h, uint32_t type, uint32_t n, uint32_t per_lane
     const uint64_t i = base + (threadIdx.x & 63u);
     const bool in = i < n;
     const float x = in ? xs[i] : 0.0f, v = in ? vs[i] : 0.0f;
-    new_many<true>(h, type, in ? 1u : 0u, [&](uint32_t, uint32_t o) {
+    new_many<true, true>(h, type, in ? 1u : 0u, [&](uint32_t, uint32_t o) {
       if (o != kNull) fill(o, (uint32_t)i, x, v);
     });
   }

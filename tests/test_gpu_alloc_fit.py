@@ -6,9 +6,13 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
+import numpy as np  # noqa: E402
+import oracle  # noqa: E402
 import torch  # noqa: E402
 from paper_1809_07444_amd import _capi as C  # noqa: E402
+from paper_1809_07444_amd import apps  # noqa: E402
 from paper_1809_07444_amd.heap import Heap  # noqa: E402
+from synth import workloads as W  # noqa: E402
 
 
 def holes(blocks, capacity, every, search=C.SEARCH_HASHED, policy=C.POLICY_DENSE, width=64, spare=0):
@@ -63,3 +67,17 @@ def test_more_than_the_room(blocks, every, search):
     assert torch.unique(torch.cat([left, got])).numel() == blocks * 64
     h.free_n(got)
     assert h.stats(raise_sticky=False)["live"] == [left.numel()] and set(h.check()) == {"sticky"}
+
+
+# Three blocks per 64 cells is what serving reserves for a world (3,072 and 768 here).
+@pytest.mark.parametrize("side,blocks,capacity", [(256, 3072, 64), (256, 5500, 32), (128, 768, 64), (1024, 45000, 64)])
+def test_a_game_of_life_in_its_budget(side, blocks, capacity):
+    g = W.gol_grid(side, side, seed=1, threshold24=1 << 22)
+    want = oracle.gol_run(g, 20)[0]
+    for _ in range(4):
+        gol = apps.GameOfLife([g], capacity=capacity, num_blocks=blocks)
+        gol.init()
+        gol.step(20)
+        assert gol.heap.stats()["oom"] == 0
+        assert np.array_equal(gol.read()[0], want)
+        gol.close()
