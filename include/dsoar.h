@@ -43,7 +43,7 @@ extern "C" {
 typedef enum {
   DSOAR_OK = 0,
   DSOAR_ERR_INVALID_ARG = -1,  /* bad size, type, field or pointer */
-  DSOAR_ERR_OOM = -2,          /* a device new found no free block (sticky) */
+  DSOAR_ERR_OOM = -2,          /* a device new found no room (sticky) */
   DSOAR_ERR_RETRY_LIMIT = -3,  /* a bounded device retry loop gave up (sticky) */
   DSOAR_ERR_HIP = -4,          /* a HIP runtime call failed */
   DSOAR_ERR_DOUBLE_FREE = -5,  /* delete of a slot that was not allocated (sticky) */
@@ -243,11 +243,10 @@ int dsoar_heap_set_unroll(dsoar_heap* heap, uint32_t blocks_per_pass);
  * Kinds: 1 enumeration; do-alls 10 visit count, 11 delete-if-mod, 12 gather,
  * 20/21 micro update/cull, 30/35 Game of Life, the Alive and the Candidate
  * objects (34 world deletion), 40 and 42..45 Sugarscape choose, move and eat,
- * request, birth and world deletion, 48 readout, 60..64 collisions, 70..76
- * wa-tor; other kernels 22 micro creation, 36/37 Game of Life initial cells
- * and admission, 46/47 Sugarscape regrow and admission, 52/53 traffic step and
- * initial cars, 66 collisions initial bodies, 77/78 wa-tor initial sea and
- * step tick. */
+ * request, birth and world deletion, 60..64 collisions, 70..76 wa-tor; other
+ * kernels 22 micro creation, 36/37 Game of Life initial cells and admission,
+ * 46..48 Sugarscape regrow, admission and readout, 52/53 traffic step and
+ * initial cars, 66 collisions initial bodies, 77 wa-tor initial sea. */
 int dsoar_heap_set_timing(dsoar_heap* heap, int enable);
 int dsoar_heap_timing(dsoar_heap* heap, uint32_t* kinds, uint32_t* counts, double* total_ms,
                       uint32_t max_kinds, uint32_t* num_kinds);
@@ -416,13 +415,14 @@ int dsoar_probe_copy(const void* src_dev, void* dst_dev, size_t bytes, void* str
  * square tori, one or many worlds in one heap.  The heap must declare, in
  * this order, Cell {int32 alive}, Alive {int32 cell, int32 world, int32
  * action} and Candidate {int32 cell, int32 world, int32 action}.  One
- * generation is four do-alls (Alive, Candidate, Alive, Candidate); Candidate
- * and Alive objects are created and deleted with device new/delete. */
+ * generation is two do-alls (Alive, then Candidate), each of two phases, on two
+ * planes of live bits; Candidate and Alive objects are created and deleted with
+ * device new/delete. */
 typedef struct dsoar_gol dsoar_gol;
 #define DSOAR_GRAPH 0x100u     /* capture one generation (step) once into a HIP graph
                                   and replay it (needs a non-default stream) */
 #define DSOAR_GOL_GRAPH DSOAR_GRAPH
-/* Device bytes for the world table and the cell index (0 if invalid).  sides:
+/* Device bytes for the world table, the cell index and the planes (0 if invalid).  sides:
  * host array of num_worlds side lengths (1..65535, total cells < 2^32). */
 size_t dsoar_gol_bytes(uint32_t num_worlds, const uint32_t* sides);
 /* World w's cell (x, y) has global index off[w] + y*side[w] + x, off being
@@ -588,8 +588,7 @@ typedef struct {
   float r2_merge; /* merge radius squared, >= 0 */
   uint32_t reserved;
 } dsoar_collide_params;
-/* Device bytes for n body ids (0 if n is 0 or above 2^24). */
-/* Device bytes for n bodies: the least dsoar_collide_create takes, and the same
+/* Device bytes for n bodies (0 if n is 0 or above 2^24): the least dsoar_collide_create takes, and the same
  * with a table of cells (16 to 32 bytes more per body) through which the merge
  * phases find near bodies; with less they compare every pair. */
 size_t dsoar_collide_bytes(uint32_t n);
