@@ -377,6 +377,9 @@ __device__ __forceinline__ void create_cells(const H& h, const World& w, uint32_
   const uint64_t wave = (uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const uint64_t base = (wave * 64u + lane_id()) * PL;  // this lane's first cell, relative to `first`
   const uint32_t k = base < n ? (uint32_t)(n - base < PL ? n - base : PL) : 0u;
+  // Loaded here: behind the Cells' stores it would wait for them (64^2 cells
+  // 14.6 -> 14.0 us).
+  uint32_t* const plane = plane_at(w, w.clock->epoch);
   uint64_t live = 0;
   if constexpr (PL == 64) {
     if (k == 64 && ((uintptr_t)(grid + base) & 15u) == 0) {
@@ -406,9 +409,9 @@ __device__ __forceinline__ void create_cells(const H& h, const World& w, uint32_
     const_cast<uint32_t*>(w.cells)[first + (uint32_t)(base + j)] = o;
   });
   if constexpr (PL == 64) {
-    if (k) write_live_range(plane_at(w, w.clock->epoch), first + (uint32_t)base, k, live & made);
+    if (k) write_live_range(plane, first + (uint32_t)base, k, live & made);
   } else {
-    write_live_run(plane_at(w, w.clock->epoch), first + (uint32_t)base, k != 0, (live & made) != 0, true);
+    write_live_run(plane, first + (uint32_t)base, k != 0, (live & made) != 0, true);
   }
   new_many(h, kAlive, (uint32_t)__popcll(live), [&](uint32_t r, uint32_t o) {
     if (o == kNull) return;
