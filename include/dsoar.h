@@ -246,7 +246,8 @@ int dsoar_heap_set_unroll(dsoar_heap* heap, uint32_t blocks_per_pass);
  * request, birth and world deletion, 60..64 collisions, 70..76 wa-tor; other
  * kernels 22 micro creation, 36/37 Game of Life initial cells and admission,
  * 46..48 Sugarscape regrow, admission and readout, 52/53 traffic step and
- * initial cars, 66 collisions initial bodies, 77 wa-tor initial sea. */
+ * initial cars, 66 collisions initial bodies, 77 wa-tor initial sea (78, its step tick, is
+ * launched no more). */
 int dsoar_heap_set_timing(dsoar_heap* heap, int enable);
 int dsoar_heap_timing(dsoar_heap* heap, uint32_t* kinds, uint32_t* counts, double* total_ms,
                       uint32_t max_kinds, uint32_t* num_kinds);

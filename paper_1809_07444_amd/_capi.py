@@ -40,7 +40,7 @@ KIND_NAMES = {1: "enumerate", 10: "visit_count", 11: "delete_if_mod", 12: "gathe
               73: "wator_shark_move", 74: "wator_fish_eaten", 75: "wator_fish_read", 76: "wator_shark_read",
               22: "micro_create", 36: "gol_init", 37: "gol_admit", 46: "sugar_regrow", 47: "sugar_admit",
               53: "traffic_init", 66: "collide_init",
-              77: "wator_init"}
+              77: "wator_init", 78: "wator_tick"}
 INV_NAMES = ["bitmap_range", "allocated", "active", "active_implies_allocated", "free",
              "container", "live_count", "free_count"]
 

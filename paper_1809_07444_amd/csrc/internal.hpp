@@ -145,6 +145,7 @@ constexpr uint32_t kKindSugarAdmit = 47;
 constexpr uint32_t kKindTrafficInit = 53;
 constexpr uint32_t kKindCollideInit = 66;
 constexpr uint32_t kKindWatorInit = 77;
+constexpr uint32_t kKindWatorTick = 78;  // of earlier traces: the enumeration advances the step
 
 // Launches `kernel` on stream s.  With timing on (and room in the record), the
 // launch itself carries a start and a stop event (hipExtLaunchKernel): they
